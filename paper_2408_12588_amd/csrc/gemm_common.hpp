@@ -1,0 +1,72 @@
+// Projections of the attention module (paper App. B.5: "qkv proj", "o proj")
+// and of the MLP module: C[M, N] = act(A[M, K] W[N, K]^T + bias[N]),
+// activations and weights bf16, fp32 accumulation on the matrix core, one
+// rounding to bf16 on the way out; act is nothing or the MLP's GELU.
+//
+// Both operands are contiguous along K, which is what the MFMA operands want:
+// with the weight rows as the A operand and the token rows as the B operand a
+// 16 x 16 sub-tile is C^T[n, m], every lane owns one token and 4 of its outputs.
+// Two kernels share the layouts below: gemm_stream.hpp for problems that fill
+// the chip with large tiles, gemm_tile.hpp for the others.
+//
+// Operand layout in LDS.  A stage holds 64 columns of K of a tile's token rows
+// and weight rows, 128 bytes per row = one cache line: with 32 columns (half
+// lines) the same kernel ran at 816 instead of 901 TFLOP/s (25440 x 3456 x
+// 1152), because L2 serves a half line at the price of a whole one.  A copy
+// round of a wavefront (one global -> LDS instruction) is 8 rows; row r's 16-byte
+// chunk q is stored at position q ^ ((r >> 1) & 7).  A 16-byte LDS read is served
+// in four cycles of 16 lanes, lanes {0-3, 12-15, 20-23, 24-27} together, then
+// {4-7, 8-11, 16-19, 28-31}, and the same in the upper half; an operand read
+// (lane = 16 chunk + row) therefore mixes chunk q of rows 0-3, 12-15 with chunk
+// q ^ 1 of rows 4-11, which this permutation sends to 16 different bank groups
+// (bank conflict counter: 0).
+//
+// K may be an odd multiple of 32.  The upper half of the last slice then repeats
+// the lower one in LDS and meets token operands set to zero, or is not computed.
+//
+// Weight rows of a pair of sub-tiles are taken in the order 8 (i >> 2) + 4 u +
+// (i & 3) (sub-tile u, operand row i), so that the two accumulators of a lane are
+// 8 consecutive features, the 16 bytes of a store.
+//
+// Stores.  A lane's 16 bytes belong to token l16, so storing them from the
+// accumulator layout would hand the 16 lanes of a quarter wavefront 16 different
+// rows: that pattern sustains 29 GB/s per CU where consecutive lanes on
+// consecutive 16 bytes of a 128-byte segment reach 76 (288-byte rows 93).  The
+// results therefore take a turn through 2 KB of LDS per wavefront (same swizzle)
+// and leave as 128-byte segments.
+#pragma once
+#include "mfma_util.hpp"
+
+namespace pab {
+
+struct GemmParams {
+  const bf16_t *A;      // [M, K]
+  const bf16_t *W;      // [N, K]
+  const bf16_t *bias;   // [N] or nullptr
+  bf16_t *C;            // feature n of token m goes to C[(n / n_split) * plane_stride + m * ldc + n % n_split]
+  int M, N, K;
+  long long ldc;        // row pitch of C in elements
+  int n_split;          // features per output plane (N: one plane; else a multiple of 8)
+  long long plane_stride;
+  int n_mt, n_nt;       // token / feature tiles (gemm_stream: n_mt full token tiles)
+  int ms_tail;          // gemm_stream: the token rows behind the full tiles are cut into tiles of 64 ms_tail rows
+  int n_units;          // gemm_stream: full tiles (n_mt x n_nt), then tail tiles
+};
+
+// chunk permutation of stage row r
+__device__ __forceinline__ int gemm_swizzle(int r) { return (r >> 1) & 7; }
+
+typedef const __attribute__((address_space(3))) bf16x8 *lds_cptr8;
+typedef __attribute__((address_space(3))) bf16x8 *lds_ptr8;
+typedef __attribute__((address_space(3))) bf16x4 *lds_ptr4;
+__device__ __forceinline__ bf16x8 lds_read8(unsigned addr) { return *(lds_cptr8)(size_t)addr; }
+__device__ __forceinline__ void lds_write8(unsigned addr, bf16x8 v) { *(lds_ptr8)(size_t)addr = v; }
+__device__ __forceinline__ void lds_write4(unsigned addr, bf16x4 v) { *(lds_ptr4)(size_t)addr = v; }
+
+// GELU in its tanh form: 0.5 x (1 + tanh u) = x / (1 + exp(-2u)), u = sqrt(2/pi) (x + 0.044715 x^3)
+__device__ __forceinline__ float gelu(float x) {
+  const float u2 = -2.302208198f * (x + 0.044715f * x * x * x);   // -2 sqrt(2/pi) log2(e) (..)
+  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(u2));
+}
+
+}  // namespace pab

@@ -1,0 +1,274 @@
+// Projection kernel for problems that fill the chip: one persistent workgroup
+// of 8 wavefronts per CU works through tiles of 256 tokens x 32 NS features,
+// 4 wavefronts along the tokens x 2 along the features, 4 x NS sub-tiles each.
+//
+// What bounds it: at full rate a 256 x 256 x 64 step needs 1.07 us of matrix
+// pipe (random operands, power limit; 0.87 us on zeros) and 64 KB from L2,
+// which delivers about 60 GB/s per CU when all CUs ask (1.07 us); it takes 1.42.
+// Against the former 128 x 256 tiles (two workgroups per CU, 32-column stages)
+// L2 traffic per multiply-add is down by a third, LDS operand reads by 40%.
+// Tried and slower: four wavefronts of 128 x 128 (one per SIMD, nothing to cover
+// a wait: 2.4 us per step), two co-resident workgroups of 128 x 192 (901 TFLOP/s
+// at 25440 x 3456 x 1152 against 1065), 32-column stages in a deeper ring.
+//
+// The K slices of all tiles of a workgroup form one stream through two LDS
+// stages.  Inside a slice (2 NS steps of one weight sub-tile x 4 token sub-tiles)
+// operands are read RING - 1 steps ahead of their MFMAs.  RING - 1 steps before the
+// end everything of the slice has been read: there one barrier frees its stage
+// and publishes the other, so that the first operands of the next slice are read
+// behind the last MFMAs of this one, and the copy of the slice after that starts,
+// one round per step (issued together they held up the wavefront's MFMAs).  The
+// copies run across tile borders: a tile's first two slices arrive during the
+// end of the previous tile and its stores.
+//
+// Tiles: full ones of 256 tokens first; the remaining token rows are cut into
+// tiles of 64, 128, 192 or 256 rows, whichever evens out the last round best
+// (25440 x 1152: 400 tiles of 256 x 288 are 1.56 rounds of 256, with 48 x 4 tail
+// tiles of 192 rows 1 + 0.78).  The last tile of either axis is moved back to end
+// at the matrix edge: rows that two tiles compute are written twice with the same
+// bits, and nothing needs a bounds check.
+//
+// NS = 8 (256 features): tiles start on cache lines.  NS = 9 (288): fits hidden
+// sizes that are multiples of 288 (72-element heads in fours) without padding; the
+// odd sub-tile of wave column 1 lies before its pairs, so that all pairs are
+// stored from 64-byte boundaries.
+#pragma once
+#include <type_traits>
+#include "gemm_common.hpp"
+
+namespace pab {
+
+template <int NS, int RING, bool GELU>
+__global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p) {
+  constexpr int BM = 256, BN = 32 * NS, BK = 64;
+  constexpr int STAGE = 128 * (BM + BN);         // bytes: token rows, pair rows of the weights, odd sub-tiles
+  constexpr int NPAIR = NS / 2;
+  constexpr bool ODD = NS % 2 != 0;
+  constexpr int W0 = 128 * BM, W1 = W0 + 128 * 64 * NPAIR;   // byte offsets of the pair rows / odd rows in a stage
+  constexpr int SHIFT1 = ODD ? 16 : 0;           // features of wave column 1 before its pairs
+  constexpr int NDMA = 4 + NPAIR + (ODD ? 1 : 0);   // copy rounds of a wavefront per slice (the last: wavefronts 0-3)
+  constexpr int NJ = 2 * NS, AHEAD = RING - 1, JB = NJ - AHEAD;   // steps per slice, operand distance, barrier step
+  static_assert(NPAIR % 2 == 0, "pairs are stored two at a time");
+  static_assert(NJ % RING == 0 && NDMA <= NJ, "the operand ring continues across slices");
+  constexpr int BIAS = 2 * STAGE, XPOSE = BIAS + 2048;   // byte offsets: two bias rows, 2 KB per wavefront
+
+  __shared__ __attribute__((aligned(16))) unsigned char smem[XPOSE + 8 * 2048];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, q16 = lane >> 4;
+  const int wm = wave >> 1, wn = wave & 1;
+  const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) unsigned char *)smem);
+  const int M = p.M, N = p.N, K = p.K, nk = (K + BK - 1) / BK;
+
+  // ---- the workgroup's tiles: unit i of it is number wg + i * gridDim.x; a round of a full grid gives each XCD 32
+  //      consecutive units, which are 4 token tiles x 8 feature tiles ----
+  struct Tile { int m0, n0, ms; };
+  constexpr int GM = 4;
+  const int n_full = p.n_mt * p.n_nt;
+  auto unit = [&](int u) __attribute__((always_inline)) {
+    Tile t;
+    if (u < n_full) {
+      const int g = u / (GM * p.n_nt), r = u % (GM * p.n_nt), gm = min(GM, p.n_mt - g * GM);   // the last group may be smaller
+      t.m0 = (g * GM + r % gm) * BM; t.n0 = (r / gm) * BN; t.ms = 4;
+    } else {
+      const int r = u - n_full;
+      t.ms = p.ms_tail;
+      t.m0 = min(p.n_mt * BM + (r / p.n_nt) * 64 * t.ms, M - 64 * t.ms); t.n0 = (r % p.n_nt) * BN;
+    }
+    t.n0 = min(t.n0, N - BN);
+    t.m0 = __builtin_amdgcn_readfirstlane(t.m0);
+    t.n0 = __builtin_amdgcn_readfirstlane(t.n0);
+    t.ms = __builtin_amdgcn_readfirstlane(t.ms);
+    return t;
+  };
+  const int wg = gridDim.x == 256 ? (blockIdx.x & 7) * 32 + (blockIdx.x >> 3) : blockIdx.x;
+  const int n_mine = (p.n_units - wg + (int)gridDim.x - 1) / (int)gridDim.x;
+
+  // ---- copies: wavefront w moves rows 8 w .. 8 w + 7 of every 64 rows; its lane row lane >> 3, position lane & 7 ----
+  const int crow = 8 * wave + (lane >> 3);
+  const int cq = (lane & 7) ^ gemm_swizzle(crow);
+  const unsigned vfull_a = (unsigned)(2 * (crow * (long long)K + 8 * cq));
+  // a round of pair rows: 32 of each wave column; row i: sub-tile i >> 4, operand row i & 15
+  const unsigned vfull_w = (unsigned)(2 * (((crow >> 5) * (16 * NS + SHIFT1) + 8 * ((crow & 15) >> 2) + 4 * ((crow >> 4) & 1) +
+                                           (crow & 3)) * (long long)K + 8 * cq));
+  // odd sub-tiles: the last 16 features of wave column 0, the first 16 of column 1
+  const unsigned vfull_s = (unsigned)(2 * (((crow >> 4 ? 16 * NS : 32 * NPAIR) + (crow & 15)) * (long long)K + 8 * cq));
+  int s_tile = 0, s_kt = 0, s_ms = 0;            // the copy stream: tile, slice, its token rows / 64
+  unsigned voff_a = vfull_a, voff_w = vfull_w, voff_s = vfull_s;   // lane offsets of the slice: a half slice repeats columns 0-31
+  bool s_live = false;
+  const bf16_t *s_a = p.A, *s_w = p.W, *s_b = p.bias;
+  auto stream_tile = [&](int i) __attribute__((always_inline)) {
+    const Tile t = unit(wg + i * (int)gridDim.x);
+    s_ms = t.ms;
+    s_a = p.A + (long long)t.m0 * K;
+    s_w = p.W + (long long)t.n0 * K;
+    s_b = p.bias + t.n0;
+  };
+  auto copy_round = [&](int stage, int i) __attribute__((always_inline)) {   // round i of the stream's current slice
+    if (!s_live) return;
+    const unsigned lds = lds0 + STAGE * stage + 1024 * wave;
+    if (i < 4) {
+      if (i < s_ms) dma16_to_lds(s_a + (long long)64 * i * K, voff_a, lds + 8192 * i);
+    } else if (i < 4 + NPAIR) {
+      dma16_to_lds(s_w + (long long)32 * (i - 4) * K, voff_w, lds + W0 + 8192 * (i - 4));
+    } else if (wave < 4) {
+      dma16_to_lds(s_w, voff_s, lds + W1);
+    }
+  };
+  auto next_slice = [&]() __attribute__((always_inline)) {
+    if (!s_live) return;
+    if (s_kt == 0 && p.bias && wave == 7) dma16_to_lds(s_b, 16 * min(lane, BN / 8 - 1), lds0 + BIAS + 1024 * (s_tile & 1));
+    s_a += BK;
+    s_w += BK;
+    if (++s_kt == nk) {
+      s_kt = 0;
+      if (++s_tile < n_mine) stream_tile(s_tile);
+    }
+    if (K & 32) {
+      const unsigned back = s_kt == nk - 1 && cq >= 4 ? 64 : 0;
+      voff_a = vfull_a - back; voff_w = vfull_w - back; voff_s = vfull_s - back;
+    }
+  };
+
+  stream_tile(0);
+  for (int stage = 0; stage < 2; ++stage) {      // the first two slices
+    s_live = s_tile < n_mine;
+#pragma unroll
+    for (int i = 0; i < NDMA; ++i) copy_round(stage, i);
+    next_slice();
+  }
+  s_live = false;
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+  const int sw = gemm_swizzle(l16);
+  const unsigned op = 128 * l16 + 16 * (q16 ^ sw);        // operand address inside 16 rows; columns 32.. : ^ 64
+  int stage = 0;
+
+  auto run_tile = [&](auto ms_tag, const Tile t, int parity) __attribute__((always_inline)) {
+    constexpr int MS = decltype(ms_tag)::value;            // token sub-tiles of a wavefront
+    f32x4 acc[MS][NS];
+    bf16x8 tf[2][MS], wf[RING];                            // token operands of both column halves, ring of weight operands
+    unsigned tb, wb;
+    auto use_stage = [&](int s) __attribute__((always_inline)) {
+      tb = lds0 + STAGE * s + 2048 * MS * wm + op;
+      wb = lds0 + STAGE * s + W0 + 4096 * wn + op;
+    };
+    auto rd_t = [&](int ks, int a) __attribute__((always_inline)) { tf[ks][a] = lds_read8((ks ? tb ^ 64 : tb) + 2048 * a); };
+    auto rd_w = [&](int j) __attribute__((always_inline)) {
+      const int b = j % NS;
+      const unsigned off = b < 2 * NPAIR ? 8192 * (b >> 1) + 2048 * (b & 1) : W1 - W0 - 2048 * wn;
+      return lds_read8((j / NS ? wb ^ 64 : wb) + off);
+    };
+    use_stage(stage);
+#pragma unroll
+    for (int a = 0; a < MS; ++a) rd_t(0, a);
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) wf[j] = rd_w(j);
+#pragma unroll
+    for (int a = 0; a < MS; ++a)
+#pragma unroll
+      for (int b = 0; b < NS; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[a][b][e] = 0.0f;
+
+    for (int kt = 0; kt < nk; ++kt) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if (j == JB) {   // this slice has been read, the next one has arrived
+          asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+          s_live = s_tile < n_mine;
+          stage ^= 1;
+          use_stage(stage);
+#pragma unroll
+          for (int a = 0; a < MS; ++a) rd_t(0, a);
+        }
+        const int d = (j - JB + NJ) % NJ;   // steps since the barrier
+        if (d < NDMA) copy_round(stage ^ 1, d);
+        if (d == NDMA - 1) next_slice();
+        wf[(j + AHEAD) % RING] = rd_w((j + AHEAD) % NJ);
+        if (j >= 1 && j <= MS) rd_t(1, j - 1);
+        if (j == MS && (K & 32) && kt == nk - 1) {
+#pragma unroll
+          for (int a = 0; a < MS; ++a) tf[1][a] = zero8();
+        }
+#pragma unroll
+        for (int a = 0; a < MS; ++a) acc[a][j % NS] = mfma16(wf[j % RING], tf[j / NS][a], acc[a][j % NS]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+
+    // ---- bias, activation, stores: 16 tokens x 64 features at a time through the wavefront's 2 KB ----
+    const int shift = wn ? SHIFT1 : 0, odd = wn ? 0 : 32 * NPAIR;   // where the pairs / the odd sub-tile start
+    const bf16_t *bs = reinterpret_cast<const bf16_t *>(smem + BIAS + 1024 * parity) + wn * 16 * NS;
+    const int f0 = t.n0 + wn * 16 * NS, m0 = t.m0 + wm * 16 * MS;
+    const unsigned xs = lds0 + XPOSE + 2048 * wave;
+    const unsigned xw = xs + 128 * l16, xr = xs + 128 * (lane >> 3) + 16 * ((lane & 7) ^ gemm_swizzle(lane >> 3));
+#pragma unroll
+    for (int h = 0; h < NPAIR / 2; ++h) {
+      float bv[2][8];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        bf16x8 b8 = zero8();
+        if (p.bias) b8 = *reinterpret_cast<const bf16x8 *>(bs + shift + 64 * h + 32 * u + 8 * q16);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bv[u][e] = (float)b8[e];
+      }
+      const int n = f0 + shift + 64 * h + 8 * (lane & 7), plane = n / p.n_split;
+      bf16_t *dst = p.C + plane * p.plane_stride + (n - plane * p.n_split) + (long long)(m0 + (lane >> 3)) * p.ldc;
+#pragma unroll
+      for (int a = 0; a < MS; ++a) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          bf16x8 y;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float x = acc[a][4 * h + 2 * u + (e >> 2)][e & 3] + bv[u][e];
+            y[e] = (bf16_t)(GELU ? gelu(x) : x);
+          }
+          lds_write8(xw + 16 * ((4 * u + q16) ^ sw), y);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const bf16x8 r0 = lds_read8(xr), r1 = lds_read8((xr ^ 64) + 1024);   // rows 8 further: swizzle ^ 4
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        *reinterpret_cast<bf16x8 *>(dst) = r0;
+        *reinterpret_cast<bf16x8 *>(dst + 8 * p.ldc) = r1;
+        dst += 16 * p.ldc;
+      }
+    }
+    if (ODD) {
+      bf16x4 b4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) b4[e] = (bf16_t)0.0f;
+      if (p.bias) b4 = *reinterpret_cast<const bf16x4 *>(bs + odd + 4 * q16);
+      const int n = f0 + odd + 8 * (lane & 1), plane = n / p.n_split;
+      bf16_t *dst = p.C + plane * p.plane_stride + (n - plane * p.n_split) + (long long)(m0 + (lane >> 1)) * p.ldc;
+#pragma unroll
+      for (int a = 0; a < MS; ++a) {
+        bf16x4 y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = acc[a][NS - 1][e] + (float)b4[e];
+          y[e] = (bf16_t)(GELU ? gelu(x) : x);
+        }
+        lds_write4(xs + 32 * (16 * a + l16) + 8 * q16, y);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int a = 0; a < (MS + 1) / 2; ++a) {
+        const bf16x8 r = lds_read8(xs + 1024 * a + 16 * lane);
+        if (2 * a + 1 < MS || lane < 32) *reinterpret_cast<bf16x8 *>(dst + 32 * a * p.ldc) = r;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+  };
+
+  for (int i = 0; i < n_mine; ++i) {
+    const Tile t = unit(wg + i * (int)gridDim.x);
+    if (t.ms == 4) run_tile(std::integral_constant<int, 4>{}, t, i & 1);
+    else if (t.ms == 3) run_tile(std::integral_constant<int, 3>{}, t, i & 1);
+    else if (t.ms == 2) run_tile(std::integral_constant<int, 2>{}, t, i & 1);
+    else run_tile(std::integral_constant<int, 1>{}, t, i & 1);
+  }
+}
+
+}  // namespace pab

@@ -1,0 +1,155 @@
+// Projection kernel for everything that does not fill the chip with the large
+// tiles of gemm_stream.hpp: one workgroup per tile, WM x WN wavefronts of MS x NS
+// sub-tiles, K in slices of 64 columns through a ring of NST LDS stages, copied
+// NST - 1 slices ahead, one barrier per slice.
+//
+// Such a problem is bound by the latency of its K loop, not by a rate: a slice
+// of a lone 64 x 64 tile takes 0.26 us, of a 128 x 128 tile 0.55 us, so the host
+// picks the smallest tile that the L2 traffic allows (about 60 GB/s per CU).
+// 1260 x 576 x 2304: 34.2 us with the former 128 x 256 tiles on 15 CUs, 12.6 us
+// with 180 tiles of 64 x 64; 1260 x 1728 x 576: 14.1 -> 8.7 us.
+#pragma once
+#include <type_traits>
+#include "gemm_common.hpp"
+
+namespace pab {
+
+template <int WM, int WN, int MS, int NS, int NST, bool GELU>
+__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_tile_kernel(const GemmParams p) {
+  constexpr int NW = WM * WN, BM = 16 * MS * WM, BN = 16 * NS * WN, BK = 64;
+  constexpr int ROWS = BM + BN, STAGE = 128 * ROWS;      // bytes
+  constexpr int ROUNDS = ROWS / 8, MYR = ROUNDS / NW, TOKR = BM / 8 / NW;   // copy rounds: all, per wavefront, of token rows
+  constexpr int SEG = NS >= 4 ? 64 : 32;                 // features stored at a time
+  static_assert(ROUNDS % NW == 0 && (BM / 8) % NW == 0, "copy rounds must deal evenly to the wavefronts");
+  static_assert(NS % 2 == 0 && (NS == 2 || NS % 4 == 0), "sub-tiles come in pairs");
+  static_assert(NST >= 2 && NST <= 3 && (NST - 2) * MYR < 16, "vmcnt immediates");
+  static_assert(NW * 2048 <= NST * STAGE, "output staging must fit the ring");
+
+  __shared__ __attribute__((aligned(16))) unsigned char smem[NST * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, q16 = lane >> 4;
+  const int wm = wave / WN, wn = wave % WN;
+  const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) unsigned char *)smem);
+
+  // every XCD takes a contiguous run of tiles, feature tiles of a token tile next to each other
+  const int n_tiles = p.n_mt * p.n_nt, per = (n_tiles + 7) >> 3;
+  const int id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per || id >= n_tiles) return;
+  const int m0 = id / p.n_nt * BM, n0 = id % p.n_nt * BN;
+  const int M = p.M, N = p.N, K = p.K, nk = (K + BK - 1) / BK;
+
+  // round r = wave + NW i: stage rows 8 r .. 8 r + 7, token rows first.  Rows past the matrix re-read its last row; what
+  // they produce is never stored.  LDS row i of a 32-row weight pair: sub-tile i >> 4, operand row i & 15.
+  unsigned voff[MYR];
+  const int cq = (lane & 7) ^ gemm_swizzle(8 * wave + (lane >> 3));   // 8 NW rows further the swizzle is the same
+  static_assert(NW % 2 == 0, "swizzle period of 16 rows");
+#pragma unroll
+  for (int i = 0; i < MYR; ++i) {
+    const int row = 8 * (wave + NW * i) + (lane >> 3);
+    int src;
+    if (i < TOKR) {
+      src = min(m0 + row, M - 1);
+    } else {
+      const int w = row - BM;
+      src = min(n0 + (w & ~31) + 8 * ((w & 15) >> 2) + 4 * ((w >> 4) & 1) + (w & 3), N - 1);
+    }
+    voff[i] = (unsigned)(2 * (src * (long long)K + 8 * cq));
+  }
+  auto issue = [&](int kt, int stage) __attribute__((always_inline)) {
+    const long long k0 = (long long)__builtin_amdgcn_readfirstlane(kt) * BK;
+    const unsigned back = (K & 32) && kt == nk - 1 && cq >= 4 ? 64 : 0;   // a half slice repeats columns 0-31
+#pragma unroll
+    for (int i = 0; i < MYR; ++i)
+      dma16_to_lds((i < TOKR ? p.A : p.W) + k0, voff[i] - back, lds0 + STAGE * stage + 1024 * (wave + NW * i));
+  };
+  const int npre = nk < NST - 1 ? nk : NST - 1;
+  for (int kt = 0; kt < npre; ++kt) issue(kt, kt);
+
+  // accumulators start from the bias: lane's features of sub-tile b are 32 (b / 2) + 8 q16 + 4 (b % 2) + 0..3
+  f32x4 acc[MS][NS];
+#pragma unroll
+  for (int b = 0; b < NS; ++b) {
+    const int n = n0 + wn * 16 * NS + 32 * (b >> 1) + 8 * q16 + 4 * (b & 1);
+    f32x4 bv = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (p.bias && n < N) {
+      const bf16x4 b4 = *reinterpret_cast<const bf16x4 *>(p.bias + n);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bv[e] = (float)b4[e];
+    }
+#pragma unroll
+    for (int a = 0; a < MS; ++a) acc[a][b] = bv;
+  }
+  const int sw = gemm_swizzle(l16);
+  const unsigned op = 128 * l16 + 16 * (q16 ^ sw);
+  const unsigned t_off = 128 * wm * 16 * MS + op, w_off = 128 * (BM + wn * 16 * NS) + op;
+
+  int stage = 0, next = npre % NST;
+  for (int kt = 0; kt < nk; ++kt) {
+    // slice kt has landed (this wavefront's share); one more may be in flight
+    if (NST == 3 && kt + 1 < nk) __builtin_amdgcn_s_waitcnt(0x0F70 | MYR);
+    else __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();                        // ... everyone's share; all are done with slice kt - 1
+    if (kt + NST - 1 < nk) {
+      issue(kt + NST - 1, next);
+      next = next + 1 == NST ? 0 : next + 1;
+    }
+    const unsigned st = lds0 + STAGE * stage;
+    stage = stage + 1 == NST ? 0 : stage + 1;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      if (ks == 1 && (K & 32) && kt == nk - 1) break;
+      bf16x8 tf[MS], wf[NS];
+#pragma unroll
+      for (int a = 0; a < MS; ++a) tf[a] = lds_read8(st + (ks ? t_off ^ 64 : t_off) + 2048 * a);
+#pragma unroll
+      for (int b = 0; b < NS; ++b) wf[b] = lds_read8(st + (ks ? w_off ^ 64 : w_off) + 2048 * b);
+#pragma unroll
+      for (int b = 0; b < NS; ++b)
+#pragma unroll
+        for (int a = 0; a < MS; ++a) acc[a][b] = mfma16(wf[b], tf[a], acc[a][b]);
+    }
+  }
+
+  // ---- activation, stores: 16 tokens x SEG features at a time through 2 KB per wavefront (the ring is free) ----
+  __syncthreads();
+  constexpr int CPR = SEG / 8, RPI = 64 / CPR;           // chunks per row segment, rows per store instruction
+  auto xpos = [](int row, int q) { return SEG == 64 ? q ^ gemm_swizzle(row) : q ^ ((row >> 2) & 2); };
+  const unsigned xs = lds0 + 2048 * wave;
+  const int mw = m0 + wm * 16 * MS;
+#pragma unroll
+  for (int h = 0; h < 16 * NS / SEG; ++h) {
+    const int fw = n0 + wn * 16 * NS + SEG * h;          // first feature of the segment
+    const int n = fw + 8 * (lane % CPR), plane = n / p.n_split;
+    bf16_t *dst = p.C + plane * p.plane_stride + (n - plane * p.n_split);
+#pragma unroll
+    for (int a = 0; a < MS; ++a) {
+#pragma unroll
+      for (int u = 0; u < SEG / 32; ++u) {
+        bf16x8 y;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float x = acc[a][SEG / 16 * h + 2 * u + (e >> 2)][e & 3];
+          y[e] = (bf16_t)(GELU ? gelu(x) : x);
+        }
+        lds_write8(xs + 2 * SEG * l16 + 16 * xpos(l16, 4 * u + q16), y);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int i = 0; i < 16 / RPI; ++i) {
+        const int row = RPI * i + lane / CPR, m = mw + 16 * a + row;
+        const bf16x8 r = lds_read8(xs + 2 * SEG * row + 16 * xpos(row, lane % CPR));
+        if (m < M && n + 8 <= N) {
+          *reinterpret_cast<bf16x8 *>(dst + m * p.ldc) = r;
+        } else if (m < M && n < N) {   // N is a multiple of 4: the last chunk of a row may be half
+          bf16x4 lo;
+          lo[0] = r[0]; lo[1] = r[1]; lo[2] = r[2]; lo[3] = r[3];
+          *reinterpret_cast<bf16x4 *>(dst + m * p.ldc) = lo;
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+  }
+}
+
+}  // namespace pab

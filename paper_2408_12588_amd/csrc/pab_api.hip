@@ -17,7 +17,8 @@
 #include "attn_cross_long.hpp"
 #include "attn_temporal.hpp"
 #include "attn_tile16.hpp"
-#include "gemm_bias.hpp"
+#include "gemm_stream.hpp"
+#include "gemm_tile.hpp"
 #include "module_rowwise.hpp"
 
 namespace {
@@ -297,11 +298,73 @@ size_t module_plane_bytes(int T, int S, int L, int H, int D) {
   return ((size_t)rows * H * D * 2 + 255) / 256 * 256;
 }
 
-// projection kernel shape: 4 x 2 wavefronts of 1 x 4 MFMA tiles = 128 tokens x 256 features per workgroup
-// (eight wavefronts measured 3% faster than four with twice the tiles each)
-constexpr int GEMM_NST = 3, GEMM_WM = 4, GEMM_WN = 2, GEMM_TM = 1, GEMM_TN = 4;
-constexpr int GEMM_MF = 16;   // 16 x 16 x 32 MFMA tiles
-constexpr int GEMM_BM = 32 * GEMM_WM * GEMM_TM, GEMM_BN = 32 * GEMM_WN * GEMM_TN;
+// ---- which projection kernel and tile: the one with the smallest estimate, in us, fitted to 100 shapes timed on the
+//      card (M 60 .. 45000, N and K 128 .. 4608; the pick was within 10% of the best in nearly all of them; K slices of 64):
+//      gemm_stream  3 + (rounds of 256 tiles) (slices t + e): t = 1.5, e = 6 at 256 features, t = 1.7, e = 8 at 288
+//                   (a tail tile of 64 / 128 / 192 token rows takes 0.50 / 0.66 / 0.82 of a full one)
+//      gemm_tile    base + slices max(latency, load l2) + load out, load = tiles / 256 + 0.25: a lone tile is bound by the
+//                   latency of its K loop, more tiles than CUs by L2 (about 60 GB/s per CU) and by their stores
+//      Both sides of the line, measured in us: 2560 x 3456 x 1152 gemm_stream 24, 128 x 128 tiles 33; 6249 x 1152 x 4608
+//      83 and 66; 1350 x 3456 x 1152 128 x 128 tiles 19, 64 x 128 23; 1260 x 576 x 2304 64 x 64 tiles 12, 128 x 128 24. ----
+constexpr int GEMM_CUS = 256;
+
+struct GemmPlan {
+  int kernel;            // 8, 9: gemm_stream with that many sub-tiles per wave column; 64, 96, 128: gemm_tile
+  int n_mt, n_nt, ms_tail, n_units;
+  double us;
+};
+
+void plan_stream(int ns, int M, int N, int slices, GemmPlan *best) {
+  static const double part[5] = {0, 0.50, 0.66, 0.82, 1.0};
+  const int bn = 32 * ns;
+  if (N < bn || M < 64 || slices < 2) return;
+  const long long n_nt = (N + bn - 1) / bn, all = (M + 255LL) / 256 * n_nt;
+  const double tile_us = ns == 8 ? 1.5 * slices + 6.0 : 1.7 * slices + 8.0;
+  for (int less = 0; less < 3; ++less) {   // full tiles for this many rounds, the rest of the token rows as tail tiles
+    const long long rounds = (all + GEMM_CUS - 1) / GEMM_CUS - less;
+    if (rounds < 0) break;
+    const long long n_mt = std::min((long long)M / 256, rounds * GEMM_CUS / n_nt), rows = M - 256 * n_mt;
+    for (int ms = 1; ms <= 4; ++ms) {
+      if (M < 64 * ms) break;
+      const long long tail = (rows + 64 * ms - 1) / (64 * ms) * n_nt, room = rounds * GEMM_CUS - n_mt * n_nt;
+      const double tail_rounds = tail > room ? (double)((tail - room + GEMM_CUS - 1) / GEMM_CUS) : 0.0;
+      const double us = 3.0 + (rounds + tail_rounds * part[ms]) * tile_us;
+      if (n_mt * n_nt + tail <= 0x7fffffffLL && us < best->us)
+        *best = GemmPlan{ns, (int)n_mt, (int)n_nt, ms, (int)(n_mt * n_nt + tail), us};
+    }
+  }
+}
+
+void plan_tile(int kernel, int bm, int bn, double base, double latency, double l2, double out, int M, int N, int slices,
+               GemmPlan *best) {
+  const long long n_mt = ((long long)M + bm - 1) / bm, n_nt = (N + bn - 1) / bn;
+  const double load = n_mt * n_nt / (double)GEMM_CUS + 0.25;
+  const double us = base + slices * std::max(latency, load * l2) + load * out;
+  if (n_mt * n_nt <= 0x7ffffff0LL && us < best->us) *best = GemmPlan{kernel, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), us};
+}
+
+GemmPlan plan_gemm(int M, int N, int K) {
+  GemmPlan best{0, 0, 0, 0, 0, 1e30};
+  const int slices = (K + 63) / 64;
+  plan_tile(64, 64, 64, 2.9, 0.26, 0.25, 0.55, M, N, slices, &best);
+  plan_tile(96, 64, 128, 3.3, 0.32, 0.36, 1.1, M, N, slices, &best);
+  plan_tile(128, 128, 128, 3.5, 0.55, 0.52, 2.2, M, N, slices, &best);
+  plan_stream(8, M, N, slices, &best);
+  plan_stream(9, M, N, slices, &best);
+  return best;
+}
+
+template <bool GELU>
+void launch_gemm_kernel(const GemmPlan &g, const pab::GemmParams &p, hipStream_t st) {
+  const dim3 persistent((unsigned)std::min(g.n_units, GEMM_CUS)), tiles((unsigned)((g.n_units + 7) / 8 * 8));
+  switch (g.kernel) {
+    case 8: hipLaunchKernelGGL((pab::gemm_stream_kernel<8, 4, GELU>), persistent, dim3(512), 0, st, p); break;
+    case 9: hipLaunchKernelGGL((pab::gemm_stream_kernel<9, 3, GELU>), persistent, dim3(512), 0, st, p); break;
+    case 64: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 2, 2, 3, GELU>), tiles, dim3(256), 0, st, p); break;
+    case 96: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 4, 2, 2, 3, GELU>), tiles, dim3(512), 0, st, p); break;
+    default: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 4, 4, 2, GELU>), tiles, dim3(256), 0, st, p); break;
+  }
+}
 
 int launch_gemm(int M, int N, int K, const void *A, const void *W, const void *bias, void *C, long long ldc,
                 int n_split, long long plane_stride, hipStream_t st, int act = 0) {
@@ -319,29 +382,14 @@ int launch_gemm(int M, int N, int K, const void *A, const void *W, const void *b
   p.A = static_cast<const pab::bf16_t *>(A);
   p.W = static_cast<const pab::bf16_t *>(W);
   p.bias = static_cast<const pab::bf16_t *>(bias);
-  p.C = C;
+  p.C = static_cast<pab::bf16_t *>(C);
   p.M = M; p.N = N; p.K = K; p.ldc = ldc;
-  p.n_split = n_split; p.plane_stride = plane_stride; p.act = act;
-  // Few token rows (the text of a cross-attention module): 128 x 64 tiles, four wavefronts stacked along the
-  // tokens, plain tile order: four times the workgroups, spread over all XCDs.
-  const bool skinny = (long long)((M + GEMM_BM - 1) / GEMM_BM) * ((N + GEMM_BN - 1) / GEMM_BN) < 512 && (M + GEMM_BM - 1) / GEMM_BM < 8;
-  const int bm = GEMM_BM, bn = skinny ? 64 : GEMM_BN;
-  p.n_mt = (M + bm - 1) / bm;
-  p.n_nt = (N + bn - 1) / bn;
-  p.xcd_map = skinny ? 0 : 1;
-  long long grid;
-  if (skinny) {
-    grid = (long long)p.n_mt * p.n_nt;
-  } else {   // an XCD owns every eighth token tile and takes them four at a time over all feature tiles
-    const long long owned = (p.n_mt + 7) / 8, groups = (owned + 3) / 4;
-    grid = 8 * groups * 4 * p.n_nt;
-  }
-  if (grid > 0x7fffffffLL) return fail(PAB_EINVAL, "matrix too large");
-  if (skinny)
-    hipLaunchKernelGGL((pab::gemm_bias_kernel<GEMM_NST, 4, 1, 1, 2, GEMM_MF>), dim3((unsigned)grid), dim3(256), 0, st, p);
-  else
-    hipLaunchKernelGGL((pab::gemm_bias_kernel<GEMM_NST, GEMM_WM, GEMM_WN, GEMM_TM, GEMM_TN, GEMM_MF>), dim3((unsigned)grid),
-                       dim3(64 * GEMM_WM * GEMM_WN), 0, st, p);
+  p.n_split = n_split; p.plane_stride = plane_stride;
+  const GemmPlan g = plan_gemm(M, N, K);
+  if (!g.kernel) return fail(PAB_EINVAL, "matrix too large");
+  p.n_mt = g.n_mt; p.n_nt = g.n_nt; p.ms_tail = g.ms_tail; p.n_units = g.n_units;
+  if (act) launch_gemm_kernel<true>(g, p, st);
+  else launch_gemm_kernel<false>(g, p, st);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(PAB_EDEVICE, "kernel launch failed: %s", hipGetErrorString(e));
   return PAB_OK;

@@ -1,0 +1,48 @@
+"""GPU parity of the projection kernels at the edges of their tiles (the plain shapes are in test_gpu_module.py)."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import pab_module_oracle as mo
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+SHAPES = [
+    # M, N, K: what the shape is chosen for (kernel as picked by the size rule)
+    (9001, 2304, 160),    # large tiles, 256 features: token tiles of 192 rows, more than one per CU, the last moved back; half slice
+    (8200, 1728, 288),    # ... full tiles and 64-row tail tiles, last feature tile moved back, K = 4.5 slices
+    (17000, 1444, 160),   # ... N = 4 mod 8: overlapping feature tiles start off 16-byte boundaries
+    (9000, 1152, 128),    # ... two K slices, the fewest it takes
+    (30000, 288, 224),    # large tiles, 288 features: one feature tile, 128-row tail tiles, half slice
+    (12001, 2596, 160),   # ... full and 64-row tail tiles, N = 9.01 tiles
+    (4097, 1156, 160),    # 128 x 128 tiles: one token row and four features in the last tiles
+    (5000, 1152, 96),     # 64 x 128 tiles
+    (700, 68, 96),        # 64 x 64 tiles: four features in the last, K = 1.5 slices
+    (65, 64, 32),         # ... half a slice in all
+]
+
+
+def rand(shape, seed, scale=1.0):
+    g = np.random.Generator(np.random.Philox(key=seed))
+    return torch.from_numpy(g.standard_normal(shape, dtype=np.float32) * np.float32(scale)).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_projection_tiles(M, N, K):
+    from paper_2408_12588_amd import pab
+    print("projection", M, N, K, flush=True)
+    a, w, b = rand((M, K), 1 + M), rand((N, K), 2 + N, 1.0 / math.sqrt(K)), rand((N,), 3 + K, 0.5)
+    pad = 8                                   # columns behind the result that must stay as they are
+    buf = torch.full((M, N + pad), 7.0, device=DEV, dtype=torch.bfloat16)
+    pab.pab_linear(a.to(DEV), w.to(DEV), b.to(DEV), out=buf[:, :N])
+    torch.cuda.synchronize()
+    assert bool((buf[:, N:] == 7.0).all())
+    got = buf[:, :N].cpu().double().numpy()
+    want = mo.linear(a.double().numpy(), w.double().numpy(), b.double().numpy())
+    # an fp32 sum rounded once to bf16, 2^-9 |y|; twice that, and as much of the typical |y| for results near zero
+    bound = 2.0 ** -8 * np.abs(want) + 2.0 ** -8 * np.abs(want).mean()
+    err = np.abs(got - want)
+    assert (err <= bound).all(), "max excess %.3e at %s" % ((err - bound).max(), np.unravel_index((err - bound).argmax(), err.shape))
