@@ -425,17 +425,11 @@ __global__ __launch_bounds__(64 * NWV, MINW) void attn_tile16_kernel(const TileP
 #pragma unroll
     for (int qh = 0; qh < 2; ++qh) {
       const float inv = 1.0f / __shfl(oacc[DEN_DT][qh][DEN_R], l16 + 16 * DEN_G);
-      const int qrow = q_wave0 + 16 * qh + l16;
-      if (qrow < sq) {
-        T *orow = ob + qrow * p.o_ss;
+      const int row0 = q_wave0 + 16 * qh;
+      f32x4 tile[DT16];
 #pragma unroll
-        for (int dt = 0; dt < DT16; ++dt) {
-          const int d0 = 16 * dt + 4 * g4;
-          if (d0 < D)
-            Io<T>::store4(orow + d0, oacc[dt][qh][0] * inv, oacc[dt][qh][1] * inv, oacc[dt][qh][2] * inv,
-                          oacc[dt][qh][3] * inv);
-        }
-      }
+      for (int dt = 0; dt < DT16; ++dt) tile[dt] = oacc[dt][qh];
+      store_rows16<T, D>(ob + row0 * p.o_ss, p.o_ss, sq - row0, tile, inv);
     }
   }
 }
