@@ -51,7 +51,13 @@ struct GemmParams {
   int n_mt, n_nt;       // token / feature tiles (gemm_stream: n_mt full token tiles)
   int ms_tail;          // gemm_stream: the token rows behind the full tiles are cut into tiles of 64 ms_tail rows
   int n_units;          // gemm_stream: full tiles (n_mt x n_nt), then tail tiles
+  // GEMM_NORM (query / key / value projection): layernorm over the head dimension of planes 0 and 1, then the rotation
+  const bf16_t *gq, *bq, *gk, *bk;   // [72] scale and shift for q and for k
+  int S, rope;          // tokens per frame (frame index = token / S); 1: rotate by the frame index (S >= 64)
+  float eps;
 };
+
+enum { GEMM_PLAIN = 0, GEMM_GELU = 1, GEMM_NORM = 2 };   // what happens to the sums
 
 // chunk permutation of stage row r
 __device__ __forceinline__ int gemm_swizzle(int r) { return (r >> 1) & 7; }

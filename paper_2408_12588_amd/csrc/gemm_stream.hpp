@@ -28,6 +28,10 @@
 // at the matrix edge: rows that two tiles compute are written twice with the same
 // bits, and nothing needs a bounds check.
 //
+// GEMM_NORM (NS = 9): the query / key / value projection finishes the paper's "layernorm2" and "pos emb" on its
+// accumulators: a wavefront's 144 features are two whole heads of 72.  The separate pass read and wrote q and k once
+// more: 46 us at 25440 tokens, 52 us at 17408 with the rotation, where the epilogue adds about 10 and 20 us.
+//
 // NS = 8 (256 features): tiles start on cache lines.  NS = 9 (288): fits hidden
 // sizes that are multiples of 288 (72-element heads in fours) without padding; the
 // odd sub-tile of wave column 1 lies before its pairs, so that all pairs are
@@ -35,10 +39,11 @@
 #pragma once
 #include <type_traits>
 #include "gemm_common.hpp"
+#include "rope_table.hpp"
 
 namespace pab {
 
-template <int NS, int RING, bool GELU>
+template <int NS, int RING, int EPI>
 __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p) {
   constexpr int BM = 256, BN = 32 * NS, BK = 64;
   constexpr int STAGE = 128 * (BM + BN);         // bytes: token rows, pair rows of the weights, odd sub-tiles
@@ -51,8 +56,12 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
   static_assert(NPAIR % 2 == 0, "pairs are stored two at a time");
   static_assert(NJ % RING == 0 && NDMA <= NJ, "the operand ring continues across slices");
   constexpr int BIAS = 2 * STAGE, XPOSE = BIAS + 2048;   // byte offsets: two bias rows, 2 KB per wavefront
+  constexpr bool NORM = EPI == GEMM_NORM;
+  constexpr int HD = 72, ROPE = HD / 2 * 8;      // head dim of GEMM_NORM, bytes of one frame's rotary factors
+  constexpr int GB = XPOSE + 8 * 2048, FACT = GB + 4 * 2 * HD;   // gamma / beta of q, k; two frames' factors per wavefront
+  static_assert(!NORM || NS == 9, "a wavefront's features are two heads of 72");
 
-  __shared__ __attribute__((aligned(16))) unsigned char smem[XPOSE + 8 * 2048];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[NORM ? FACT + 8 * 2 * ROPE : GB];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, q16 = lane >> 4;
@@ -130,6 +139,11 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
     }
   };
 
+  if (NORM && tid < 4 * HD) {
+    const int which = tid / HD, i = tid % HD;
+    const bf16_t *src = which == 0 ? p.gq : which == 1 ? p.bq : which == 2 ? p.gk : p.bk;
+    reinterpret_cast<bf16_t *>(smem + GB)[tid] = src[i];
+  }
   stream_tile(0);
   for (int stage = 0; stage < 2; ++stage) {      // the first two slices
     s_live = s_tile < n_mine;
@@ -143,6 +157,128 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
   const int sw = gemm_swizzle(l16);
   const unsigned op = 128 * l16 + 16 * (q16 ^ sw);        // operand address inside 16 rows; columns 32.. : ^ 64
   int stage = 0;
+
+  // ---- GEMM_NORM: bias, then layernorm over the two heads of the wavefront's 144 features and the rotation, on the
+  //      accumulators of a tile of plane 0 (q) or 1 (k); plane 2 (v) takes the bias only.  A lane holds chunks of 8 (the
+  //      odd sub-tile: 4) consecutive features, each inside one head, and the four lanes of a token hold all of it. ----
+  auto norm_heads = [&](auto &acc, const bf16_t *bs, int plane, int m0) __attribute__((always_inline)) {
+    constexpr int MS = sizeof(acc) / sizeof(acc[0]), NCH = NPAIR + 1;
+    const int shift = wn ? SHIFT1 : 0, odd = wn ? 0 : 32 * NPAIR;
+    auto feature = [&](int c) { return c < NPAIR ? shift + 32 * c + 8 * q16 : odd + 4 * q16; };   // of the 144
+    auto value = [&](int a, int c, int e) { return c < NPAIR ? acc[a][2 * c + (e >> 2)][e & 3] : acc[a][NS - 1][e]; };
+    auto set = [&](int a, int c, int e, float x) {
+      if (c < NPAIR) acc[a][2 * c + (e >> 2)][e & 3] = x;
+      else acc[a][NS - 1][e] = x;
+    };
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      const int n = c < NPAIR ? 8 : 4;
+      if (p.bias) {
+#pragma unroll
+        for (int e = 0; e < n; ++e) {
+          const float b = (float)bs[feature(c) + e];
+#pragma unroll
+          for (int a = 0; a < MS; ++a) set(a, c, e, value(a, c, e) + b);
+        }
+      }
+    }
+    if (plane > 1) return;
+    float mean[MS][2], rstd[MS][2];
+    auto across = [](float x) {   // over the four lanes of a token
+      x += __shfl_xor(x, 16);
+      return x + __shfl_xor(x, 32);
+    };
+#pragma unroll
+    for (int a = 0; a < MS; ++a) {
+      float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        float s = 0.0f;
+#pragma unroll
+        for (int e = 0; e < (c < NPAIR ? 8 : 4); ++e) s += value(a, c, e);
+        const bool second = feature(c) >= HD;
+        s0 += second ? 0.0f : s;
+        s1 += second ? s : 0.0f;
+      }
+      mean[a][0] = across(s0) * (1.0f / HD);
+      mean[a][1] = across(s1) * (1.0f / HD);
+      s0 = s1 = 0.0f;
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        const bool second = feature(c) >= HD;
+        const float m = second ? mean[a][1] : mean[a][0];
+        float s = 0.0f;
+#pragma unroll
+        for (int e = 0; e < (c < NPAIR ? 8 : 4); ++e) {
+          const float d = value(a, c, e) - m;
+          set(a, c, e, d);
+          s += d * d;
+        }
+        s0 += second ? 0.0f : s;
+        s1 += second ? s : 0.0f;
+      }
+      rstd[a][0] = 1.0f / sqrtf(across(s0) * (1.0f / HD) + p.eps);
+      rstd[a][1] = 1.0f / sqrtf(across(s1) * (1.0f / HD) + p.eps);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // rotary factors of the one or two frames that the wavefront's (at most 64) tokens lie in: frames have 64 or more
+    const int frame0 = m0 / p.S, frame1 = (m0 + 16 * MS - 1) / p.S;
+    const unsigned fact = lds0 + FACT + 2 * ROPE * wave;
+    if (p.rope) {
+#pragma unroll
+      for (int i = lane; i < HD; i += 64) {
+        const f32x2 f = rope_factor<HD>(i < HD / 2 ? frame0 : frame1, i % (HD / 2));
+        *(__attribute__((address_space(3))) f32x2 *)(size_t)(fact + 8 * i) = f;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    const bf16_t *gamma = reinterpret_cast<const bf16_t *>(smem + GB) + 2 * HD * plane, *beta = gamma + HD;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      const int n = c < NPAIR ? 8 : 4;
+      const bool second = feature(c) >= HD;
+      const int d0 = feature(c) - (second ? HD : 0);          // inside the head
+      float g[8], b[8];
+#pragma unroll
+      for (int e = 0; e < n; ++e) {
+        g[e] = (float)gamma[d0 + e];
+        b[e] = (float)beta[d0 + e];
+      }
+#pragma unroll
+      for (int a = 0; a < MS; ++a) {
+        const float r = second ? rstd[a][1] : rstd[a][0];
+#pragma unroll
+        for (int e = 0; e < n; ++e) set(a, c, e, value(a, c, e) * r * g[e] + b[e]);
+      }
+      if (p.rope) {
+        auto factors = [&](unsigned frame, f32x4 *f) {
+#pragma unroll
+          for (int i = 0; i < n / 4; ++i) f[i] = *(const __attribute__((address_space(3))) f32x4 *)(size_t)(fact + frame + 4 * d0 + 16 * i);
+        };
+        auto rotate = [&](int a, const f32x4 *f) {
+#pragma unroll
+          for (int i = 0; i < n / 2; ++i) {
+            const float x = value(a, c, 2 * i), y = value(a, c, 2 * i + 1), cs = f[i / 2][2 * (i & 1)], sn = f[i / 2][2 * (i & 1) + 1];
+            set(a, c, 2 * i, x * cs - y * sn);
+            set(a, c, 2 * i + 1, x * sn + y * cs);
+          }
+        };
+        f32x4 f[2];
+        factors(0, f);
+        if (frame0 == frame1) {
+#pragma unroll
+          for (int a = 0; a < MS; ++a) rotate(a, f);
+        } else {
+#pragma unroll
+          for (int a = 0; a < MS; ++a) {
+            factors(m0 + 16 * a + l16 >= frame1 * p.S ? ROPE : 0, f);
+            rotate(a, f);
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
 
   auto run_tile = [&](auto ms_tag, const Tile t, int parity) __attribute__((always_inline)) {
     constexpr int MS = decltype(ms_tag)::value;            // token sub-tiles of a wavefront
@@ -197,10 +333,11 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
       }
     }
 
-    // ---- bias, activation, stores: 16 tokens x 64 features at a time through the wavefront's 2 KB ----
     const int shift = wn ? SHIFT1 : 0, odd = wn ? 0 : 32 * NPAIR;   // where the pairs / the odd sub-tile start
     const bf16_t *bs = reinterpret_cast<const bf16_t *>(smem + BIAS + 1024 * parity) + wn * 16 * NS;
     const int f0 = t.n0 + wn * 16 * NS, m0 = t.m0 + wm * 16 * MS;
+    if constexpr (NORM) norm_heads(acc, bs, t.n0 / p.n_split, m0);
+    // ---- bias, activation, stores: 16 tokens x 64 features at a time through the wavefront's 2 KB ----
     const unsigned xs = lds0 + XPOSE + 2048 * wave;
     const unsigned xw = xs + 128 * l16, xr = xs + 128 * (lane >> 3) + 16 * ((lane & 7) ^ gemm_swizzle(lane >> 3));
 #pragma unroll
@@ -209,7 +346,7 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         bf16x8 b8 = zero8();
-        if (p.bias) b8 = *reinterpret_cast<const bf16x8 *>(bs + shift + 64 * h + 32 * u + 8 * q16);
+        if (!NORM && p.bias) b8 = *reinterpret_cast<const bf16x8 *>(bs + shift + 64 * h + 32 * u + 8 * q16);
 #pragma unroll
         for (int e = 0; e < 8; ++e) bv[u][e] = (float)b8[e];
       }
@@ -223,7 +360,7 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             const float x = acc[a][4 * h + 2 * u + (e >> 2)][e & 3] + bv[u][e];
-            y[e] = (bf16_t)(GELU ? gelu(x) : x);
+            y[e] = (bf16_t)(EPI == GEMM_GELU ? gelu(x) : x);
           }
           lds_write8(xw + 16 * ((4 * u + q16) ^ sw), y);
         }
@@ -239,7 +376,7 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
       bf16x4 b4;
 #pragma unroll
       for (int e = 0; e < 4; ++e) b4[e] = (bf16_t)0.0f;
-      if (p.bias) b4 = *reinterpret_cast<const bf16x4 *>(bs + odd + 4 * q16);
+      if (!NORM && p.bias) b4 = *reinterpret_cast<const bf16x4 *>(bs + odd + 4 * q16);
       const int n = f0 + odd + 8 * (lane & 1), plane = n / p.n_split;
       bf16_t *dst = p.C + plane * p.plane_stride + (n - plane * p.n_split) + (long long)(m0 + (lane >> 1)) * p.ldc;
 #pragma unroll
@@ -248,7 +385,7 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float x = acc[a][NS - 1][e] + (float)b4[e];
-          y[e] = (bf16_t)(GELU ? gelu(x) : x);
+          y[e] = (bf16_t)(EPI == GEMM_GELU ? gelu(x) : x);
         }
         lds_write4(xs + 32 * (16 * a + l16) + 8 * q16, y);
       }

@@ -14,13 +14,14 @@
 
 namespace pab {
 
-template <int WM, int WN, int MS, int NS, int NST, bool GELU>
+template <int WM, int WN, int MS, int NS, int NST, int EPI>
 __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_tile_kernel(const GemmParams p) {
   constexpr int NW = WM * WN, BM = 16 * MS * WM, BN = 16 * NS * WN, BK = 64;
   constexpr int ROWS = BM + BN, STAGE = 128 * ROWS;      // bytes
   constexpr int ROUNDS = ROWS / 8, MYR = ROUNDS / NW, TOKR = BM / 8 / NW;   // copy rounds: all, per wavefront, of token rows
   constexpr int SEG = NS >= 4 ? 64 : 32;                 // features stored at a time
   static_assert(ROUNDS % NW == 0 && (BM / 8) % NW == 0, "copy rounds must deal evenly to the wavefronts");
+  static_assert(EPI != GEMM_NORM, "tiles of whole heads only");
   static_assert(NS % 2 == 0 && (NS == 2 || NS % 4 == 0), "sub-tiles come in pairs");
   static_assert(NST >= 2 && NST <= 3 && (NST - 2) * MYR < 16, "vmcnt immediates");
   static_assert(NW * 2048 <= NST * STAGE, "output staging must fit the ring");
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_tile_kernel(const GemmPa
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const float x = acc[a][SEG / 16 * h + 2 * u + (e >> 2)][e & 3];
-          y[e] = (bf16_t)(GELU ? gelu(x) : x);
+          y[e] = (bf16_t)(EPI == GEMM_GELU ? gelu(x) : x);
         }
         lds_write8(xs + 2 * SEG * l16 + 16 * xpos(l16, 4 * u + q16), y);
       }

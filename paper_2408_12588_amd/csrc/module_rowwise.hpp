@@ -15,6 +15,7 @@
 //                        handful of registers.
 #pragma once
 #include "mfma_util.hpp"
+#include "rope_table.hpp"
 
 namespace pab {
 
@@ -87,7 +88,6 @@ struct QkNormParams {
   int n_tok, H, S;                 // S: tokens per frame (frame index = token / S)
   int rope;                        // 1: rotate by the frame index afterwards
   float eps;
-  float log2_base;                 // log2 of the rotary base
 };
 
 // LPR lanes share one (token, head) row, D / LPR consecutive elements each (a multiple of 8 and
@@ -145,13 +145,11 @@ __global__ __launch_bounds__(256) void qk_norm_rope_kernel(const QkNormParams p)
     for (int e = 0; e < 8; ++e) v[8 * i + e] = (v[8 * i + e] - mean) * rstd * (float)gm[e] + (float)bt[e];
   }
   if (p.rope) {
-    const float pos = (float)(int)(row / p.H / p.S);   // frame index of this row's token
+    const int pos = (int)(row / p.H / p.S);   // frame index of this row's token
 #pragma unroll
     for (int i = 0; i < EPL / 2; ++i) {
-      const float pair = (float)(part * (EPL / 2) + i);          // index of the feature pair inside the head
-      const float theta = __builtin_amdgcn_exp2f(-(2.0f * pair / (float)D) * p.log2_base);
-      float sn, cs;
-      sincosf(pos * theta, &sn, &cs);
+      const f32x2 f = rope_factor<D>(pos, part * (EPL / 2) + i);   // index of the feature pair inside the head
+      const float cs = f[0], sn = f[1];
       const float a = v[2 * i], b = v[2 * i + 1];
       v[2 * i] = a * cs - b * sn;
       v[2 * i + 1] = a * sn + b * cs;

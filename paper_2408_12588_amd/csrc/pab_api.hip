@@ -354,20 +354,20 @@ GemmPlan plan_gemm(int M, int N, int K) {
   return best;
 }
 
-template <bool GELU>
+template <int EPI>
 void launch_gemm_kernel(const GemmPlan &g, const pab::GemmParams &p, hipStream_t st) {
   const dim3 persistent((unsigned)std::min(g.n_units, GEMM_CUS)), tiles((unsigned)((g.n_units + 7) / 8 * 8));
   switch (g.kernel) {
-    case 8: hipLaunchKernelGGL((pab::gemm_stream_kernel<8, 4, GELU>), persistent, dim3(512), 0, st, p); break;
-    case 9: hipLaunchKernelGGL((pab::gemm_stream_kernel<9, 3, GELU>), persistent, dim3(512), 0, st, p); break;
-    case 64: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 2, 2, 3, GELU>), tiles, dim3(256), 0, st, p); break;
-    case 96: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 4, 2, 2, 3, GELU>), tiles, dim3(512), 0, st, p); break;
-    default: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 4, 4, 2, GELU>), tiles, dim3(256), 0, st, p); break;
+    case 8: hipLaunchKernelGGL((pab::gemm_stream_kernel<8, 4, EPI>), persistent, dim3(512), 0, st, p); break;
+    case 9: hipLaunchKernelGGL((pab::gemm_stream_kernel<9, 3, EPI>), persistent, dim3(512), 0, st, p); break;
+    case 64: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 2, 2, 3, EPI>), tiles, dim3(256), 0, st, p); break;
+    case 96: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 4, 2, 2, 3, EPI>), tiles, dim3(512), 0, st, p); break;
+    default: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 4, 4, 2, EPI>), tiles, dim3(256), 0, st, p); break;
   }
 }
 
-int launch_gemm(int M, int N, int K, const void *A, const void *W, const void *bias, void *C, long long ldc,
-                int n_split, long long plane_stride, hipStream_t st, int act = 0) {
+int gemm_params(pab::GemmParams *p, int M, int N, int K, const void *A, const void *W, const void *bias, void *C,
+                long long ldc, int n_split, long long plane_stride) {
   if (!A || !W || !C) return fail(PAB_EINVAL, "A, W and C must not be NULL");
   if ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(C) |
        reinterpret_cast<uintptr_t>(bias)) & 15u)
@@ -378,18 +378,32 @@ int launch_gemm(int M, int N, int K, const void *A, const void *W, const void *b
     return fail(PAB_EINVAL, "N=%d and ldc=%lld must be multiples of 4", N, ldc);
   if ((long long)M * K > 0x7fffffffLL || (long long)N * K > 0x7fffffffLL)
     return fail(PAB_EINVAL, "matrix too large");
-  pab::GemmParams p;
-  p.A = static_cast<const pab::bf16_t *>(A);
-  p.W = static_cast<const pab::bf16_t *>(W);
-  p.bias = static_cast<const pab::bf16_t *>(bias);
-  p.C = static_cast<pab::bf16_t *>(C);
-  p.M = M; p.N = N; p.K = K; p.ldc = ldc;
-  p.n_split = n_split; p.plane_stride = plane_stride;
-  const GemmPlan g = plan_gemm(M, N, K);
+  p->A = static_cast<const pab::bf16_t *>(A);
+  p->W = static_cast<const pab::bf16_t *>(W);
+  p->bias = static_cast<const pab::bf16_t *>(bias);
+  p->C = static_cast<pab::bf16_t *>(C);
+  p->M = M; p->N = N; p->K = K; p->ldc = ldc;
+  p->n_split = n_split; p->plane_stride = plane_stride;
+  p->gq = p->bq = p->gk = p->bk = nullptr;
+  p->S = 1; p->rope = 0; p->eps = 0.0f;
+  return PAB_OK;
+}
+
+int gemm_planned(const GemmPlan &g, pab::GemmParams *p) {
   if (!g.kernel) return fail(PAB_EINVAL, "matrix too large");
-  p.n_mt = g.n_mt; p.n_nt = g.n_nt; p.ms_tail = g.ms_tail; p.n_units = g.n_units;
-  if (act) launch_gemm_kernel<true>(g, p, st);
-  else launch_gemm_kernel<false>(g, p, st);
+  p->n_mt = g.n_mt; p->n_nt = g.n_nt; p->ms_tail = g.ms_tail; p->n_units = g.n_units;
+  return PAB_OK;
+}
+
+int launch_gemm(int M, int N, int K, const void *A, const void *W, const void *bias, void *C, long long ldc,
+                int n_split, long long plane_stride, hipStream_t st, int act = 0) {
+  pab::GemmParams p;
+  int rc = gemm_params(&p, M, N, K, A, W, bias, C, ldc, n_split, plane_stride);
+  if (rc != PAB_OK) return rc;
+  const GemmPlan g = plan_gemm(M, N, K);
+  if ((rc = gemm_planned(g, &p)) != PAB_OK) return rc;
+  if (act) launch_gemm_kernel<pab::GEMM_GELU>(g, p, st);
+  else launch_gemm_kernel<pab::GEMM_PLAIN>(g, p, st);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(PAB_EDEVICE, "kernel launch failed: %s", hipGetErrorString(e));
   return PAB_OK;
@@ -420,7 +434,6 @@ int launch_qk_norm(int n_tok, int H, int D, int S, int rope, void *q, void *k, c
   p.gq = static_cast<const pab::bf16_t *>(w->gamma_q); p.bq = static_cast<const pab::bf16_t *>(w->beta_q);
   p.gk = static_cast<const pab::bf16_t *>(w->gamma_k); p.bk = static_cast<const pab::bf16_t *>(w->beta_k);
   p.n_tok = n_tok; p.H = H; p.S = S; p.rope = rope; p.eps = 1e-6f;
-  p.log2_base = 13.287712379549449f;   // log2(10000)
   // three lanes per 72-element row (21 rows per wavefront), two per 32-element row (32 rows)
   const int rows_per_wave = D == 72 ? 21 : 32;
   const long long waves = ((long long)n_tok * H + rows_per_wave - 1) / rows_per_wave;
@@ -428,6 +441,33 @@ int launch_qk_norm(int n_tok, int H, int D, int S, int rope, void *q, void *k, c
   if (D == 72) hipLaunchKernelGGL((pab::qk_norm_rope_kernel<72, 3>), grid, block, 0, st, p);
   else hipLaunchKernelGGL((pab::qk_norm_rope_kernel<32, 2>), grid, block, 0, st, p);
   return PAB_OK;
+}
+
+// q, k, v projections of a self-attention module with layernorm2 (+ rotation) of q and k.  Heads of 72: in the epilogue of
+// the large-tile projection where that is faster than the best plain projection and a pass over q and k (each read and
+// written once at 4.8 TB/s, 3 us at least); the epilogue costs a tile 3 us.
+int launch_qkv(int n_tok, int H, int D, int S, int rope, const void *h, const pab_module_weights *w, void *q,
+               long long plane_elems, hipStream_t st) {
+  const int C = H * D;
+  pab::GemmParams p;
+  int rc = gemm_params(&p, n_tok, 3 * C, C, h, w->w_qkv, w->b_qkv, q, C, C, plane_elems);
+  if (rc != PAB_OK) return rc;
+  GemmPlan plain = plan_gemm(n_tok, 3 * C, C), fused{0, 0, 0, 0, 0, 1e30};
+  if (D == 72 && C % 288 == 0 && (!rope || S >= 64)) plan_stream(9, n_tok, 3 * C, (C + 63) / 64, &fused);
+  const double pass = 3.0 + 8e-6 * n_tok * C / 4.8;
+  const double rounds = fused.n_units / (double)GEMM_CUS + 0.5;
+  if (fused.kernel && fused.us + 3.0 * rounds < plain.us + pass) {
+    if ((rc = gemm_planned(fused, &p)) != PAB_OK) return rc;
+    p.gq = static_cast<const pab::bf16_t *>(w->gamma_q); p.bq = static_cast<const pab::bf16_t *>(w->beta_q);
+    p.gk = static_cast<const pab::bf16_t *>(w->gamma_k); p.bk = static_cast<const pab::bf16_t *>(w->beta_k);
+    p.S = S; p.rope = rope; p.eps = 1e-6f;
+    hipLaunchKernelGGL((pab::gemm_stream_kernel<9, 3, pab::GEMM_NORM>), dim3((unsigned)std::min(fused.n_units, GEMM_CUS)),
+                       dim3(512), 0, st, p);
+    return PAB_OK;
+  }
+  if ((rc = gemm_planned(plain, &p)) != PAB_OK) return rc;
+  launch_gemm_kernel<pab::GEMM_PLAIN>(plain, p, st);
+  return launch_qk_norm(n_tok, H, D, S, rope, q, static_cast<pab::bf16_t *>(q) + plane_elems, w, st);
 }
 
 int launch_module(int kind, int T, int S, int L, int H, int D, const void *x, const void *text,
@@ -453,8 +493,7 @@ int launch_module(int kind, int T, int S, int L, int H, int D, const void *x, co
     if (!w->shift || !w->scale || !w->w_qkv || !w->gamma_q || !w->beta_q || !w->gamma_k || !w->beta_k || !w->w_o)
       return fail(PAB_EINVAL, "self-attention module needs shift, scale, w_qkv, gamma/beta of q and k, w_o");
     if ((rc = launch_ln_modulate((int)tok, C, x, w->shift, w->scale, p_ho, st)) != PAB_OK) return rc;
-    if ((rc = launch_gemm((int)tok, 3 * C, C, p_ho, w->w_qkv, w->b_qkv, p_q, C, C, plane_elems, st)) != PAB_OK) return rc;
-    if ((rc = launch_qk_norm((int)tok, H, D, S, kind == PAB_TEMPORAL, p_q, p_k, w, st)) != PAB_OK) return rc;
+    if ((rc = launch_qkv((int)tok, H, D, S, kind == PAB_TEMPORAL, p_ho, w, p_q, plane_elems, st)) != PAB_OK) return rc;
   }
   if ((rc = launch_checked(kind, PAB_BF16, T, S, L, H, D, p_q, p_k, p_v, p_ho, st)) != PAB_OK) return rc;
   if ((rc = launch_gemm((int)tok, C, C, p_ho, w->w_o, w->b_o, out, C, C, 0, st)) != PAB_OK) return rc;

@@ -46,3 +46,35 @@ def test_projection_tiles(M, N, K):
     bound = 2.0 ** -8 * np.abs(want) + 2.0 ** -8 * np.abs(want).mean()
     err = np.abs(got - want)
     assert (err <= bound).all(), "max excess %.3e at %s" % ((err - bound).max(), np.unravel_index((err - bound).argmax(), err.shape))
+
+
+MODULES = [
+    # kind, T, S, heads (of 72): sizes at which the projection normalises and rotates q and k itself, unless noted
+    (0, 5, 1999, 4),     # no rotation, ragged token tail
+    (1, 70, 130, 4),     # wavefronts whose tokens lie in two frames; frame indices beyond 63 (two digits of the table)
+    (1, 160, 64, 4),     # shortest frames it takes: one per wavefront
+    (1, 33, 301, 8),     # hidden size 576
+    (1, 171, 60, 4),     # shorter frames: separate pass over q and k
+]
+
+
+@pytest.mark.parametrize("kind,T,S,heads", MODULES)
+def test_norm_and_rotation(kind, T, S, heads):
+    """Modules are independent per frame (spatial) or position (temporal): some of them against the oracle, held to
+    1e-2 of the largest output as the modules are elsewhere (bf16 planes in between)."""
+    from paper_2408_12588_amd import pab, workloads as W
+    print("module", W.KIND_NAMES[kind], T, S, heads, flush=True)
+    wl = W.Workload("norm", 1, T, S, 0, heads, 72, "bf16", 1, (1, 1, 0), 0, 0, seed=77 + T)
+    x, w = W.make_module_input(wl, 0, kind, 0), W.make_module_weights(wl, 0, kind)
+    wd = pab.module_weights(**{n: t.to(DEV) for n, t in w.items()})
+    out = pab.pab_module_compute(kind, x.to(DEV), None, wd, heads).cpu()
+    torch.cuda.synchronize()
+    assert torch.isfinite(out.float()).all()
+    f64 = lambda t: t.double().numpy()
+    for i in (0, 2, T - 1) if kind == 0 else (0, 1, 63 % S, S // 2, S - 1):
+        xi, got = (x[i:i + 1], out[i:i + 1]) if kind == 0 else (x[:, i:i + 1].contiguous(), out[:, i:i + 1])
+        want = mo.self_attention_module(kind, f64(xi), f64(w["shift"]), f64(w["scale"]), f64(w["w_qkv"]), f64(w["b_qkv"]),
+                                        f64(w["gamma_q"]), f64(w["beta_q"]), f64(w["gamma_k"]), f64(w["beta_k"]),
+                                        f64(w["w_o"]), f64(w["b_o"]), heads)
+        err = np.abs(f64(got) - want).max()
+        assert err <= 1e-2 * np.abs(want).max(), (i, err, np.abs(want).max())
