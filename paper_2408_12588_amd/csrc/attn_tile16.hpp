@@ -8,9 +8,10 @@
 //   split item:  32 NWV / G consecutive queries.  The wavefronts form G key groups per query tile;
 //                group g takes the key tiles t = g (mod G), so the item is done in 1/G of the steps,
 //                and the partial results (running maximum, O^T with its denominator row) are combined
-//                through LDS at the end.  The host turns the (batch, head) problems of a nearly empty
-//                last round of workgroups into split items: four times as many workgroups, each a
-//                quarter as long, fill the chip where a few long ones would leave most of it idle.
+//                through LDS at the end: four times as many workgroups, each a quarter as long, at 1.3 times the
+//                work.  The host takes them for small launches, which would leave CUs empty, and for the problems
+//                that would make some CUs hold a workgroup more than the others (the rule and its figures are at
+//                the launch).
 // Each wavefront keeps the q operands of its 32 queries in registers.  Keys and values stream through
 // a ring of NRING LDS stages, one 32-key tile per stage, rows packed as in memory (for bf16 inputs the
 // global loads write LDS directly, no registers in between).  A step of the loop publishes G tiles with

@@ -42,7 +42,7 @@ size_t elem_size(int dtype) { return dtype == PAB_BF16 ? 2 : 4; }
 constexpr int TILE_NWV = 8;    // wavefronts per workgroup: 256 queries share each staged K/V tile (4: 1.5-2% slower)
 constexpr int TILE_MINW = 4;   // wavefronts per SIMD the register budget is sized for
 constexpr int TILE_SPLIT_G = 4;   // key groups of a split item
-constexpr int TILE_SLOTS = 512;   // workgroups the chip holds at once: 2 per CU (16 wavefronts) x 256 CUs
+constexpr int TILE_CUS = 32;      // CUs of an XCD; a CU holds two workgroups (16 wavefronts)
 
 template <typename T, int D>
 int launch_tile(int n_batch, int n_head, int sq, int sk, long long q_bs, long long q_ss, long long kv_bs,
@@ -59,18 +59,31 @@ int launch_tile(int n_batch, int n_head, int sq, int sk, long long q_bs, long lo
   if (32 * TILE_SPLIT_G * kv_ss * (long long)sizeof(T) >= (1LL << 32)) return fail(PAB_EINVAL, "sequence stride too large");
   const long long n_bh = (long long)n_batch * n_head;
   if (n_bh > 0x3fffffffLL) return fail(PAB_EINVAL, "problem too large for one launch");
-  // Workgroups all take about the same time, so a launch runs in rounds of TILE_SLOTS.  When the last round
-  // would be at most a quarter full, the (batch, head) problems it would hold are done as split items
-  // instead (a quarter of the queries, four key groups each): four times the workgroups, a quarter of the steps.
+  // Split items (a quarter of the queries, four key groups: a quarter of the steps) for some problems, or for all.  An XCD
+  // takes every eighth (batch, head) problem and has TILE_CUS CUs; workgroups take about the same time, so an XCD's time
+  // steps up where its workgroups pass a multiple of TILE_CUS: by half with the second workgroup of a CU (S = 1024, 16 heads:
+  // 29.0 us with 24 per XCD, 43.3 with 36).  Measured in us, 72-element heads, before -> after:
+  //   everything split where that fits one workgroup per CU (16 problems of 1024: 26.3 -> 16.1, of 300: 11.9 -> 10.8), with long
+  //   sequences up to two (32 of 1024: 27.3 -> 23.8; but 48 of 512 17.0 -> 17.6, 32 of 1590 40.8 -> 52.3); below 8 key tiles the
+  //   combination costs more (16 of 128: 7.0 -> 8.8);
+  //   else the problems that stand over the last multiple, if few (72 of 1024: 43.3 -> 32.3, 84 of 700: 31.6 -> 25.0, 204 of
+  //   1024: 86.5 -> 76.4, 40 of 3600 with 456 split items 202 -> 192; but 40 of 2400 with 608: 90 -> 97, and with fp32 rows 84 of
+  //   2484 with 468: 251 -> 286), or those over the last full round of two workgroups per CU (91 of 3066, fp32: 499 -> 472).
   p.bh_plain = (int)n_bh;
   p.n_split = 0;
   p.split_g = TILE_SPLIT_G;
-  const long long total = n_bh * p.n_item, rest = total % TILE_SLOTS;
   const int ntile = (sk + 31) / 32;
-  if (total > TILE_SLOTS && rest >= p.n_item && rest * 4 <= TILE_SLOTS && ntile >= 4 * TILE_SPLIT_G) {
-    p.bh_plain = (int)(n_bh - rest / p.n_item);
-    p.n_split = (sq + QBLK / TILE_SPLIT_G - 1) / (QBLK / TILE_SPLIT_G);
+  const long long per_xcd = (n_bh + 7) / 8 * p.n_item, n_split = (sq + QBLK / TILE_SPLIT_G - 1) / (QBLK / TILE_SPLIT_G);
+  if (per_xcd <= TILE_CUS) {
+    const long long split_xcd = (n_bh + 7) / 8 * n_split;
+    if (ntile >= 8 && split_xcd <= (ntile >= 32 ? 2 * TILE_CUS : TILE_CUS)) p.bh_plain = 0;
+  } else if (per_xcd % TILE_CUS && ntile >= 8) {
+    const long long keep = per_xcd / TILE_CUS * TILE_CUS / p.n_item * 8;
+    const long long rest = n_bh * p.n_item % (16 * TILE_CUS);
+    if (keep < n_bh && (n_bh - keep) * n_split <= (sizeof(T) == 2 ? 15 : 12) * TILE_CUS) p.bh_plain = (int)keep;
+    else if (per_xcd > 2 * TILE_CUS && rest >= p.n_item && rest <= 4 * TILE_CUS && ntile >= 16) p.bh_plain = (int)(n_bh - rest / p.n_item);
   }
+  if (p.bh_plain < n_bh) p.n_split = (int)n_split;
   const long long plain_wgs = (long long)(p.bh_plain + 7) / 8 * 8 * p.n_item;
   const long long grid = plain_wgs + (n_bh - p.bh_plain + 7) / 8 * 8 * p.n_split;
   if (grid > 0x7fffffffLL) return fail(PAB_EINVAL, "problem too large for one launch (%lld workgroups)", grid);

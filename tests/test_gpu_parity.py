@@ -511,3 +511,32 @@ def test_seeded_random_shapes(pab):
         err = assert_close(out, orc.kind_attention(kind, q, k, v), v, "fuzz case %d" % case)
         worst = max(worst, err / (TOL * float(v.abs().max())))
     print("worst error / bound over the fuzz cases: %.2f" % worst)
+
+
+SPLIT_SHAPES = [
+    # kind, T, S, L, H, D, dtype: launches that run as split items, in whole or in part
+    (W.SPATIAL, 1, 225, 0, 3, 72, "bf16"),     # all split: eight key tiles, the fewest, the last with one key; 33 queries in the last item
+    (W.SPATIAL, 1, 289, 0, 1, 32, "bf16"),     # ... ten key tiles: groups with two and with three
+    (W.SPATIAL, 5, 252, 0, 8, 72, "bf16"),     # ... several problems per XCD
+    (W.SPATIAL, 2, 1000, 0, 16, 72, "bf16"),   # ... two items per CU
+    (W.SPATIAL, 3, 257, 0, 3, 72, "f32"),      # ... fp32 rows
+    (W.SPATIAL, 7, 700, 0, 12, 72, "bf16"),    # 84 problems, three items each: the last four split
+    (W.SPATIAL, 9, 513, 0, 11, 32, "f32"),     # 99 problems: the last 19 split, fp32 rows
+    (W.TEMPORAL, 230, 3, 0, 2, 72, "bf16"),    # long clip, strides exchanged
+    (W.CROSS, 3, 200, 300, 4, 72, "f32"),      # cross attention on the tile kernel: 600 queries, 300 keys
+    (W.CROSS, 1, 90, 530, 2, 72, "bf16"),
+]
+
+
+@pytest.mark.parametrize("peaked", [0.0, 0.05])
+@pytest.mark.parametrize("kind,T,S,L,H,D,dtype", SPLIT_SHAPES)
+def test_split_items(pab, kind, T, S, L, H, D, dtype, peaked):
+    print("split", W.KIND_NAMES[kind], T, S, L, H, D, dtype, peaked, flush=True)
+    q, k, v = rand_qkv(kind, T, S, L, H, D, dtype, seed=2000 + S + L, scale_rows=peaked)
+    out = pab.pab_attention_compute(kind, q.to(DEV), k.to(DEV), v.to(DEV))
+    torch.cuda.synchronize()
+    # fp32 rows are rounded to bf16 on load, which moves a logit s by up to 2^-8 |s|: 0.2 for the rows scaled by 8, whose
+    # logits reach 50, and the output by as much of itself.  The combination of the groups is what is tested here, so the
+    # oracle gets the rounded rows.
+    q, k, v = (t.to(torch.bfloat16).to(t.dtype) for t in (q, k, v))
+    assert_close(out, orc.kind_attention(kind, q, k, v), v, "split case")
