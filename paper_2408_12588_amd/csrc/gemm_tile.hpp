@@ -8,14 +8,21 @@
 // picks the smallest tile that the L2 traffic allows (about 60 GB/s per CU).
 // 1260 x 576 x 2304: 34.2 us with the former 128 x 256 tiles on 15 CUs, 12.6 us
 // with 180 tiles of 64 x 64; 1260 x 1728 x 576: 14.1 -> 8.7 us.
+//
+// The latency is that of barrier, operand reads and MFMAs, one behind the other,
+// with one wavefront per SIMD: more slices in flight did not help (4, 6, 9 stages:
+// 5.4 -> 5.6 .. 6.2 us at 1260 x 576 x 576), more wavefronts do.  Where every tile has a
+// CU to itself, KG groups of WM x WN wavefronts share it: group g takes the
+// slices g (mod KG) through a ring of its own, and the groups' fp32 sums are added
+// through LDS at the end (1260 x 576 x 2304 13.9 -> 10.1 us with three groups).
 #pragma once
 #include <type_traits>
 #include "gemm_common.hpp"
 
 namespace pab {
 
-template <int WM, int WN, int MS, int NS, int NST, int EPI>
-__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_tile_kernel(const GemmParams p) {
+template <int WM, int WN, int MS, int NS, int NST, int KG, int EPI>
+__global__ __launch_bounds__(64 * WM * WN * KG, KG > 1 ? WM * WN * KG / 4 : 2) void gemm_tile_kernel(const GemmParams p) {
   constexpr int NW = WM * WN, BM = 16 * MS * WM, BN = 16 * NS * WN, BK = 64;
   constexpr int ROWS = BM + BN, STAGE = 128 * ROWS;      // bytes
   constexpr int ROUNDS = ROWS / 8, MYR = ROUNDS / NW, TOKR = BM / 8 / NW;   // copy rounds: all, per wavefront, of token rows
@@ -24,14 +31,16 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_tile_kernel(const GemmPa
   static_assert(EPI != GEMM_NORM, "tiles of whole heads only");
   static_assert(NS % 2 == 0 && (NS == 2 || NS % 4 == 0), "sub-tiles come in pairs");
   static_assert(NST >= 2 && NST <= 3 && (NST - 2) * MYR < 16, "vmcnt immediates");
-  static_assert(NW * 2048 <= NST * STAGE, "output staging must fit the ring");
+  constexpr int PART = 1024 * MS * NS * NW;              // bytes of a group's sums
+  static_assert(NW * 2048 + (KG - 1) * PART <= KG * NST * STAGE, "output staging must fit the rings");
 
-  __shared__ __attribute__((aligned(16))) unsigned char smem[NST * STAGE];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[KG * NST * STAGE];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = __builtin_amdgcn_readfirstlane(tid >> 6) / NW, wave = __builtin_amdgcn_readfirstlane(tid >> 6) % NW;
   const int l16 = lane & 15, q16 = lane >> 4;
   const int wm = wave / WN, wn = wave % WN;
-  const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) unsigned char *)smem);
+  const unsigned lds_all = (unsigned)(size_t)((__attribute__((address_space(3))) unsigned char *)smem);
+  const unsigned lds0 = lds_all + NST * STAGE * kg;      // the group's ring
 
   // every XCD takes a contiguous run of tiles, feature tiles of a token tile next to each other
   const int n_tiles = p.n_mt * p.n_nt, per = (n_tiles + 7) >> 3;
@@ -64,8 +73,10 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_tile_kernel(const GemmPa
     for (int i = 0; i < MYR; ++i)
       dma16_to_lds((i < TOKR ? p.A : p.W) + k0, voff[i] - back, lds0 + STAGE * stage + 1024 * (wave + NW * i));
   };
-  const int npre = nk < NST - 1 ? nk : NST - 1;
-  for (int kt = 0; kt < npre; ++kt) issue(kt, kt);
+  // group g takes the slices kt = g (mod KG); all groups go through the same number of steps
+  const int n_mine = (nk - kg + KG - 1) / KG, n_step = (nk + KG - 1) / KG;
+  const int npre = n_mine < NST - 1 ? n_mine : NST - 1;
+  for (int s = 0; s < npre; ++s) issue(KG * s + kg, s);
 
   // accumulators start from the bias: lane's features of sub-tile b are 32 (b / 2) + 8 q16 + 4 (b % 2) + 0..3
   f32x4 acc[MS][NS];
@@ -73,7 +84,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_tile_kernel(const GemmPa
   for (int b = 0; b < NS; ++b) {
     const int n = n0 + wn * 16 * NS + 32 * (b >> 1) + 8 * q16 + 4 * (b & 1);
     f32x4 bv = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (p.bias && n < N) {
+    if (kg == 0 && p.bias && n < N) {
       const bf16x4 b4 = *reinterpret_cast<const bf16x4 *>(p.bias + n);
 #pragma unroll
       for (int e = 0; e < 4; ++e) bv[e] = (float)b4[e];
@@ -86,15 +97,17 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_tile_kernel(const GemmPa
   const unsigned t_off = 128 * wm * 16 * MS + op, w_off = 128 * (BM + wn * 16 * NS) + op;
 
   int stage = 0, next = npre % NST;
-  for (int kt = 0; kt < nk; ++kt) {
-    // slice kt has landed (this wavefront's share); one more may be in flight
-    if (NST == 3 && kt + 1 < nk) __builtin_amdgcn_s_waitcnt(0x0F70 | MYR);
+  for (int s = 0; s < n_step; ++s) {
+    // slice s of the group has landed (this wavefront's share); one more may be in flight
+    if (NST == 3 && s + 1 < n_mine) __builtin_amdgcn_s_waitcnt(0x0F70 | MYR);
     else __builtin_amdgcn_s_waitcnt(0x0F70);
-    __syncthreads();                        // ... everyone's share; all are done with slice kt - 1
-    if (kt + NST - 1 < nk) {
-      issue(kt + NST - 1, next);
+    __syncthreads();                        // ... everyone's share; all are done with slice s - 1
+    if (s + NST - 1 < n_mine) {
+      issue(KG * (s + NST - 1) + kg, next);
       next = next + 1 == NST ? 0 : next + 1;
     }
+    if (KG > 1 && s >= n_mine) break;       // the last step, for groups that have no slice left
+    const int kt = KG * s + kg;
     const unsigned st = lds0 + STAGE * stage;
     stage = stage + 1 == NST ? 0 : stage + 1;
 #pragma unroll
@@ -112,8 +125,28 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_tile_kernel(const GemmPa
     }
   }
 
+  if (KG > 1) {   // groups 1 .. leave their sums in LDS, 16 bytes per lane, group 0 adds them to its own
+    __syncthreads();
+    typedef __attribute__((address_space(3))) f32x4 *lds_ptr_f4;
+    const unsigned part = lds_all + 2048 * NW + 1024 * MS * NS * wave + 16 * lane;
+    if (kg) {
+#pragma unroll
+      for (int a = 0; a < MS; ++a)
+#pragma unroll
+        for (int b = 0; b < NS; ++b) *(lds_ptr_f4)(size_t)(part + PART * (kg - 1) + 1024 * (NS * a + b)) = acc[a][b];
+    }
+    __syncthreads();
+    if (kg) return;
+#pragma unroll
+    for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+      for (int a = 0; a < MS; ++a)
+#pragma unroll
+        for (int b = 0; b < NS; ++b) acc[a][b] += *(lds_ptr_f4)(size_t)(part + PART * g + 1024 * (NS * a + b));
+  }
+
   // ---- activation, stores: 16 tokens x SEG features at a time through 2 KB per wavefront (the ring is free) ----
-  __syncthreads();
+  if (KG == 1) __syncthreads();
   constexpr int CPR = SEG / 8, RPI = 64 / CPR;           // chunks per row segment, rows per store instruction
   auto xpos = [](int row, int q) { return SEG == 64 ? q ^ gemm_swizzle(row) : q ^ ((row >> 2) & 2); };
   const unsigned xs = lds0 + 2048 * wave;

@@ -318,11 +318,15 @@ size_t module_plane_bytes(int T, int S, int L, int H, int D) {
 //      gemm_tile    base + slices max(latency, load l2) + load out, load = tiles / 256 + 0.25: a lone tile is bound by the
 //                   latency of its K loop, more tiles than CUs by L2 (about 60 GB/s per CU) and by their stores
 //      Both sides of the line, measured in us: 2560 x 3456 x 1152 gemm_stream 24, 128 x 128 tiles 33; 6249 x 1152 x 4608
-//      83 and 66; 1350 x 3456 x 1152 128 x 128 tiles 19, 64 x 128 23; 1260 x 576 x 2304 64 x 64 tiles 12, 128 x 128 24. ----
+//      83 and 66; 1350 x 3456 x 1152 128 x 128 tiles 19, 64 x 128 23; 1260 x 576 x 2304 64 x 64 tiles 12, 128 x 128 24.
+//      K groups (odd numbers) where every workgroup has a CU to itself and there are 6 slices or more: 64 x 64 tiles, three
+//      groups, 1260 x 576 x 2304 13.9 -> 10.1, 800 x 1152 x 1152 8.7 -> 7.0, 60 x 1152 x 4608 22.8 -> 15.1, but 1260 x 288 x 288 the
+//      same 4.2, and 360 tiles on 256 CUs 30.6 -> 33.0; 64 x 128, two groups, 1260 x 1152 x 4608 29.7 -> 24.6; 128 x 128, two
+//      groups, 2800 x 1152 x 4608 47.3 -> 39.4, 500 x 4608 x 1152 16.2 -> 14.2. ----
 constexpr int GEMM_CUS = 256;
 
 struct GemmPlan {
-  int kernel;            // 8, 9: gemm_stream with that many sub-tiles per wave column; 64, 96, 128: gemm_tile
+  int kernel;            // 8, 9: gemm_stream with that many sub-tiles per wave column; 64, 96, 128: gemm_tile, 1 more: its K groups
   int n_mt, n_nt, ms_tail, n_units;
   double us;
 };
@@ -351,6 +355,7 @@ void plan_stream(int ns, int M, int N, int slices, GemmPlan *best) {
 void plan_tile(int kernel, int bm, int bn, double base, double latency, double l2, double out, int M, int N, int slices,
                GemmPlan *best) {
   const long long n_mt = ((long long)M + bm - 1) / bm, n_nt = (N + bn - 1) / bn;
+  if ((kernel & 1) && (n_mt * n_nt > GEMM_CUS || slices < 6)) return;   // K groups: one workgroup per CU
   const double load = n_mt * n_nt / (double)GEMM_CUS + 0.25;
   const double us = base + slices * std::max(latency, load * l2) + load * out;
   if (n_mt * n_nt <= 0x7ffffff0LL && us < best->us) *best = GemmPlan{kernel, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), us};
@@ -360,8 +365,11 @@ GemmPlan plan_gemm(int M, int N, int K) {
   GemmPlan best{0, 0, 0, 0, 0, 1e30};
   const int slices = (K + 63) / 64;
   plan_tile(64, 64, 64, 2.9, 0.26, 0.25, 0.55, M, N, slices, &best);
+  plan_tile(65, 64, 64, 2.95, 0.185, 0.17, 0.55, M, N, slices, &best);
   plan_tile(96, 64, 128, 3.3, 0.32, 0.36, 1.1, M, N, slices, &best);
+  plan_tile(97, 64, 128, 3.2, 0.285, 0.24, 1.1, M, N, slices, &best);
   plan_tile(128, 128, 128, 3.5, 0.55, 0.52, 2.2, M, N, slices, &best);
+  plan_tile(129, 128, 128, 3.6, 0.48, 0.45, 1.6, M, N, slices, &best);
   plan_stream(8, M, N, slices, &best);
   plan_stream(9, M, N, slices, &best);
   return best;
@@ -373,9 +381,12 @@ void launch_gemm_kernel(const GemmPlan &g, const pab::GemmParams &p, hipStream_t
   switch (g.kernel) {
     case 8: hipLaunchKernelGGL((pab::gemm_stream_kernel<8, 4, EPI>), persistent, dim3(512), 0, st, p); break;
     case 9: hipLaunchKernelGGL((pab::gemm_stream_kernel<9, 3, EPI>), persistent, dim3(512), 0, st, p); break;
-    case 64: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 2, 2, 3, EPI>), tiles, dim3(256), 0, st, p); break;
-    case 96: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 4, 2, 2, 3, EPI>), tiles, dim3(512), 0, st, p); break;
-    default: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 4, 4, 2, EPI>), tiles, dim3(256), 0, st, p); break;
+    case 64: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 2, 2, 3, 1, EPI>), tiles, dim3(256), 0, st, p); break;
+    case 65: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 2, 2, 3, 3, EPI>), tiles, dim3(768), 0, st, p); break;
+    case 96: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 4, 2, 2, 3, 1, EPI>), tiles, dim3(512), 0, st, p); break;
+    case 97: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 4, 2, 2, 3, 2, EPI>), tiles, dim3(1024), 0, st, p); break;
+    case 128: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 4, 4, 2, 1, EPI>), tiles, dim3(256), 0, st, p); break;
+    default: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 4, 4, 2, 2, EPI>), tiles, dim3(512), 0, st, p); break;
   }
 }
 

@@ -30,7 +30,19 @@ def rand(shape, seed, scale=1.0):
     return torch.from_numpy(g.standard_normal(shape, dtype=np.float32) * np.float32(scale)).to(torch.bfloat16)
 
 
-@pytest.mark.parametrize("M,N,K", SHAPES)
+K_GROUPS = [
+    # M, N, K: small tiles whose K slices are dealt to groups of wavefronts (kernel as picked by the size rule)
+    (65, 68, 384),        # 64 x 64, three groups: two slices each, the fewest; one token row and four features in the last tiles
+    (100, 64, 416),       # ... 6.5 slices: one group has a third, half a slice
+    (1260, 576, 480),     # ... the half slice with the second group
+    (33, 1152, 2304),     # ... 36 slices
+    (1300, 1156, 480),    # 64 x 128, two groups: 7.5 slices
+    (1300, 1152, 448),    # ... an odd number of them
+    (2500, 1156, 1120),   # 128 x 128, two groups: 17.5 slices, ragged tiles
+]
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES + K_GROUPS)
 def test_projection_tiles(M, N, K):
     from paper_2408_12588_amd import pab
     print("projection", M, N, K, flush=True)
