@@ -50,7 +50,12 @@ struct GemmParams {
   long long plane_stride;
   int n_mt, n_nt;       // token / feature tiles (gemm_stream: n_mt full token tiles)
   int ms_tail;          // gemm_stream: the token rows behind the full tiles are cut into tiles of 64 ms_tail rows
-  int n_units;          // gemm_stream: full tiles (n_mt x n_nt), then tail tiles
+  int n_units;          // gemm_stream: full tiles (n_mt x n_nt), then tail tiles, then those of the second problem
+  // GEMM_PLAIN: a second problem of the same K, ldc, n_split and plane_stride in the same launch (n_units2 = 0: none)
+  const bf16_t *A2, *W2, *bias2;
+  bf16_t *C2;
+  int M2, N2, n_nt2, n_units2;
+  int ms2;              // gemm_stream: token rows / 64 of its tiles
   // GEMM_NORM (query / key / value projection): layernorm over the head dimension of planes 0 and 1, then the rotation
   const bf16_t *gq, *bq, *gk, *bk;   // [72] scale and shift for q and for k
   int S, rope;          // tokens per frame (frame index = token / S); 1: rotate by the frame index (S >= 64)

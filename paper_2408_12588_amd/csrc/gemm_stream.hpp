@@ -71,11 +71,20 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
 
   // ---- the workgroup's tiles: unit i of it is number wg + i * gridDim.x; a round of a full grid gives each XCD 32
   //      consecutive units, which are 4 token tiles x 8 feature tiles ----
-  struct Tile { int m0, n0, ms; };
+  struct Tile { int m0, n0, ms; bool second; };
+  constexpr bool PAIR = EPI == GEMM_PLAIN;       // the tiles of a second problem come last, where the last round has room
   constexpr int GM = 4;
   const int n_full = p.n_mt * p.n_nt;
   auto unit = [&](int u) __attribute__((always_inline)) {
     Tile t;
+    t.second = PAIR && u >= p.n_units - p.n_units2;
+    if (t.second) {
+      const int r = u - (p.n_units - p.n_units2);
+      t.ms = __builtin_amdgcn_readfirstlane(p.ms2);
+      t.m0 = __builtin_amdgcn_readfirstlane(min(r / p.n_nt2 * 64 * p.ms2, p.M2 - 64 * p.ms2));
+      t.n0 = __builtin_amdgcn_readfirstlane(min(r % p.n_nt2 * BN, p.N2 - BN));
+      return t;
+    }
     if (u < n_full) {
       const int g = u / (GM * p.n_nt), r = u % (GM * p.n_nt), gm = min(GM, p.n_mt - g * GM);   // the last group may be smaller
       t.m0 = (g * GM + r % gm) * BM; t.n0 = (r / gm) * BN; t.ms = 4;
@@ -109,9 +118,10 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
   auto stream_tile = [&](int i) __attribute__((always_inline)) {
     const Tile t = unit(wg + i * (int)gridDim.x);
     s_ms = t.ms;
-    s_a = p.A + (long long)t.m0 * K;
-    s_w = p.W + (long long)t.n0 * K;
-    s_b = p.bias + t.n0;
+    s_a = (t.second ? p.A2 : p.A) + (long long)t.m0 * K;
+    s_w = (t.second ? p.W2 : p.W) + (long long)t.n0 * K;
+    s_b = t.second ? p.bias2 : p.bias;
+    if (s_b) s_b += t.n0;
   };
   auto copy_round = [&](int stage, int i) __attribute__((always_inline)) {   // round i of the stream's current slice
     if (!s_live) return;
@@ -126,7 +136,7 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
   };
   auto next_slice = [&]() __attribute__((always_inline)) {
     if (!s_live) return;
-    if (s_kt == 0 && p.bias && wave == 7) dma16_to_lds(s_b, 16 * min(lane, BN / 8 - 1), lds0 + BIAS + 1024 * (s_tile & 1));
+    if (s_kt == 0 && s_b && wave == 7) dma16_to_lds(s_b, 16 * min(lane, BN / 8 - 1), lds0 + BIAS + 1024 * (s_tile & 1));
     s_a += BK;
     s_w += BK;
     if (++s_kt == nk) {
@@ -336,6 +346,8 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
     const int shift = wn ? SHIFT1 : 0, odd = wn ? 0 : 32 * NPAIR;   // where the pairs / the odd sub-tile start
     const bf16_t *bs = reinterpret_cast<const bf16_t *>(smem + BIAS + 1024 * parity) + wn * 16 * NS;
     const int f0 = t.n0 + wn * 16 * NS, m0 = t.m0 + wm * 16 * MS;
+    const bool bias = (t.second ? p.bias2 : p.bias) != nullptr;
+    bf16_t *const C = t.second ? p.C2 : p.C;
     if constexpr (NORM) norm_heads(acc, bs, t.n0 / p.n_split, m0);
     // ---- bias, activation, stores: 16 tokens x 64 features at a time through the wavefront's 2 KB ----
     const unsigned xs = lds0 + XPOSE + 2048 * wave;
@@ -346,12 +358,12 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         bf16x8 b8 = zero8();
-        if (!NORM && p.bias) b8 = *reinterpret_cast<const bf16x8 *>(bs + shift + 64 * h + 32 * u + 8 * q16);
+        if (!NORM && bias) b8 = *reinterpret_cast<const bf16x8 *>(bs + shift + 64 * h + 32 * u + 8 * q16);
 #pragma unroll
         for (int e = 0; e < 8; ++e) bv[u][e] = (float)b8[e];
       }
       const int n = f0 + shift + 64 * h + 8 * (lane & 7), plane = n / p.n_split;
-      bf16_t *dst = p.C + plane * p.plane_stride + (n - plane * p.n_split) + (long long)(m0 + (lane >> 3)) * p.ldc;
+      bf16_t *dst = C + plane * p.plane_stride + (n - plane * p.n_split) + (long long)(m0 + (lane >> 3)) * p.ldc;
 #pragma unroll
       for (int a = 0; a < MS; ++a) {
 #pragma unroll
@@ -376,9 +388,9 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
       bf16x4 b4;
 #pragma unroll
       for (int e = 0; e < 4; ++e) b4[e] = (bf16_t)0.0f;
-      if (!NORM && p.bias) b4 = *reinterpret_cast<const bf16x4 *>(bs + odd + 4 * q16);
+      if (!NORM && bias) b4 = *reinterpret_cast<const bf16x4 *>(bs + odd + 4 * q16);
       const int n = f0 + odd + 8 * (lane & 1), plane = n / p.n_split;
-      bf16_t *dst = p.C + plane * p.plane_stride + (n - plane * p.n_split) + (long long)(m0 + (lane >> 1)) * p.ldc;
+      bf16_t *dst = C + plane * p.plane_stride + (n - plane * p.n_split) + (long long)(m0 + (lane >> 1)) * p.ldc;
 #pragma unroll
       for (int a = 0; a < MS; ++a) {
         bf16x4 y;

@@ -43,11 +43,17 @@ __global__ __launch_bounds__(64 * WM * WN * KG, KG > 1 ? WM * WN * KG / 4 : 2) v
   const unsigned lds0 = lds_all + NST * STAGE * kg;      // the group's ring
 
   // every XCD takes a contiguous run of tiles, feature tiles of a token tile next to each other
-  const int n_tiles = p.n_mt * p.n_nt, per = (n_tiles + 7) >> 3;
-  const int id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  constexpr bool PAIR = EPI == GEMM_PLAIN;               // the tiles of a second problem follow those of the first
+  const int n_first = p.n_mt * p.n_nt, n_tiles = n_first + (PAIR ? p.n_units2 : 0), per = (n_tiles + 7) >> 3;
+  int id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if ((int)(blockIdx.x >> 3) >= per || id >= n_tiles) return;
-  const int m0 = id / p.n_nt * BM, n0 = id % p.n_nt * BN;
-  const int M = p.M, N = p.N, K = p.K, nk = (K + BK - 1) / BK;
+  const bool second = PAIR && id >= n_first;
+  id -= second ? n_first : 0;
+  const bf16_t *A = second ? p.A2 : p.A, *W = second ? p.W2 : p.W, *bias = second ? p.bias2 : p.bias;
+  bf16_t *C = second ? p.C2 : p.C;
+  const int M = second ? p.M2 : p.M, N = second ? p.N2 : p.N, n_nt = second ? p.n_nt2 : p.n_nt;
+  const int m0 = id / n_nt * BM, n0 = id % n_nt * BN;
+  const int K = p.K, nk = (K + BK - 1) / BK;
 
   // round r = wave + NW i: stage rows 8 r .. 8 r + 7, token rows first.  Rows past the matrix re-read its last row; what
   // they produce is never stored.  LDS row i of a 32-row weight pair: sub-tile i >> 4, operand row i & 15.
@@ -71,7 +77,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, KG > 1 ? WM * WN * KG / 4 : 2) v
     const unsigned back = (K & 32) && kt == nk - 1 && cq >= 4 ? 64 : 0;   // a half slice repeats columns 0-31
 #pragma unroll
     for (int i = 0; i < MYR; ++i)
-      dma16_to_lds((i < TOKR ? p.A : p.W) + k0, voff[i] - back, lds0 + STAGE * stage + 1024 * (wave + NW * i));
+      dma16_to_lds((i < TOKR ? A : W) + k0, voff[i] - back, lds0 + STAGE * stage + 1024 * (wave + NW * i));
   };
   // group g takes the slices kt = g (mod KG); all groups go through the same number of steps
   const int n_mine = (nk - kg + KG - 1) / KG, n_step = (nk + KG - 1) / KG;
@@ -84,8 +90,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG, KG > 1 ? WM * WN * KG / 4 : 2) v
   for (int b = 0; b < NS; ++b) {
     const int n = n0 + wn * 16 * NS + 32 * (b >> 1) + 8 * q16 + 4 * (b & 1);
     f32x4 bv = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (kg == 0 && p.bias && n < N) {
-      const bf16x4 b4 = *reinterpret_cast<const bf16x4 *>(p.bias + n);
+    if (kg == 0 && bias && n < N) {
+      const bf16x4 b4 = *reinterpret_cast<const bf16x4 *>(bias + n);
 #pragma unroll
       for (int e = 0; e < 4; ++e) bv[e] = (float)b4[e];
     }
@@ -155,7 +161,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, KG > 1 ? WM * WN * KG / 4 : 2) v
   for (int h = 0; h < 16 * NS / SEG; ++h) {
     const int fw = n0 + wn * 16 * NS + SEG * h;          // first feature of the segment
     const int n = fw + 8 * (lane % CPR), plane = n / p.n_split;
-    bf16_t *dst = p.C + plane * p.plane_stride + (n - plane * p.n_split);
+    bf16_t *dst = C + plane * p.plane_stride + (n - plane * p.n_split);
 #pragma unroll
     for (int a = 0; a < MS; ++a) {
 #pragma unroll

@@ -90,3 +90,34 @@ def test_norm_and_rotation(kind, T, S, heads):
                                         f64(w["w_o"]), f64(w["b_o"]), heads)
         err = np.abs(f64(got) - want).max()
         assert err <= 1e-2 * np.abs(want).max(), (i, err, np.abs(want).max())
+
+
+CROSS_PAIRS = [
+    # T, S, L, heads (of 72): the text's k / v projection in the launch of the query projection, as ...
+    (5, 252, 60, 8),        # ... 64 x 64 tiles with K groups, ragged in the text
+    (1, 1, 1, 4),           # ... one token, one text token
+    (12, 500, 300, 12),     # ... more tiles than CUs
+    (8, 1590, 64, 16),      # ... tiles of the last round of gemm_stream, one of 64 rows
+    (16, 1590, 131, 16),    # ... 128-row tiles, the second moved back
+    (16, 1590, 63, 16),     # fewer than 64 text tokens: by itself
+    (16, 1590, 500, 16),    # long text
+    (1, 900, 250, 16),      # K groups, more tiles than CUs in all: by itself
+]
+
+
+@pytest.mark.parametrize("T,S,L,heads", CROSS_PAIRS)
+def test_query_and_text_projection(T, S, L, heads):
+    """Cross modules are independent per token: some against the oracle, 1e-2 of the largest output as elsewhere."""
+    from paper_2408_12588_amd import pab, workloads as W
+    print("cross pair", T, S, L, heads, flush=True)
+    wl = W.Workload("pair", 1, T, S, L, heads, 72, "bf16", 1, (0, 0, 1), 0, 0, seed=55 + L)
+    x, text, w = W.make_module_input(wl, 0, W.CROSS, 0), W.make_text(wl), W.make_module_weights(wl, 0, W.CROSS)
+    out = pab.pab_module_compute(W.CROSS, x.to(DEV), text.to(DEV), pab.module_weights(**{n: t.to(DEV) for n, t in w.items()}), heads)
+    out = out.cpu().view(T * S, -1)
+    assert torch.isfinite(out.float()).all()
+    f64 = lambda t: t.double().numpy()
+    rows = sorted({0, T * S // 3, T * S // 2, T * S - 65, T * S - 1} & set(range(T * S)))
+    want = mo.cross_attention_module(f64(x.view(1, T * S, -1)[:, rows]), f64(text), *(f64(w[k]) for k in (
+        "w_qkv", "b_qkv", "w_kv", "b_kv", "w_o", "b_o")), heads)[0]
+    err = np.abs(f64(out[rows]) - want).max()
+    assert err <= 1e-2 * np.abs(want).max(), (err, np.abs(want).max())
