@@ -212,6 +212,10 @@ def pab_workspace_bytes(cfg: pab_config) -> int:
 
 def _stream(stream) -> int:
     if stream is None:
+        # The current stream's handle without a Stream object around it: 0.3 us instead of 2.7, of 4.2 us that a reused
+        # call took in all.
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream

@@ -540,3 +540,15 @@ def test_split_items(pab, kind, T, S, L, H, D, dtype, peaked):
     # oracle gets the rounded rows.
     q, k, v = (t.to(torch.bfloat16).to(t.dtype) for t in (q, k, v))
     assert_close(out, orc.kind_attention(kind, q, k, v), v, "split case")
+
+
+def test_default_stream_argument_is_the_current_stream(pab):
+    """Without a stream argument calls go to torch's current stream: default, side stream, nested."""
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    assert pab._stream(None) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(s1):
+        assert pab._stream(None) == s1.cuda_stream
+        with torch.cuda.stream(s2):
+            assert pab._stream(None) == s2.cuda_stream
+        assert pab._stream(None) == s1.cuda_stream
+    assert pab._stream(None) == torch.cuda.current_stream().cuda_stream
