@@ -17,6 +17,7 @@
 #include "attn_cross_long.hpp"
 #include "attn_temporal.hpp"
 #include "attn_tile16.hpp"
+#include "gemm_heads.hpp"
 #include "gemm_stream.hpp"
 #include "gemm_tile.hpp"
 #include "module_rowwise.hpp"
@@ -361,6 +362,15 @@ void plan_tile(int kernel, int bm, int bn, double base, double latency, double l
   if (n_mt * n_nt <= 0x7ffffff0LL && us < best->us) *best = GemmPlan{kernel, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), us};
 }
 
+// gemm_heads (estimate fitted like those above, whole temporal modules in us, separate pass -> gemm_heads): 1260 tokens of 576
+// 28.0 -> 23.8, 800 of 864 31.0 -> 27.2, 630 of 1152 35.3 -> 31.0; but 250 of 1152 26.2 -> 26.9, 60 of 864 22.0 -> 23.2.
+void plan_heads(int D, int M, int N, int slices, GemmPlan *best) {
+  const int bn = D == 72 ? 144 : 96;
+  const long long n_mt = (M + 63LL) / 64, n_nt = (N + bn - 1) / bn;
+  if (n_mt * n_nt > GEMM_CUS) return;
+  *best = GemmPlan{bn, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), 5.5 + 0.3 * slices + n_mt * n_nt / (double)GEMM_CUS};
+}
+
 GemmPlan plan_gemm(int M, int N, int K) {
   GemmPlan best{0, 0, 0, 0, 0, 1e30};
   const int slices = (K + 63) / 64;
@@ -508,24 +518,33 @@ int launch_qk_norm(int n_tok, int H, int D, int S, int rope, void *q, void *k, c
   return PAB_OK;
 }
 
-// q, k, v projections of a self-attention module with layernorm2 (+ rotation) of q and k.  Heads of 72: in the epilogue of
-// the large-tile projection where that is faster than the best plain projection and a pass over q and k (each read and
-// written once at 4.8 TB/s, 3 us at least); the epilogue costs a tile 3 us.
+// q, k, v projections of a self-attention module with layernorm2 (+ rotation) of q and k, whichever is estimated fastest:
+//   the best plain projection and a pass over q and k (each read and written once at 4.8 TB/s, 3 us at least);
+//   heads of 72: in the epilogue of the large-tile projection (it costs a tile 3 us);
+//   few tokens, one tile of two (heads of 32: three) heads per CU: in the epilogue of gemm_heads.
 int launch_qkv(int n_tok, int H, int D, int S, int rope, const void *h, const pab_module_weights *w, void *q,
                long long plane_elems, hipStream_t st) {
-  const int C = H * D;
+  const int C = H * D, slices = (C + 63) / 64;
   pab::GemmParams p;
   int rc = gemm_params(&p, n_tok, 3 * C, C, h, w->w_qkv, w->b_qkv, q, C, C, plane_elems);
   if (rc != PAB_OK) return rc;
-  GemmPlan plain = plan_gemm(n_tok, 3 * C, C), fused{0, 0, 0, 0, 0, 1e30};
-  if (D == 72 && C % 288 == 0 && (!rope || S >= 64)) plan_stream(9, n_tok, 3 * C, (C + 63) / 64, &fused);
-  const double pass = 3.0 + 8e-6 * n_tok * C / 4.8;
-  const double rounds = fused.n_units / (double)GEMM_CUS + 0.5;
-  if (fused.kernel && fused.us + 3.0 * rounds < plain.us + pass) {
+  GemmPlan plain = plan_gemm(n_tok, 3 * C, C), fused{0, 0, 0, 0, 0, 1e30}, heads{0, 0, 0, 0, 0, 1e30};
+  if (D == 72 && C % 288 == 0 && (!rope || S >= 64)) plan_stream(9, n_tok, 3 * C, slices, &fused);
+  fused.us += 3.0 * (fused.n_units / (double)GEMM_CUS + 0.5);
+  plan_heads(D, n_tok, 3 * C, slices, &heads);
+  plain.us += 3.0 + 8e-6 * n_tok * C / 4.8;
+  p.gq = static_cast<const pab::bf16_t *>(w->gamma_q); p.bq = static_cast<const pab::bf16_t *>(w->beta_q);
+  p.gk = static_cast<const pab::bf16_t *>(w->gamma_k); p.bk = static_cast<const pab::bf16_t *>(w->beta_k);
+  p.S = S; p.rope = rope; p.eps = 1e-6f;
+  if (heads.kernel && heads.us < std::min(fused.us, plain.us)) {
+    if ((rc = gemm_planned(heads, &p)) != PAB_OK) return rc;
+    const dim3 tiles((unsigned)((heads.n_units + 7) / 8 * 8)), block(768);
+    if (D == 72) hipLaunchKernelGGL((pab::gemm_heads_kernel<2, 3, 2, 3, 3, 2, 72>), tiles, block, 0, st, p);
+    else hipLaunchKernelGGL((pab::gemm_heads_kernel<2, 3, 2, 2, 3, 2, 32>), tiles, block, 0, st, p);
+    return PAB_OK;
+  }
+  if (fused.kernel && fused.us < plain.us) {
     if ((rc = gemm_planned(fused, &p)) != PAB_OK) return rc;
-    p.gq = static_cast<const pab::bf16_t *>(w->gamma_q); p.bq = static_cast<const pab::bf16_t *>(w->beta_q);
-    p.gk = static_cast<const pab::bf16_t *>(w->gamma_k); p.bk = static_cast<const pab::bf16_t *>(w->beta_k);
-    p.S = S; p.rope = rope; p.eps = 1e-6f;
     hipLaunchKernelGGL((pab::gemm_stream_kernel<9, 3, pab::GEMM_NORM>), dim3((unsigned)std::min(fused.n_units, GEMM_CUS)),
                        dim3(512), 0, st, p);
     return PAB_OK;

@@ -121,3 +121,29 @@ def test_query_and_text_projection(T, S, L, heads):
         "w_qkv", "b_qkv", "w_kv", "b_kv", "w_o", "b_o")), heads)[0]
     err = np.abs(f64(out[rows]) - want).max()
     assert err <= 1e-2 * np.abs(want).max(), (err, np.abs(want).max())
+
+
+FEW_TOKENS = [
+    # kind, T, S, heads, head dim: sizes at which q and k are normalised (and rotated) in the epilogue of gemm_heads
+    (0, 1, 705, 8, 72),      # one token in the last token tile
+    (1, 70, 3, 4, 72),       # several frames per tile, frame indices beyond 63; hidden size 288 = 4.5 slices: the second group ends early
+    (1, 5, 90, 12, 72),      # hidden size 864 = 13.5 slices: the half slice with the second group
+    (0, 1, 449, 16, 72),
+    (1, 9, 21, 4, 32),       # heads of 32, three per tile: tiles across the q / k / v planes
+    (0, 1, 1, 1, 32),        # one token, half a slice: the second group has none
+]
+
+
+@pytest.mark.parametrize("kind,T,S,heads,D", FEW_TOKENS)
+def test_norm_and_rotation_few_tokens(kind, T, S, heads, D):
+    """Whole outputs against the oracle, 1e-2 of the largest output as for the modules elsewhere."""
+    from paper_2408_12588_amd import pab, workloads as W
+    print("few tokens", kind, T, S, heads, D, flush=True)
+    f64 = lambda t: t.double().numpy()
+    wl = W.Workload("few", 1, T, S, 0, heads, D, "bf16", 1, (1, 1, 0), 0, 0, seed=91 + S)
+    x, w = W.make_module_input(wl, 0, kind, 0), W.make_module_weights(wl, 0, kind)
+    out = pab.pab_module_compute(kind, x.to(DEV), None, pab.module_weights(**{k: t.to(DEV) for k, t in w.items()}), heads)
+    want = mo.self_attention_module(kind, f64(x), *(f64(w[k]) for k in ("shift", "scale", "w_qkv", "b_qkv", "gamma_q", "beta_q",
+                                                                        "gamma_k", "beta_k", "w_o", "b_o")), heads)
+    err = np.abs(f64(out.cpu()) - want).max()
+    assert err <= 1e-2 * np.abs(want).max(), (err, np.abs(want).max())
