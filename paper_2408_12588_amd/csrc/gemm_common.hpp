@@ -6,8 +6,9 @@
 // Both operands are contiguous along K, which is what the MFMA operands want:
 // with the weight rows as the A operand and the token rows as the B operand a
 // 16 x 16 sub-tile is C^T[n, m], every lane owns one token and 4 of its outputs.
-// Two kernels share the layouts below: gemm_stream.hpp for problems that fill
-// the chip with large tiles, gemm_tile.hpp for the others.
+// Three kernels share the layouts below: gemm_stream.hpp for problems that fill
+// the chip with large tiles, gemm_tile.hpp for the others, gemm_heads.hpp for
+// few tokens where q and k are normalised per head behind the projection.
 //
 // Operand layout in LDS.  A stage holds 64 columns of K of a tile's token rows
 // and weight rows, 128 bytes per row = one cache line: with 32 columns (half
@@ -56,9 +57,9 @@ struct GemmParams {
   bf16_t *C2;
   int M2, N2, n_nt2, n_units2;
   int ms2;              // gemm_stream: token rows / 64 of its tiles
-  // GEMM_NORM (query / key / value projection): layernorm over the head dimension of planes 0 and 1, then the rotation
-  const bf16_t *gq, *bq, *gk, *bk;   // [72] scale and shift for q and for k
-  int S, rope;          // tokens per frame (frame index = token / S); 1: rotate by the frame index (S >= 64)
+  // GEMM_NORM and gemm_heads (query / key / value projection): layernorm over the head dimension of planes 0 and 1, then the rotation
+  const bf16_t *gq, *bq, *gk, *bk;   // [head dim] scale and shift for q and for k
+  int S, rope;          // tokens per frame (frame index = token / S); 1: rotate by the frame index (gemm_stream: S >= 64)
   float eps;
 };
 
