@@ -448,8 +448,9 @@ int launch_gemm(int M, int N, int K, const void *A, const void *W, const void *b
 // Two projections of the same K in one launch: C = A W^T and, side by side in n_split-wide planes, C2 = A2 W2^T.  The second
 // one (few rows: the text of the cross module) rides along where it costs no round of its own: as further tiles of
 // gemm_tile, or in the room that the last round of gemm_stream leaves (there with 64 rows or more, the least a tile has); else it
-// is launched by itself.  25440 and 120 tokens, 1152 features: module 182.8 -> 181.3 us; 1260 and 60 tokens, 576 features: one
-// launch of 4 us less, a small clip's blocks 2067 -> 2006.
+// is launched by itself (25440 and 120 tokens: 12 units of room for 18).  Cross modules in us, two launches -> one: 17408 and 300
+// tokens of 1152 features 149 -> 144, 34000 and 120 of 864 147 -> 143; 2048 and 120 of 1152 39.5 -> 33.0, 6000 and 300 of 864
+// 59.4 -> 54.1, 1260 and 60 of 576 20.0 -> 15.4.
 int launch_gemm_pair(int M, int N, int K, const void *A, const void *W, const void *bias, void *C, int M2, int N2, const void *A2,
                      const void *W2, const void *bias2, void *C2, long long ldc, int n_split, long long plane_stride,
                      hipStream_t st) {
