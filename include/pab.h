@@ -239,7 +239,7 @@ size_t pab_module_scratch_bytes(const pab_config *cfg);
 
 /*
  * One module, no schedule and no cache: x [T, S, C] (and text [L, C] for
- * cross attention) -> out [T, S, C], five kernel launches (four for cross)
+ * cross attention) -> out [T, S, C], three to five kernel launches by size
  * on `hip_stream`.  `scratch` must be 256-byte aligned and at least
  * pab_module_scratch_bytes() of the same shape long.
  * PAB_EINVAL: bad kind / shape / head_dim, C not a multiple of 32 or > 2048,
