@@ -23,7 +23,8 @@
 // (bank conflict counter: 0).
 //
 // K may be an odd multiple of 32.  The upper half of the last slice then repeats
-// the lower one in LDS and meets token operands set to zero, or is not computed.
+// the lower one in LDS and is not computed: zeros against the repeated weights
+// would turn an infinite weight into a NaN.
 //
 // Weight rows of a pair of sub-tiles are taken in the order 8 (i >> 2) + 4 u +
 // (i & 3) (sub-tile u, operand row i), so that the two accumulators of a lane are

@@ -317,7 +317,9 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[a][b][e] = 0.0f;
 
-    for (int kt = 0; kt < nk; ++kt) {
+    // one slice; HALF: the last one of an odd multiple of 32 columns, whose columns 32-63 do not exist and are not computed
+    auto slice = [&](auto half_tag) __attribute__((always_inline)) {
+      constexpr bool HALF = decltype(half_tag)::value;
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         if (j == JB) {   // this slice has been read, the next one has arrived
@@ -331,17 +333,17 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
         const int d = (j - JB + NJ) % NJ;   // steps since the barrier
         if (d < NDMA) copy_round(stage ^ 1, d);
         if (d == NDMA - 1) next_slice();
-        wf[(j + AHEAD) % RING] = rd_w((j + AHEAD) % NJ);
-        if (j >= 1 && j <= MS) rd_t(1, j - 1);
-        if (j == MS && (K & 32) && kt == nk - 1) {
+        if (!HALF || j + AHEAD < NS || j + AHEAD >= NJ) wf[(j + AHEAD) % RING] = rd_w((j + AHEAD) % NJ);
+        if (!HALF && j >= 1 && j <= MS) rd_t(1, j - 1);
+        if (!HALF || j < NS) {
 #pragma unroll
-          for (int a = 0; a < MS; ++a) tf[1][a] = zero8();
+          for (int a = 0; a < MS; ++a) acc[a][j % NS] = mfma16(wf[j % RING], tf[j / NS][a], acc[a][j % NS]);
         }
-#pragma unroll
-        for (int a = 0; a < MS; ++a) acc[a][j % NS] = mfma16(wf[j % RING], tf[j / NS][a], acc[a][j % NS]);
         __builtin_amdgcn_sched_barrier(0);
       }
-    }
+    };
+    for (int kt = 0; kt < K / BK; ++kt) slice(std::false_type{});
+    if (K & 32) slice(std::true_type{});
 
     const int shift = wn ? SHIFT1 : 0, odd = wn ? 0 : 32 * NPAIR;   // where the pairs / the odd sub-tile start
     const bf16_t *bs = reinterpret_cast<const bf16_t *>(smem + BIAS + 1024 * parity) + wn * 16 * NS;

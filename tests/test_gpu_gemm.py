@@ -60,6 +60,33 @@ def test_projection_tiles(M, N, K):
     assert (err <= bound).all(), "max excess %.3e at %s" % ((err - bound).max(), np.unravel_index((err - bound).argmax(), err.shape))
 
 
+HALF_SLICES = [
+    # M, N, K: odd multiples of 32, the last K slice has 32 columns (kernel as picked by the size rule)
+    (9001, 2304, 160),    # large tiles, 256 features
+    (12001, 2596, 160),   # ... 288 features
+    (8200, 1728, 288),    # ... full and tail tiles
+    (1260, 576, 480),     # 64 x 64 tiles, K groups
+    (700, 68, 96),        # ... without
+]
+
+
+@pytest.mark.parametrize("M,N,K", HALF_SLICES)
+def test_infinite_weights_of_a_half_slice(M, N, K):
+    """An infinite weight gives infinities with the sign of its token's element, never NaN, and only in its own feature."""
+    from paper_2408_12588_amd import pab
+    print("infinite weights", M, N, K, flush=True)
+    a, w = rand((M, K), 1 + M), rand((N, K), 2 + N, 1.0 / math.sqrt(K))
+    a[a == 0] = 1.0
+    hit = {3: K - 32, 5: K - 1, N - 1: K - 7, 9: K - 33}     # feature: column of the half slice (the last: in the slice before it)
+    for n, k in hit.items():
+        w[n, k] = float("inf") if n != 5 else float("-inf")
+    got = pab.pab_linear(a.to(DEV), w.to(DEV)).cpu()
+    for n, k in hit.items():
+        assert torch.equal(got[:, n].float(), (a[:, k].float() * w[n, k].float())), n
+    rest = [n for n in range(N) if n not in hit]
+    assert bool(torch.isfinite(got[:, rest].float()).all())
+
+
 MODULES = [
     # kind, T, S, heads (of 72): sizes at which the projection normalises and rotates q and k itself, unless noted
     (0, 5, 1999, 4),     # no rotation, ragged token tail
