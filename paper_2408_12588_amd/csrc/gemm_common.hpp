@@ -77,8 +77,10 @@ __device__ __forceinline__ void lds_write8(unsigned addr, bf16x8 v) { *(lds_ptr8
 __device__ __forceinline__ void lds_write4(unsigned addr, bf16x4 v) { *(lds_ptr4)(size_t)addr = v; }
 
 // GELU in its tanh form: 0.5 x (1 + tanh u) = x / (1 + exp(-2u)), u = sqrt(2/pi) (x + 0.044715 x^3)
+// (fused product written out: the same bits wherever it is inlined, see gemm_stream.hpp on rows that two tiles compute)
 __device__ __forceinline__ float gelu(float x) {
-  const float u2 = -2.302208198f * (x + 0.044715f * x * x * x);   // -2 sqrt(2/pi) log2(e) (..)
+#pragma clang fp contract(off)
+  const float u2 = -2.302208198f * __builtin_fmaf(0.044715f * x * x, x, x);   // -2 sqrt(2/pi) log2(e) (..)
   return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(u2));
 }
 

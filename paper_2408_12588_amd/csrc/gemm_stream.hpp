@@ -172,6 +172,9 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
   //      accumulators of a tile of plane 0 (q) or 1 (k); plane 2 (v) takes the bias only.  A lane holds chunks of 8 (the
   //      odd sub-tile: 4) consecutive features, each inside one head, and the four lanes of a token hold all of it. ----
   auto norm_heads = [&](auto &acc, const bf16_t *bs, int plane, int m0) __attribute__((always_inline)) {
+    // A token that two tiles compute goes through two instantiations of this code (tiles of 64 .. 256 rows): which products
+    // are fused is written out, or the compiler chose differently in them and the last bits depended on the tile.
+#pragma clang fp contract(off)
     constexpr int MS = sizeof(acc) / sizeof(acc[0]), NCH = NPAIR + 1;
     const int shift = wn ? SHIFT1 : 0, odd = wn ? 0 : 32 * NPAIR;
     auto feature = [&](int c) { return c < NPAIR ? shift + 32 * c + 8 * q16 : odd + 4 * q16; };   // of the 144
@@ -222,13 +225,13 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
         for (int e = 0; e < (c < NPAIR ? 8 : 4); ++e) {
           const float d = value(a, c, e) - m;
           set(a, c, e, d);
-          s += d * d;
+          s = __builtin_fmaf(d, d, s);
         }
         s0 += second ? 0.0f : s;
         s1 += second ? s : 0.0f;
       }
-      rstd[a][0] = 1.0f / sqrtf(across(s0) * (1.0f / HD) + p.eps);
-      rstd[a][1] = 1.0f / sqrtf(across(s1) * (1.0f / HD) + p.eps);
+      rstd[a][0] = 1.0f / sqrtf(__builtin_fmaf(across(s0), 1.0f / HD, p.eps));
+      rstd[a][1] = 1.0f / sqrtf(__builtin_fmaf(across(s1), 1.0f / HD, p.eps));
       __builtin_amdgcn_sched_barrier(0);
     }
     // rotary factors of the one or two frames that the wavefront's (at most 64) tokens lie in: frames have 64 or more
@@ -258,7 +261,7 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
       for (int a = 0; a < MS; ++a) {
         const float r = second ? rstd[a][1] : rstd[a][0];
 #pragma unroll
-        for (int e = 0; e < n; ++e) set(a, c, e, value(a, c, e) * r * g[e] + b[e]);
+        for (int e = 0; e < n; ++e) set(a, c, e, __builtin_fmaf(value(a, c, e) * r, g[e], b[e]));
       }
       if (p.rope) {
         auto factors = [&](unsigned frame, f32x4 *f) {
@@ -269,8 +272,8 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(const GemmParams p)
 #pragma unroll
           for (int i = 0; i < n / 2; ++i) {
             const float x = value(a, c, 2 * i), y = value(a, c, 2 * i + 1), cs = f[i / 2][2 * (i & 1)], sn = f[i / 2][2 * (i & 1) + 1];
-            set(a, c, 2 * i, x * cs - y * sn);
-            set(a, c, 2 * i + 1, x * sn + y * cs);
+            set(a, c, 2 * i, __builtin_fmaf(x, cs, -(y * sn)));
+            set(a, c, 2 * i + 1, __builtin_fmaf(x, sn, y * cs));
           }
         };
         f32x4 f[2];

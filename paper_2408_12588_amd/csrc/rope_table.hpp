@@ -52,15 +52,16 @@ template <int D> __device__ constexpr RopeTable<D> rope_table = make_rope_table<
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 
-// factor of position pos >= 0 and feature pair i
+// factor of position pos >= 0 and feature pair i; the fused products are written out, so that it has the same bits wherever it is inlined
 template <int D> __device__ __forceinline__ f32x2 rope_factor(int pos, int i) {
+#pragma clang fp contract(off)
   const RopeTable<D> &t = rope_table<D>;
   f32x2 f = {t.v[0][pos % ROPE_BASE][i][0], t.v[0][pos % ROPE_BASE][i][1]};
   for (int k = 1; k < ROPE_DIGITS; ++k) {
     pos /= ROPE_BASE;
     if (pos == 0) break;
     const float c = t.v[k][pos % ROPE_BASE][i][0], s = t.v[k][pos % ROPE_BASE][i][1];
-    f = f32x2{f[0] * c - f[1] * s, f[0] * s + f[1] * c};
+    f = f32x2{__builtin_fmaf(f[0], c, -(f[1] * s)), __builtin_fmaf(f[0], s, f[1] * c)};
   }
   return f;
 }

@@ -119,6 +119,46 @@ def test_norm_and_rotation(kind, T, S, heads):
         assert err <= 1e-2 * np.abs(want).max(), (i, err, np.abs(want).max())
 
 
+MOVED = [
+    # kind, T, S, heads (of 72): the last token tile reaches back over rows of the tile before it, whatever their sizes
+    (1, 8, 1601, 16),
+    (1, 17, 1024, 16),
+    (1, 16, 1589, 16),
+    (1, 8, 1100, 12),
+    (1, 33, 301, 8),
+    (0, 5, 1999, 4),
+]
+
+
+@pytest.mark.parametrize("kind,T,S,heads", MOVED)
+def test_tokens_have_the_same_bits_in_every_tile(kind, T, S, heads):
+    """Frames (spatial) and positions (temporal) are independent: moved to other rows of x, hence to other tiles of the
+    projections, they give the same bits.  Rows that two tiles compute are stored by both, in either order."""
+    from paper_2408_12588_amd import pab, workloads as W
+    print("moved", W.KIND_NAMES[kind], T, S, heads, flush=True)
+    wl = W.Workload("moved", 1, T, S, 0, heads, 72, "bf16", 1, (1, 1, 0), 0, 0, seed=31 + S)
+    x = W.make_module_input(wl, 0, kind, 0).to(DEV)
+    w = pab.module_weights(**{n: t.to(DEV) for n, t in W.make_module_weights(wl, 0, kind).items()})
+    out = pab.pab_module_compute(kind, x, None, w, heads)
+    for by in (1, S // 5, S // 2) if kind == 1 else (1, 2):
+        moved = pab.pab_module_compute(kind, torch.roll(x, by, kind).contiguous(), None, w, heads)
+        differ = int((moved != torch.roll(out, by, kind)).any(-1).sum())
+        assert differ == 0, "moved by %d: %d tokens differ" % (by, differ)
+
+
+@pytest.mark.parametrize("tokens,hidden", [(9001, 1152), (17001, 384), (12345, 864)])
+def test_tokens_have_the_same_bits_in_every_tile_of_the_mlp(tokens, hidden):
+    from paper_2408_12588_amd import pab
+    print("moved mlp", tokens, hidden, flush=True)
+    inner, dev = 4 * hidden, lambda *a: rand(*a).to(DEV)
+    w = pab.mlp_weights(shift=dev((hidden,), 1, 0.3), scale=dev((hidden,), 2, 0.3), w1=dev((inner, hidden), 3, hidden ** -0.5),
+                        b1=dev((inner,), 4, 0.1), w2=dev((hidden, inner), 5, inner ** -0.5), b2=dev((hidden,), 6, 0.1))
+    x = dev((tokens, hidden), 7)
+    out = pab.pab_mlp_compute(x, w, inner)
+    for by in (1, 333, 1700):
+        assert torch.equal(pab.pab_mlp_compute(torch.roll(x, by, 0).contiguous(), w, inner), torch.roll(out, by, 0))
+
+
 CROSS_PAIRS = [
     # T, S, L, heads (of 72): the text's k / v projection in the launch of the query projection, as ...
     (5, 252, 60, 8),        # ... 64 x 64 tiles with K groups, ragged in the text
