@@ -20,6 +20,7 @@
 #include "gemm_heads.hpp"
 #include "gemm_stream.hpp"
 #include "gemm_tile.hpp"
+#include "launch_plan.hpp"
 #include "module_rowwise.hpp"
 
 namespace {
@@ -40,10 +41,11 @@ size_t elem_size(int dtype) { return dtype == PAB_BF16 ? 2 : 4; }
 
 // ---- launches -----------------------------------------------------------------
 
-constexpr int TILE_NWV = 8;    // wavefronts per workgroup: 256 queries share each staged K/V tile (4: 1.5-2% slower)
+using pab::GEMM_CUS;
+using pab::GemmPlan;
+using pab::TILE_NWV;
+using pab::TILE_SPLIT_G;
 constexpr int TILE_MINW = 4;   // wavefronts per SIMD the register budget is sized for
-constexpr int TILE_SPLIT_G = 4;   // key groups of a split item
-constexpr int TILE_CUS = 32;      // CUs of an XCD; a CU holds two workgroups (16 wavefronts)
 
 template <typename T, int D>
 int launch_tile(int n_batch, int n_head, int sq, int sk, long long q_bs, long long q_ss, long long kv_bs,
@@ -54,37 +56,15 @@ int launch_tile(int n_batch, int n_head, int sq, int sk, long long q_bs, long lo
   p.q_bs = q_bs; p.q_ss = q_ss; p.k_bs = kv_bs; p.k_ss = kv_ss; p.v_bs = kv_bs; p.v_ss = kv_ss;
   p.o_bs = q_bs; p.o_ss = q_ss;
   p.c = (float)(1.4426950408889634 / std::sqrt((double)D));
-  constexpr int QBLK = 32 * TILE_NWV;
-  p.n_item = (sq + QBLK - 1) / QBLK;
   // staging addresses the key tiles of one step with 32-bit byte offsets
   if (32 * TILE_SPLIT_G * kv_ss * (long long)sizeof(T) >= (1LL << 32)) return fail(PAB_EINVAL, "sequence stride too large");
   const long long n_bh = (long long)n_batch * n_head;
   if (n_bh > 0x3fffffffLL) return fail(PAB_EINVAL, "problem too large for one launch");
-  // Split items (a quarter of the queries, four key groups: a quarter of the steps) for some problems, or for all.  An XCD
-  // takes every eighth (batch, head) problem and has TILE_CUS CUs; workgroups take about the same time, so an XCD's time
-  // steps up where its workgroups pass a multiple of TILE_CUS: by half with the second workgroup of a CU (S = 1024, 16 heads:
-  // 29.0 us with 24 per XCD, 43.3 with 36).  Measured in us, 72-element heads, before -> after:
-  //   everything split where that fits one workgroup per CU (16 problems of 1024: 26.3 -> 16.1, of 300: 11.9 -> 10.8), with long
-  //   sequences up to two (32 of 1024: 27.3 -> 23.8; but 48 of 512 17.0 -> 17.6, 32 of 1590 40.8 -> 52.3); below 8 key tiles the
-  //   combination costs more (16 of 128: 7.0 -> 8.8);
-  //   else the problems that stand over the last multiple, if few (72 of 1024: 43.3 -> 32.3, 84 of 700: 31.6 -> 25.0, 204 of
-  //   1024: 86.5 -> 76.4, 40 of 3600 with 456 split items 202 -> 192; but 40 of 2400 with 608: 90 -> 97, and with fp32 rows 84 of
-  //   2484 with 468: 251 -> 286), or those over the last full round of two workgroups per CU (91 of 3066, fp32: 499 -> 472).
-  p.bh_plain = (int)n_bh;
-  p.n_split = 0;
+  const pab::ItemPlan items = pab::plan_items(n_bh, sq, sk, sizeof(T));
+  p.n_item = items.n_item;
+  p.bh_plain = (int)items.bh_plain;
+  p.n_split = (int)items.n_split;
   p.split_g = TILE_SPLIT_G;
-  const int ntile = (sk + 31) / 32;
-  const long long per_xcd = (n_bh + 7) / 8 * p.n_item, n_split = (sq + QBLK / TILE_SPLIT_G - 1) / (QBLK / TILE_SPLIT_G);
-  if (per_xcd <= TILE_CUS) {
-    const long long split_xcd = (n_bh + 7) / 8 * n_split;
-    if (ntile >= 8 && split_xcd <= (ntile >= 32 ? 2 * TILE_CUS : TILE_CUS)) p.bh_plain = 0;
-  } else if (per_xcd % TILE_CUS && ntile >= 8) {
-    const long long keep = per_xcd / TILE_CUS * TILE_CUS / p.n_item * 8;
-    const long long rest = n_bh * p.n_item % (16 * TILE_CUS);
-    if (keep < n_bh && (n_bh - keep) * n_split <= (sizeof(T) == 2 ? 15 : 12) * TILE_CUS) p.bh_plain = (int)keep;
-    else if (per_xcd > 2 * TILE_CUS && rest >= p.n_item && rest <= 4 * TILE_CUS && ntile >= 16) p.bh_plain = (int)(n_bh - rest / p.n_item);
-  }
-  if (p.bh_plain < n_bh) p.n_split = (int)n_split;
   const long long plain_wgs = (long long)(p.bh_plain + 7) / 8 * 8 * p.n_item;
   const long long grid = plain_wgs + (n_bh - p.bh_plain + 7) / 8 * 8 * p.n_split;
   if (grid > 0x7fffffffLL) return fail(PAB_EINVAL, "problem too large for one launch (%lld workgroups)", grid);
@@ -312,79 +292,6 @@ size_t module_plane_bytes(int T, int S, int L, int H, int D) {
   return ((size_t)rows * H * D * 2 + 255) / 256 * 256;
 }
 
-// ---- which projection kernel and tile: the one with the smallest estimate, in us, fitted to 100 shapes timed on the
-//      card (M 60 .. 45000, N and K 128 .. 4608; the pick was within 10% of the best in nearly all of them; K slices of 64):
-//      gemm_stream  3 + (rounds of 256 tiles) (slices t + e): t = 1.5, e = 6 at 256 features, t = 1.7, e = 8 at 288
-//                   (a tail tile of 64 / 128 / 192 token rows takes 0.50 / 0.66 / 0.82 of a full one)
-//      gemm_tile    base + slices max(latency, load l2) + load out, load = tiles / 256 + 0.25: a lone tile is bound by the
-//                   latency of its K loop, more tiles than CUs by L2 (about 60 GB/s per CU) and by their stores
-//      Both sides of the line, measured in us: 2560 x 3456 x 1152 gemm_stream 24, 128 x 128 tiles 33; 6249 x 1152 x 4608
-//      83 and 66; 1350 x 3456 x 1152 128 x 128 tiles 19, 64 x 128 23; 1260 x 576 x 2304 64 x 64 tiles 12, 128 x 128 24.
-//      K groups (odd numbers) where every workgroup has a CU to itself and there are 6 slices or more: 64 x 64 tiles, three
-//      groups, 1260 x 576 x 2304 13.9 -> 10.1, 800 x 1152 x 1152 8.7 -> 7.0, 60 x 1152 x 4608 22.8 -> 15.1, but 1260 x 288 x 288 the
-//      same 4.2, and 360 tiles on 256 CUs 30.6 -> 33.0; 64 x 128, two groups, 1260 x 1152 x 4608 29.7 -> 24.6; 128 x 128, two
-//      groups, 2800 x 1152 x 4608 47.3 -> 39.4, 500 x 4608 x 1152 16.2 -> 14.2. ----
-constexpr int GEMM_CUS = 256;
-
-struct GemmPlan {
-  int kernel;            // 8, 9: gemm_stream with that many sub-tiles per wave column; 64, 96, 128: gemm_tile, 1 more: its K groups
-  int n_mt, n_nt, ms_tail, n_units;
-  double us;
-};
-
-void plan_stream(int ns, int M, int N, int slices, GemmPlan *best) {
-  static const double part[5] = {0, 0.50, 0.66, 0.82, 1.0};
-  const int bn = 32 * ns;
-  if (N < bn || M < 64 || slices < 2) return;
-  const long long n_nt = (N + bn - 1) / bn, all = (M + 255LL) / 256 * n_nt;
-  const double tile_us = ns == 8 ? 1.5 * slices + 6.0 : 1.7 * slices + 8.0;
-  for (int less = 0; less < 3; ++less) {   // full tiles for this many rounds, the rest of the token rows as tail tiles
-    const long long rounds = (all + GEMM_CUS - 1) / GEMM_CUS - less;
-    if (rounds < 0) break;
-    const long long n_mt = std::min((long long)M / 256, rounds * GEMM_CUS / n_nt), rows = M - 256 * n_mt;
-    for (int ms = 1; ms <= 4; ++ms) {
-      if (M < 64 * ms) break;
-      const long long tail = (rows + 64 * ms - 1) / (64 * ms) * n_nt, room = rounds * GEMM_CUS - n_mt * n_nt;
-      const double tail_rounds = tail > room ? (double)((tail - room + GEMM_CUS - 1) / GEMM_CUS) : 0.0;
-      const double us = 3.0 + (rounds + tail_rounds * part[ms]) * tile_us;
-      if (n_mt * n_nt + tail <= 0x7fffffffLL && us < best->us)
-        *best = GemmPlan{ns, (int)n_mt, (int)n_nt, ms, (int)(n_mt * n_nt + tail), us};
-    }
-  }
-}
-
-void plan_tile(int kernel, int bm, int bn, double base, double latency, double l2, double out, int M, int N, int slices,
-               GemmPlan *best) {
-  const long long n_mt = ((long long)M + bm - 1) / bm, n_nt = (N + bn - 1) / bn;
-  if ((kernel & 1) && (n_mt * n_nt > GEMM_CUS || slices < 6)) return;   // K groups: one workgroup per CU
-  const double load = n_mt * n_nt / (double)GEMM_CUS + 0.25;
-  const double us = base + slices * std::max(latency, load * l2) + load * out;
-  if (n_mt * n_nt <= 0x7ffffff0LL && us < best->us) *best = GemmPlan{kernel, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), us};
-}
-
-// gemm_heads (estimate fitted like those above, whole temporal modules in us, separate pass -> gemm_heads): 1260 tokens of 576
-// 28.0 -> 23.8, 800 of 864 31.0 -> 27.2, 630 of 1152 35.3 -> 31.0; but 250 of 1152 26.2 -> 26.9, 60 of 864 22.0 -> 23.2.
-void plan_heads(int D, int M, int N, int slices, GemmPlan *best) {
-  const int bn = D == 72 ? 144 : 96;
-  const long long n_mt = (M + 63LL) / 64, n_nt = (N + bn - 1) / bn;
-  if (n_mt * n_nt > GEMM_CUS) return;
-  *best = GemmPlan{bn, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), 5.5 + 0.3 * slices + n_mt * n_nt / (double)GEMM_CUS};
-}
-
-GemmPlan plan_gemm(int M, int N, int K) {
-  GemmPlan best{0, 0, 0, 0, 0, 1e30};
-  const int slices = (K + 63) / 64;
-  plan_tile(64, 64, 64, 2.9, 0.26, 0.25, 0.55, M, N, slices, &best);
-  plan_tile(65, 64, 64, 2.95, 0.185, 0.17, 0.55, M, N, slices, &best);
-  plan_tile(96, 64, 128, 3.3, 0.32, 0.36, 1.1, M, N, slices, &best);
-  plan_tile(97, 64, 128, 3.2, 0.285, 0.24, 1.1, M, N, slices, &best);
-  plan_tile(128, 128, 128, 3.5, 0.55, 0.52, 2.2, M, N, slices, &best);
-  plan_tile(129, 128, 128, 3.6, 0.48, 0.45, 1.6, M, N, slices, &best);
-  plan_stream(8, M, N, slices, &best);
-  plan_stream(9, M, N, slices, &best);
-  return best;
-}
-
 template <int EPI>
 void launch_gemm_kernel(const GemmPlan &g, const pab::GemmParams &p, hipStream_t st) {
   const dim3 persistent((unsigned)std::min(g.n_units, GEMM_CUS)), tiles((unsigned)((g.n_units + 7) / 8 * 8));
@@ -436,7 +343,7 @@ int launch_gemm(int M, int N, int K, const void *A, const void *W, const void *b
   pab::GemmParams p;
   int rc = gemm_params(&p, M, N, K, A, W, bias, C, ldc, n_split, plane_stride);
   if (rc != PAB_OK) return rc;
-  const GemmPlan g = plan_gemm(M, N, K);
+  const GemmPlan g = pab::plan_gemm(M, N, K);
   if ((rc = gemm_planned(g, &p)) != PAB_OK) return rc;
   if (act) launch_gemm_kernel<pab::GEMM_GELU>(g, p, st);
   else launch_gemm_kernel<pab::GEMM_PLAIN>(g, p, st);
@@ -445,39 +352,22 @@ int launch_gemm(int M, int N, int K, const void *A, const void *W, const void *b
   return PAB_OK;
 }
 
-// Two projections of the same K in one launch: C = A W^T and, side by side in n_split-wide planes, C2 = A2 W2^T.  The second
-// one (few rows: the text of the cross module) rides along where it costs no round of its own: as further tiles of
-// gemm_tile, or in the room that the last round of gemm_stream leaves (there with 64 rows or more, the least a tile has); else it
-// is launched by itself (25440 and 120 tokens: 12 units of room for 18).  Cross modules in us, two launches -> one: 17408 and 300
-// tokens of 1152 features 149 -> 144, 34000 and 120 of 864 147 -> 143; 2048 and 120 of 1152 39.5 -> 33.0, 6000 and 300 of 864
-// 59.4 -> 54.1, 1260 and 60 of 576 20.0 -> 15.4.
+// Two projections of the same K, in one launch where plan_pair says so: C = A W^T and, side by side in n_split-wide planes, C2 = A2 W2^T.
 int launch_gemm_pair(int M, int N, int K, const void *A, const void *W, const void *bias, void *C, int M2, int N2, const void *A2,
                      const void *W2, const void *bias2, void *C2, long long ldc, int n_split, long long plane_stride,
                      hipStream_t st) {
   pab::GemmParams p, p2;
   int rc = gemm_params(&p, M, N, K, A, W, bias, C, ldc, n_split, plane_stride);
   if (rc != PAB_OK || (rc = gemm_params(&p2, M2, N2, K, A2, W2, bias2, C2, ldc, n_split, plane_stride)) != PAB_OK) return rc;
-  GemmPlan g = plan_gemm(M, N, K);
-  long long units2 = 0;
-  if (g.kernel == 8 || g.kernel == 9) {
-    const int bn = 32 * g.kernel, room = (GEMM_CUS - g.n_units % GEMM_CUS) % GEMM_CUS;
-    p.ms2 = M2 >= 128 ? 2 : 1;
-    p.n_nt2 = (N2 + bn - 1) / bn;
-    units2 = (M2 + 64LL * p.ms2 - 1) / (64 * p.ms2) * p.n_nt2;
-    if (M2 < 64 || N2 < bn || units2 > room) units2 = 0;
-  } else if (g.kernel) {
-    const int bm = g.kernel >= 128 ? 128 : 64, bn = g.kernel < 96 ? 64 : 128;
-    p.n_nt2 = (N2 + bn - 1) / bn;
-    units2 = ((long long)M2 + bm - 1) / bm * p.n_nt2;
-    if (g.n_units + units2 > (g.kernel & 1 ? (long long)GEMM_CUS : 0x7ffffff0LL)) units2 = 0;
-  }
-  if (!units2) {
+  const pab::PairPlan pair = pab::plan_pair(M, N, M2, N2, K);
+  if (!pair.n_units2) {
     if ((rc = launch_gemm(M, N, K, A, W, bias, C, ldc, N, 0, st)) != PAB_OK) return rc;
     return launch_gemm(M2, N2, K, A2, W2, bias2, C2, ldc, n_split, plane_stride, st);
   }
   p.A2 = p2.A; p.W2 = p2.W; p.bias2 = p2.bias; p.C2 = p2.C;
-  p.M2 = M2; p.N2 = N2; p.n_units2 = (int)units2;
-  g.n_units += (int)units2;
+  p.M2 = M2; p.N2 = N2; p.n_units2 = (int)pair.n_units2; p.n_nt2 = pair.n_nt2; p.ms2 = pair.ms2;
+  GemmPlan g = pair.first;
+  g.n_units += p.n_units2;
   if ((rc = gemm_planned(g, &p)) != PAB_OK) return rc;
   launch_gemm_kernel<pab::GEMM_PLAIN>(g, p, st);
   const hipError_t e = hipGetLastError();
@@ -519,39 +409,30 @@ int launch_qk_norm(int n_tok, int H, int D, int S, int rope, void *q, void *k, c
   return PAB_OK;
 }
 
-// q, k, v projections of a self-attention module with layernorm2 (+ rotation) of q and k, whichever is estimated fastest:
-//   the best plain projection and a pass over q and k (each read and written once at 4.8 TB/s, 3 us at least);
-//   heads of 72: in the epilogue of the large-tile projection (it costs a tile 3 us);
-//   few tokens, one tile of two (heads of 32: three) heads per CU: in the epilogue of gemm_heads.
+// q, k, v projections of a self-attention module with layernorm2 (+ rotation) of q and k: plan_qkv says in which kernel
 int launch_qkv(int n_tok, int H, int D, int S, int rope, const void *h, const pab_module_weights *w, void *q,
                long long plane_elems, hipStream_t st) {
-  const int C = H * D, slices = (C + 63) / 64;
+  const int C = H * D;
   pab::GemmParams p;
   int rc = gemm_params(&p, n_tok, 3 * C, C, h, w->w_qkv, w->b_qkv, q, C, C, plane_elems);
   if (rc != PAB_OK) return rc;
-  GemmPlan plain = plan_gemm(n_tok, 3 * C, C), fused{0, 0, 0, 0, 0, 1e30}, heads{0, 0, 0, 0, 0, 1e30};
-  if (D == 72 && C % 288 == 0 && (!rope || S >= 64)) plan_stream(9, n_tok, 3 * C, slices, &fused);
-  fused.us += 3.0 * (fused.n_units / (double)GEMM_CUS + 0.5);
-  plan_heads(D, n_tok, 3 * C, slices, &heads);
-  plain.us += 3.0 + 8e-6 * n_tok * C / 4.8;
+  const pab::QkvPlan plan = pab::plan_qkv(n_tok, H, D, S, rope);
+  if ((rc = gemm_planned(plan.gemm, &p)) != PAB_OK) return rc;
   p.gq = static_cast<const pab::bf16_t *>(w->gamma_q); p.bq = static_cast<const pab::bf16_t *>(w->beta_q);
   p.gk = static_cast<const pab::bf16_t *>(w->gamma_k); p.bk = static_cast<const pab::bf16_t *>(w->beta_k);
   p.S = S; p.rope = rope; p.eps = 1e-6f;
-  if (heads.kernel && heads.us < std::min(fused.us, plain.us)) {
-    if ((rc = gemm_planned(heads, &p)) != PAB_OK) return rc;
-    const dim3 tiles((unsigned)((heads.n_units + 7) / 8 * 8)), block(768);
+  if (plan.way == pab::QKV_HEADS) {
+    const dim3 tiles((unsigned)((p.n_units + 7) / 8 * 8)), block(768);
     if (D == 72) hipLaunchKernelGGL((pab::gemm_heads_kernel<2, 3, 2, 3, 3, 2, 72>), tiles, block, 0, st, p);
     else hipLaunchKernelGGL((pab::gemm_heads_kernel<2, 3, 2, 2, 3, 2, 32>), tiles, block, 0, st, p);
     return PAB_OK;
   }
-  if (fused.kernel && fused.us < plain.us) {
-    if ((rc = gemm_planned(fused, &p)) != PAB_OK) return rc;
-    hipLaunchKernelGGL((pab::gemm_stream_kernel<9, 3, pab::GEMM_NORM>), dim3((unsigned)std::min(fused.n_units, GEMM_CUS)),
+  if (plan.way == pab::QKV_STREAM) {
+    hipLaunchKernelGGL((pab::gemm_stream_kernel<9, 3, pab::GEMM_NORM>), dim3((unsigned)std::min(p.n_units, GEMM_CUS)),
                        dim3(512), 0, st, p);
     return PAB_OK;
   }
-  if ((rc = gemm_planned(plain, &p)) != PAB_OK) return rc;
-  launch_gemm_kernel<pab::GEMM_PLAIN>(plain, p, st);
+  launch_gemm_kernel<pab::GEMM_PLAIN>(plan.gemm, p, st);
   return launch_qk_norm(n_tok, H, D, S, rope, q, static_cast<pab::bf16_t *>(q) + plane_elems, w, st);
 }
 

@@ -120,7 +120,7 @@ def test_norm_and_rotation(kind, T, S, heads):
 
 
 MOVED = [
-    # kind, T, S, heads (of 72): the last token tile reaches back over rows of the tile before it, whatever their sizes
+    # kind, T, S, heads (of 72): tail tiles beside full ones, the last of most reaching back over rows of the one before it
     (1, 8, 1601, 16),
     (1, 17, 1024, 16),
     (1, 16, 1589, 16),
@@ -164,12 +164,23 @@ CROSS_PAIRS = [
     (5, 252, 60, 8),        # ... 64 x 64 tiles with K groups, ragged in the text
     (1, 1, 1, 4),           # ... one token, one text token
     (12, 500, 300, 12),     # ... more tiles than CUs
-    (8, 1590, 64, 16),      # ... tiles of the last round of gemm_stream, one of 64 rows
-    (16, 1590, 131, 16),    # ... 128-row tiles, the second moved back
-    (16, 1590, 63, 16),     # fewer than 64 text tokens: by itself
+    (1, 900, 250, 16),      # ... the last of the K groups' 256 workgroups
+    (17, 1024, 64, 16),     # ... tiles of the last round of gemm_stream, 256 features: one of 64 rows
+    (17, 1024, 100, 16),    # ... two of 64 rows, the second moved back
+    (17, 1024, 131, 16),    # ... two of 128 rows, the second moved back
+    (20, 1700, 64, 12),     # ... 288 features: one of 64 rows
+    (20, 1700, 131, 12),    # ... two of 128 rows, the second moved back
+    # ... or in one of its own:
+    (8, 1590, 64, 16),      # no room in the last round
+    (16, 1590, 131, 16),
     (16, 1590, 500, 16),    # long text
-    (1, 900, 250, 16),      # K groups, more tiles than CUs in all: by itself
+    (17, 1024, 63, 16),     # fewer than 64 text tokens: less than a tile of gemm_stream
+    (16, 1590, 63, 16),     # ... and no room
+    (1, 1300, 250, 16),     # K groups, more tiles than CUs in all
 ]
+# of each: kernel of the query projection; rows / 64 of gemm_stream's tiles for the text; whether the text rides along
+CROSS_PAIR_PATHS = [(65, 0, True), (64, 0, True), (128, 0, True), (97, 0, True), (8, 1, True), (8, 1, True), (8, 2, True),
+                    (9, 1, True), (9, 2, True), (8, 0, False), (8, 0, False), (8, 0, False), (8, 0, False), (8, 0, False), (97, 0, False)]
 
 
 @pytest.mark.parametrize("T,S,L,heads", CROSS_PAIRS)

@@ -1,0 +1,105 @@
+"""Which kernel, tile and item a shape takes: the library's planning header, compiled by itself for the host.  The GPU
+tests of the kernels choose their shapes for the path that they run; here that choice is held, so that a change of a
+planner's constant cannot silently empty one of them."""
+import os
+import subprocess
+
+import pytest
+
+import test_gpu_gemm as G
+import test_gpu_parity as P
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+QUERY = r'''
+#include <cstdio>
+#include <cstring>
+#include "launch_plan.hpp"
+int main() {
+  char what[16];
+  while (scanf("%15s", what) == 1) {
+    if (!strcmp(what, "gemm")) {
+      int M, N, K;
+      if (scanf("%d %d %d", &M, &N, &K) != 3) return 1;
+      const pab::GemmPlan g = pab::plan_gemm(M, N, K);
+      printf("%d %d %d %d %d\n", g.kernel, g.n_mt, g.n_nt, g.ms_tail, g.n_units);
+    } else if (!strcmp(what, "pair")) {
+      int M, N, M2, N2, K;
+      if (scanf("%d %d %d %d %d", &M, &N, &M2, &N2, &K) != 5) return 1;
+      const pab::PairPlan p = pab::plan_pair(M, N, M2, N2, K);
+      printf("%d %d %d %lld\n", p.first.kernel, p.first.n_units, p.ms2, p.n_units2);
+    } else if (!strcmp(what, "qkv")) {
+      int n, H, D, S, rope;
+      if (scanf("%d %d %d %d %d", &n, &H, &D, &S, &rope) != 5) return 1;
+      const pab::QkvPlan p = pab::plan_qkv(n, H, D, S, rope);
+      printf("%d %d %d %d\n", p.way, p.gemm.n_mt, p.gemm.ms_tail, p.gemm.n_units);
+    } else {
+      long long n_bh; int sq, sk, size;
+      if (scanf("%lld %d %d %d", &n_bh, &sq, &sk, &size) != 4) return 1;
+      const pab::ItemPlan p = pab::plan_items(n_bh, sq, sk, size);
+      printf("%d %lld %lld\n", p.n_item, p.bh_plain, p.n_split);
+    }
+    fflush(stdout);
+  }
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "query.cpp").write_text(QUERY)
+    exe = str(d / "query")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-I", os.path.join(ROOT, "paper_2408_12588_amd", "csrc"), "-o", exe,
+                    str(d / "query.cpp")], check=True, timeout=120)
+
+    def ask(what, rows):
+        text = "".join("%s %s\n" % (what, " ".join(str(int(x)) for x in r)) for r in rows)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True, timeout=60).stdout
+        got = [tuple(int(x) for x in line.split()) for line in out.splitlines()]
+        assert len(got) == len(rows)
+        return got
+
+    return ask
+
+
+def items_of(shape):
+    """(problems, queries, keys, bytes per element) of a call that runs on the tile kernel."""
+    kind, T, S, L, H, D, dtype = shape
+    size = 2 if dtype == "bf16" else 4
+    return {0: (T * H, S, S, size), 1: (S * H, T, T, size), 2: (H, T * S, L, size)}[kind]
+
+
+def test_projection_shapes_take_the_kernels_they_are_chosen_for(plan):
+    got = plan("gemm", G.SHAPES)
+    assert [g[0] for g in got] == [8, 8, 8, 8, 9, 9, 128, 96, 64, 64]
+    tails = [g[3] for g in got[:6]]
+    assert (tails[0], tails[1], tails[4], tails[5]) == (3, 1, 2, 1)
+    assert [g[1] > 0 for g in got[:6]] == [False, True, True, False, False, True]    # full tiles beside the tail tiles
+    assert all(g[4] > 256 for g in got[:1] + got[2:3] + got[5:6])                    # more than one tile per CU
+    assert [g[0] for g in plan("gemm", G.K_GROUPS)] == [65, 65, 65, 65, 97, 97, 129]
+    assert [g[0] for g in plan("gemm", G.HALF_SLICES)] == [8, 9, 8, 65, 64]
+
+
+def test_module_shapes_take_the_ways_they_are_chosen_for(plan):
+    qkv = lambda shapes: plan("qkv", [(T * S, H, D, S, kind == 1) for kind, T, S, H, D in shapes])
+    assert [q[0] for q in qkv([m + (72,) for m in G.MODULES])] == [1, 1, 1, 1, 0]
+    assert [q[0] for q in qkv(G.FEW_TOKENS)] == [2] * 6
+    # moved tokens: in the epilogue of the large tiles, with tail tiles of which most reach back over rows of another
+    moved = qkv([m + (72,) for m in G.MOVED])
+    assert all(way == 1 and ms < 4 for way, n_mt, ms, units in moved)
+    assert sum((T * S - 256 * n_mt) % (64 * ms) > 0 for (kind, T, S, H), (way, n_mt, ms, units) in zip(G.MOVED, moved)) >= 4
+
+
+def test_text_projection_rides_where_it_is_meant_to(plan):
+    got = plan("pair", [(T * S, 72 * H, L, 144 * H, 72 * H) for T, S, L, H in G.CROSS_PAIRS])
+    for shape, want, (kernel, units, ms2, units2) in zip(G.CROSS_PAIRS, G.CROSS_PAIR_PATHS, got, strict=True):
+        assert (kernel, ms2 if units2 and kernel < 16 else 0, units2 > 0) == want, shape
+        if units2 and kernel in (8, 9):       # no round of its own
+            assert units % 256 + units2 <= 256
+
+
+def test_split_shapes_are_split(plan):
+    part = {(0, 7, 700, 0, 12, 72, "bf16"): 4, (0, 9, 513, 0, 11, 32, "f32"): 19}
+    calls = [items_of(shape) for shape in P.SPLIT_SHAPES]
+    for shape, (n_bh, sq, sk, size), (n_item, bh_plain, n_split) in zip(P.SPLIT_SHAPES, calls, plan("items", calls)):
+        assert n_bh - bh_plain == part.get(shape, n_bh) and n_split == -(-sq // 64), shape
