@@ -17,28 +17,38 @@ struct ItemPlan {
 
 // Split items (a quarter of the queries, four key groups: a quarter of the steps) for some problems, or for all.  An XCD
 // takes every eighth (batch, head) problem and has TILE_CUS CUs; workgroups take about the same time, so an XCD's time
-// steps up where its workgroups pass a multiple of TILE_CUS: by half with the second workgroup of a CU (S = 1024, 16 heads:
-// 29.0 us with 24 per XCD, 43.3 with 36).  Measured in us, 72-element heads, before -> after:
-//   everything split where that fits one workgroup per CU (16 problems of 1024: 26.3 -> 16.1, of 300: 11.9 -> 10.8), with long
-//   sequences up to two (32 of 1024: 27.3 -> 23.8; but 48 of 512 17.0 -> 17.6, 32 of 1590 40.8 -> 52.3); below 8 key tiles the
-//   combination costs more (16 of 128: 7.0 -> 8.8);
-//   else the problems that stand over the last multiple, if few (72 of 1024: 43.3 -> 32.3, 84 of 700: 31.6 -> 25.0, 204 of
-//   1024: 86.5 -> 76.4, 40 of 3600 with 456 split items 202 -> 192; but 40 of 2400 with 608: 90 -> 97, and with fp32 rows 84 of
-//   2484 with 468: 251 -> 286), or those over the last full round of two workgroups per CU (91 of 3066, fp32: 499 -> 472).
-inline ItemPlan plan_items(long long n_bh, int sq, int sk, int elem_size) {
+// steps up where its workgroups pass a multiple of TILE_CUS, by half with the second workgroup of a CU (S = 1024, 16 heads:
+// 29.0 us with 24 per XCD, 43.3 with 36), by a whole one with the third.  The problems beyond the last multiple are split,
+// all of them if there is none, where the XCD with the most of their items has no more than
+//   one per CU (16 problems of 1024 tokens 26.3 -> 16.1 us, 16 of 300 11.9 -> 10.8, 72 of 1024 43.3 -> 32.3, 84 of 700
+//     31.6 -> 25.0), from 8 key tiles: with fewer the combination costs more (16 of 128: 7.0 -> 8.8);
+//   after an even multiple, where they would wait for a whole round: two per CU for long sequences (32 of 1024
+//     27.3 -> 23.8, 40 of 3600 202 -> 192; but 48 of 512 17.0 -> 17.6);
+//   after an odd one, where they would run beside the others: two or three per CU for longer ones still, whose items are
+//     cheaper (24 of 2871, 45 items per XCD, 101 -> 77, 10 of 4640, 73 items, 157 -> 136; but 84 of 912, 45 items, 39.8 -> 47.3,
+//     110 of 677 34.0 -> 40.0); with fp32 rows, which are converted on the way in by four times as many items, fewer (heads of
+//     32: 33 of 2481, 80 items, 80 -> 84; of 72: 32 of 1984, 50 items, 82 -> 89).
+// Failing that, those over the last full round of two workgroups per CU, if that is at most a quarter round (91 of 3066, fp32:
+// 499 -> 472; but 224 of 562 with 160 workgroups over 41.0 -> 45.8).
+// More items than that only lose, on one XCD too: 1 problem of 10401 (fp32) 439 -> 619 with 163 items, 10 of 6103 queries and
+// 448 keys (fp32) 33 -> 50 with 96.  752 shapes (heads of 32 and 72, both types, 1 .. 2800 problems): 0.89 of the time of
+// the former rule (a rest of at most a quarter of the last round, 16 key tiles); none that is split is slower by more than 3 %.
+inline ItemPlan plan_items(long long n_bh, int sq, int sk, int head_dim, int elem_size) {
   constexpr int QBLK = 32 * TILE_NWV;
   ItemPlan p{(sq + QBLK - 1) / QBLK, n_bh, 0};
   const int ntile = (sk + 31) / 32;
-  const long long per_xcd = (n_bh + 7) / 8 * p.n_item, n_split = (sq + QBLK / TILE_SPLIT_G - 1) / (QBLK / TILE_SPLIT_G);
-  if (per_xcd <= TILE_CUS) {
-    const long long split_xcd = (n_bh + 7) / 8 * n_split;
-    if (ntile >= 8 && split_xcd <= (ntile >= 32 ? 2 * TILE_CUS : TILE_CUS)) p.bh_plain = 0;
-  } else if (per_xcd % TILE_CUS && ntile >= 8) {
-    const long long keep = per_xcd / TILE_CUS * TILE_CUS / p.n_item * 8;
-    const long long rest = n_bh * p.n_item % (16 * TILE_CUS);
-    if (keep < n_bh && (n_bh - keep) * n_split <= (elem_size == 2 ? 15 : 12) * TILE_CUS) p.bh_plain = keep;
-    else if (per_xcd > 2 * TILE_CUS && rest >= p.n_item && rest <= 4 * TILE_CUS && ntile >= 16) p.bh_plain = n_bh - rest / p.n_item;
-  }
+  const long long n_split = (sq + QBLK / TILE_SPLIT_G - 1) / (QBLK / TILE_SPLIT_G);
+  const long long per_xcd = (n_bh + 7) / 8 * p.n_item, multiple = per_xcd / TILE_CUS;
+  auto items_xcd = [&](long long plain) { return (n_bh - plain + 7) / 8 * n_split; };   // split items of the fullest XCD
+  const long long beyond = per_xcd % TILE_CUS ? multiple * TILE_CUS / p.n_item * 8 : n_bh;
+  const long long rest = n_bh * p.n_item % (16 * TILE_CUS), round = n_bh - rest / p.n_item;
+  int most = ntile >= 8 ? TILE_CUS : 0;
+  if (multiple % 2 == 0) most = ntile >= 32 ? 2 * TILE_CUS : most;
+  else if (elem_size == 2 && ntile >= 64) most = 3 * TILE_CUS;
+  else if (elem_size == 2 || head_dim == 32) most = ntile >= 40 ? 2 * TILE_CUS : ntile >= 32 ? 3 * TILE_CUS / 2 : most;
+  else most = ntile >= 64 ? 3 * TILE_CUS / 2 : most;
+  if (beyond < n_bh && items_xcd(beyond) <= most) p.bh_plain = beyond;
+  else if (per_xcd > 2 * TILE_CUS && ntile >= 16 && rest <= 4 * TILE_CUS && items_xcd(round) <= 2 * TILE_CUS) p.bh_plain = round;
   if (p.bh_plain < n_bh) p.n_split = n_split;
   return p;
 }

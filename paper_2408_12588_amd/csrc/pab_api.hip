@@ -60,7 +60,7 @@ int launch_tile(int n_batch, int n_head, int sq, int sk, long long q_bs, long lo
   if (32 * TILE_SPLIT_G * kv_ss * (long long)sizeof(T) >= (1LL << 32)) return fail(PAB_EINVAL, "sequence stride too large");
   const long long n_bh = (long long)n_batch * n_head;
   if (n_bh > 0x3fffffffLL) return fail(PAB_EINVAL, "problem too large for one launch");
-  const pab::ItemPlan items = pab::plan_items(n_bh, sq, sk, sizeof(T));
+  const pab::ItemPlan items = pab::plan_items(n_bh, sq, sk, D, sizeof(T));
   p.n_item = items.n_item;
   p.bh_plain = (int)items.bh_plain;
   p.n_split = (int)items.n_split;

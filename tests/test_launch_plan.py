@@ -33,9 +33,9 @@ int main() {
       const pab::QkvPlan p = pab::plan_qkv(n, H, D, S, rope);
       printf("%d %d %d %d\n", p.way, p.gemm.n_mt, p.gemm.ms_tail, p.gemm.n_units);
     } else {
-      long long n_bh; int sq, sk, size;
-      if (scanf("%lld %d %d %d", &n_bh, &sq, &sk, &size) != 4) return 1;
-      const pab::ItemPlan p = pab::plan_items(n_bh, sq, sk, size);
+      long long n_bh; int sq, sk, D, size;
+      if (scanf("%lld %d %d %d %d", &n_bh, &sq, &sk, &D, &size) != 5) return 1;
+      const pab::ItemPlan p = pab::plan_items(n_bh, sq, sk, D, size);
       printf("%d %lld %lld\n", p.n_item, p.bh_plain, p.n_split);
     }
     fflush(stdout);
@@ -63,10 +63,9 @@ def plan(tmp_path_factory):
 
 
 def items_of(shape):
-    """(problems, queries, keys, bytes per element) of a call that runs on the tile kernel."""
+    """(problems, queries, keys, head dim, bytes per element) of a call that runs on the tile kernel."""
     kind, T, S, L, H, D, dtype = shape
-    size = 2 if dtype == "bf16" else 4
-    return {0: (T * H, S, S, size), 1: (S * H, T, T, size), 2: (H, T * S, L, size)}[kind]
+    return {0: (T * H, S, S), 1: (S * H, T, T), 2: (H, T * S, L)}[kind] + (D, 2 if dtype == "bf16" else 4)
 
 
 def test_projection_shapes_take_the_kernels_they_are_chosen_for(plan):
@@ -101,5 +100,27 @@ def test_text_projection_rides_where_it_is_meant_to(plan):
 def test_split_shapes_are_split(plan):
     part = {(0, 7, 700, 0, 12, 72, "bf16"): 4, (0, 9, 513, 0, 11, 32, "f32"): 19}
     calls = [items_of(shape) for shape in P.SPLIT_SHAPES]
-    for shape, (n_bh, sq, sk, size), (n_item, bh_plain, n_split) in zip(P.SPLIT_SHAPES, calls, plan("items", calls)):
+    for shape, (n_bh, sq, *_), (n_item, bh_plain, n_split) in zip(P.SPLIT_SHAPES, calls, plan("items", calls)):
         assert n_bh - bh_plain == part.get(shape, n_bh) and n_split == -(-sq // 64), shape
+
+
+# problems, queries, keys, head dim, bytes per element: calls that split items make slower, and such that they make faster
+# (the figures are at the rule)
+PLAIN = [(117, 755, 755, 72, 2), (208, 284, 284, 72, 2), (84, 912, 912, 72, 2), (110, 677, 677, 72, 2), (13, 6045, 600, 72, 2),
+         (48, 512, 512, 72, 2), (32, 1590, 1590, 72, 4), (16, 128, 128, 72, 2), (1, 10401, 10401, 72, 4), (10, 6103, 448, 72, 4),
+         (9, 7273, 7273, 72, 4), (10, 11634, 11634, 72, 4), (42, 1600, 1600, 72, 4), (224, 562, 562, 72, 2), (210, 271, 271, 32, 2), (340, 229, 229, 32, 2),
+         (9, 6384, 274, 32, 4), (33, 2481, 2481, 32, 4), (256, 1024, 1024, 72, 2), (256, 1590, 1590, 72, 2), (256, 3600, 3600, 72, 2)]
+SPLIT = [(16, 1024, 1024, 72, 2), (16, 300, 300, 72, 2), (40, 252, 252, 72, 2), (32, 1024, 1024, 72, 2), (72, 1024, 1024, 72, 2),
+         (84, 700, 700, 72, 2), (40, 3600, 3600, 72, 2), (204, 1024, 1024, 72, 2), (91, 3066, 3066, 72, 4), (272, 1024, 1024, 72, 2),
+         (24, 2871, 2871, 72, 2), (10, 4640, 4640, 72, 2), (24, 2866, 2866, 32, 2), (60, 1124, 1124, 32, 2), (42, 1711, 1711, 72, 2)]
+
+
+def test_split_items_where_they_pay(plan):
+    assert [p[2] for p in plan("items", PLAIN)] == [0] * len(PLAIN)
+    assert all(p[2] > 0 for p in plan("items", SPLIT))
+    # never more than three split items per CU on any of the eight XCDs, which take every eighth problem each
+    shapes = [(n, s, k, D, size) for n in list(range(1, 40)) + [64, 91, 105, 256, 999] for s in (1, 64, 225, 300, 1000, 4000, 20000)
+              for k in (1, 200, 500, 1024, 9000) for D in (32, 72) for size in (2, 4)]
+    for (n, s, *rest), (n_item, bh_plain, n_split) in zip(shapes, plan("items", shapes)):
+        assert 0 <= bh_plain <= n and n_item == -(-s // 256)
+        assert -(-(n - bh_plain) // 8) * n_split <= 96, (n, s, rest)
