@@ -51,6 +51,8 @@ struct GemmParams {
   int n_split;          // features per output plane (N: one plane; else a multiple of 8)
   long long plane_stride;
   int n_mt, n_nt;       // token / feature tiles (gemm_stream: n_mt full token tiles)
+  int by_feature;       // gemm_tile, gemm_heads: 1: consecutive tiles share their features, 0: their tokens,
+  int n_inner, n_inner2;   // ... as many as there are token (1) or feature tiles (0), of the first and of the second problem
   int ms_tail;          // gemm_stream: the token rows behind the full tiles are cut into tiles of 64 ms_tail rows
   int n_units;          // gemm_stream: full tiles (n_mt x n_nt), then tail tiles, then those of the second problem
   // GEMM_PLAIN: a second problem of the same K, ldc, n_split and plane_stride in the same launch (n_units2 = 0: none)

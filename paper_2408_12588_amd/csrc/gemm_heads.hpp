@@ -32,11 +32,12 @@ __global__ __launch_bounds__(64 * WM * WN * KG, WM * WN * KG / 4) void gemm_head
   const int wm = wave / WN, wn = wave % WN;
   const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) unsigned char *)smem) + NST * STAGE * kg;
 
-  // every XCD takes a contiguous run of tiles, feature tiles of a token tile next to each other
+  // every XCD takes a contiguous run of tiles, in the order in which it touches fewer rows (tile_order in launch_plan.hpp)
   const int n_tiles = p.n_mt * p.n_nt, per = (n_tiles + 7) >> 3;
   const int id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if ((int)(blockIdx.x >> 3) >= per || id >= n_tiles) return;
-  const int m0 = id / p.n_nt * BM, n0 = id % p.n_nt * BN;
+  const int outer = id / p.n_inner, in = id - outer * p.n_inner;
+  const int m0 = (p.by_feature ? in : outer) * BM, n0 = (p.by_feature ? outer : in) * BN;
   const int M = p.M, N = p.N, K = p.K, nk = (K + BK - 1) / BK;
 
   // round r copies stage rows 8 r .. 8 r + 7, token rows first; rows past the matrix re-read its last one

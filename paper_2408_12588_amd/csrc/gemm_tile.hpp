@@ -42,7 +42,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, KG > 1 ? WM * WN * KG / 4 : 2) v
   const unsigned lds_all = (unsigned)(size_t)((__attribute__((address_space(3))) unsigned char *)smem);
   const unsigned lds0 = lds_all + NST * STAGE * kg;      // the group's ring
 
-  // every XCD takes a contiguous run of tiles, feature tiles of a token tile next to each other
+  // every XCD takes a contiguous run of tiles, in the order in which it touches fewer rows (tile_order in launch_plan.hpp)
   constexpr bool PAIR = EPI == GEMM_PLAIN;               // the tiles of a second problem follow those of the first
   const int n_first = p.n_mt * p.n_nt, n_tiles = n_first + (PAIR ? p.n_units2 : 0), per = (n_tiles + 7) >> 3;
   int id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
@@ -51,8 +51,9 @@ __global__ __launch_bounds__(64 * WM * WN * KG, KG > 1 ? WM * WN * KG / 4 : 2) v
   id -= second ? n_first : 0;
   const bf16_t *A = second ? p.A2 : p.A, *W = second ? p.W2 : p.W, *bias = second ? p.bias2 : p.bias;
   bf16_t *C = second ? p.C2 : p.C;
-  const int M = second ? p.M2 : p.M, N = second ? p.N2 : p.N, n_nt = second ? p.n_nt2 : p.n_nt;
-  const int m0 = id / n_nt * BM, n0 = id % n_nt * BN;
+  const int M = second ? p.M2 : p.M, N = second ? p.N2 : p.N, inner = second ? p.n_inner2 : p.n_inner;
+  const int outer = id / inner, in = id - outer * inner;
+  const int m0 = (p.by_feature ? in : outer) * BM, n0 = (p.by_feature ? outer : in) * BN;
   const int K = p.K, nk = (K + BK - 1) / BK;
 
   // round r = wave + NW i: stage rows 8 r .. 8 r + 7, token rows first.  Rows past the matrix re-read its last row; what

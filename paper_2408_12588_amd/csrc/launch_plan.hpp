@@ -53,8 +53,8 @@ inline ItemPlan plan_items(long long n_bh, int sq, int sk, int head_dim, int ele
   return p;
 }
 
-// ---- which projection kernel and tile: the one with the smallest estimate, in us, fitted to 100 shapes timed on the
-//      card (M 60 .. 45000, N and K 128 .. 4608; the pick was within 10% of the best in nearly all of them; K slices of 64):
+// ---- which projection kernel and tile: the one with the smallest estimate, in us, fitted to shapes timed on the
+//      card (1358 of them, M 16 .. 45000, N and K 64 .. 4608: the picks take 1.006 of the best kernel's time; K slices of 64):
 //      gemm_stream  3 + (rounds of 256 tiles) (slices t + e): t = 1.5, e = 6 at 256 features, t = 1.7, e = 8 at 288
 //                   (a tail tile of 64 / 128 / 192 token rows takes 0.50 / 0.66 / 0.82 of a full one)
 //      gemm_tile    base + slices max(latency, load l2) + load out, load = tiles / 256 + 0.25: a lone tile is bound by the
@@ -71,7 +71,23 @@ struct GemmPlan {
   int kernel;            // 8, 9: gemm_stream with that many sub-tiles per wave column; 64, 96, 128: gemm_tile, 1 more: its K groups
   int n_mt, n_nt, ms_tail, n_units;
   double us;
+  int by_feature;        // gemm_tile, gemm_heads: the order of the tiles
 };
+
+// Order of the tiles, of which an XCD takes a contiguous eighth: along the features of a token tile, or (1) along the tokens of
+// a feature tile.  With few tokens the weights are the larger operand, and eighths along the features have every XCD load most
+// of them: the second order is taken where it loads half the rows or fewer.  In us, the same weights each time / others each
+// time: 600 x 3456 x 1152 15.3 -> 13.5 / 15.6 -> 15.1, 400 x 4608 x 1152 14.4 -> 9.2 / 14.8 -> 11.1, MLP of 400 tokens and 1152 features
+// 35.7 -> 31.7.  With less to gain it costs the attention kernel behind a q / k / v projection as much (900 x 2592 x 864, 0.52 of
+// the rows: 11.8 -> 13.1).
+inline int tile_order(int bm, int bn, long long n_mt, long long n_nt) {
+  const long long all = n_mt * n_nt, run = (all + 7) / 8;
+  auto rows = [&](long long inner, long long outer, int b_inner, int b_outer) {   // of a run along `inner`
+    const long long touched = (run + inner - 1) / inner + (run % inner && all > run ? 1 : 0);
+    return std::min(inner, run) * b_inner + std::min(outer, touched) * b_outer;
+  };
+  return 2 * rows(n_mt, n_nt, bm, bn) <= rows(n_nt, n_mt, bn, bm);
+}
 
 inline void plan_stream(int ns, int M, int N, int slices, GemmPlan *best) {
   static const double part[5] = {0, 0.50, 0.66, 0.82, 1.0};
@@ -89,7 +105,7 @@ inline void plan_stream(int ns, int M, int N, int slices, GemmPlan *best) {
       const double tail_rounds = tail > room ? (double)((tail - room + GEMM_CUS - 1) / GEMM_CUS) : 0.0;
       const double us = 3.0 + (rounds + tail_rounds * part[ms]) * tile_us;
       if (n_mt * n_nt + tail <= 0x7fffffffLL && us < best->us)
-        *best = GemmPlan{ns, (int)n_mt, (int)n_nt, ms, (int)(n_mt * n_nt + tail), us};
+        *best = GemmPlan{ns, (int)n_mt, (int)n_nt, ms, (int)(n_mt * n_nt + tail), us, 0};
     }
   }
 }
@@ -100,7 +116,8 @@ inline void plan_tile(int kernel, int bm, int bn, double base, double latency, d
   if ((kernel & 1) && (n_mt * n_nt > GEMM_CUS || slices < 6)) return;   // K groups: one workgroup per CU
   const double load = n_mt * n_nt / (double)GEMM_CUS + 0.25;
   const double us = base + slices * std::max(latency, load * l2) + load * out;
-  if (n_mt * n_nt <= 0x7ffffff0LL && us < best->us) *best = GemmPlan{kernel, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), us};
+  if (n_mt * n_nt <= 0x7ffffff0LL && us < best->us)
+    *best = GemmPlan{kernel, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), us, tile_order(bm, bn, n_mt, n_nt)};
 }
 
 // gemm_heads (estimate fitted like those above, whole temporal modules in us, separate pass -> gemm_heads): 1260 tokens of 576
@@ -109,11 +126,12 @@ inline void plan_heads(int D, int M, int N, int slices, GemmPlan *best) {
   const int bn = D == 72 ? 144 : 96;
   const long long n_mt = (M + 63LL) / 64, n_nt = (N + bn - 1) / bn;
   if (n_mt * n_nt > GEMM_CUS) return;
-  *best = GemmPlan{bn, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), 5.5 + 0.3 * slices + n_mt * n_nt / (double)GEMM_CUS};
+  *best = GemmPlan{bn, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), 5.5 + 0.3 * slices + n_mt * n_nt / (double)GEMM_CUS,
+                   tile_order(64, bn, n_mt, n_nt)};
 }
 
 inline GemmPlan plan_gemm(int M, int N, int K) {
-  GemmPlan best{0, 0, 0, 0, 0, 1e30};
+  GemmPlan best{0, 0, 0, 0, 0, 1e30, 0};
   const int slices = (K + 63) / 64;
   plan_tile(64, 64, 64, 2.9, 0.26, 0.25, 0.55, M, N, slices, &best);
   plan_tile(65, 64, 64, 2.95, 0.185, 0.17, 0.55, M, N, slices, &best);
@@ -168,7 +186,7 @@ struct QkvPlan {
 
 inline QkvPlan plan_qkv(int n_tok, int H, int D, int S, int rope) {
   const int C = H * D, slices = (C + 63) / 64;
-  GemmPlan plain = plan_gemm(n_tok, 3 * C, C), fused{0, 0, 0, 0, 0, 1e30}, heads{0, 0, 0, 0, 0, 1e30};
+  GemmPlan plain = plan_gemm(n_tok, 3 * C, C), fused{0, 0, 0, 0, 0, 1e30, 0}, heads{0, 0, 0, 0, 0, 1e30, 0};
   if (D == 72 && C % 288 == 0 && (!rope || S >= 64)) plan_stream(9, n_tok, 3 * C, slices, &fused);
   fused.us += 3.0 * (fused.n_units / (double)GEMM_CUS + 0.5);
   plan_heads(D, n_tok, 3 * C, slices, &heads);

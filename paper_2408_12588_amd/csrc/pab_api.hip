@@ -329,12 +329,15 @@ int gemm_params(pab::GemmParams *p, int M, int N, int K, const void *A, const vo
   p->S = 1; p->rope = 0; p->eps = 0.0f;
   p->A2 = p->W2 = p->bias2 = nullptr; p->C2 = nullptr;
   p->M2 = p->N2 = p->n_nt2 = p->n_units2 = p->ms2 = 0;
+  p->n_inner2 = 1;
   return PAB_OK;
 }
 
 int gemm_planned(const GemmPlan &g, pab::GemmParams *p) {
   if (!g.kernel) return fail(PAB_EINVAL, "matrix too large");
-  p->n_mt = g.n_mt; p->n_nt = g.n_nt; p->ms_tail = g.ms_tail; p->n_units = g.n_units;
+  p->n_mt = g.n_mt; p->n_nt = g.n_nt; p->by_feature = g.by_feature;
+  p->n_inner = g.by_feature ? g.n_mt : g.n_nt;
+  p->ms_tail = g.ms_tail; p->n_units = g.n_units;
   return PAB_OK;
 }
 
@@ -368,6 +371,7 @@ int launch_gemm_pair(int M, int N, int K, const void *A, const void *W, const vo
   p.M2 = M2; p.N2 = N2; p.n_units2 = (int)pair.n_units2; p.n_nt2 = pair.n_nt2; p.ms2 = pair.ms2;
   GemmPlan g = pair.first;
   g.n_units += p.n_units2;
+  p.n_inner2 = g.by_feature ? p.n_units2 / p.n_nt2 : p.n_nt2;
   if ((rc = gemm_planned(g, &p)) != PAB_OK) return rc;
   launch_gemm_kernel<pab::GEMM_PLAIN>(g, p, st);
   const hipError_t e = hipGetLastError();

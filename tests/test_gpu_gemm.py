@@ -22,6 +22,7 @@ SHAPES = [
     (5000, 1152, 96),     # 64 x 128 tiles
     (700, 68, 96),        # 64 x 64 tiles: four features in the last, K = 1.5 slices
     (65, 64, 32),         # ... half a slice in all
+    (601, 3460, 352),     # 64 x 128 tiles, consecutive tiles along the tokens; 25 token rows and four features in the last tiles
 ]
 
 
@@ -39,6 +40,9 @@ K_GROUPS = [
     (1300, 1156, 480),    # 64 x 128, two groups: 7.5 slices
     (1300, 1152, 448),    # ... an odd number of them
     (2500, 1156, 1120),   # 128 x 128, two groups: 17.5 slices, ragged tiles
+    (250, 3460, 480),     # 64 x 64, three groups, consecutive tiles along the tokens; ragged tiles
+    (401, 4484, 480),     # 64 x 128, two groups, ...
+    (481, 4612, 864),     # 128 x 128, two groups, ...
 ]
 
 
@@ -165,6 +169,7 @@ CROSS_PAIRS = [
     (1, 1, 1, 4),           # ... one token, one text token
     (12, 500, 300, 12),     # ... more tiles than CUs
     (1, 900, 250, 16),      # ... the last of the K groups' 256 workgroups
+    (1, 200, 100, 28),      # ... consecutive tiles along the tokens, of both problems
     (17, 1024, 64, 16),     # ... tiles of the last round of gemm_stream, 256 features: one of 64 rows
     (17, 1024, 100, 16),    # ... two of 64 rows, the second moved back
     (17, 1024, 131, 16),    # ... two of 128 rows, the second moved back
@@ -179,7 +184,7 @@ CROSS_PAIRS = [
     (1, 1300, 250, 16),     # K groups, more tiles than CUs in all
 ]
 # of each: kernel of the query projection; rows / 64 of gemm_stream's tiles for the text; whether the text rides along
-CROSS_PAIR_PATHS = [(65, 0, True), (64, 0, True), (128, 0, True), (97, 0, True), (8, 1, True), (8, 1, True), (8, 2, True),
+CROSS_PAIR_PATHS = [(65, 0, True), (64, 0, True), (128, 0, True), (97, 0, True), (65, 0, True), (8, 1, True), (8, 1, True), (8, 2, True),
                     (9, 1, True), (9, 2, True), (8, 0, False), (8, 0, False), (8, 0, False), (8, 0, False), (8, 0, False), (97, 0, False)]
 
 

@@ -21,7 +21,7 @@ int main() {
       int M, N, K;
       if (scanf("%d %d %d", &M, &N, &K) != 3) return 1;
       const pab::GemmPlan g = pab::plan_gemm(M, N, K);
-      printf("%d %d %d %d %d\n", g.kernel, g.n_mt, g.n_nt, g.ms_tail, g.n_units);
+      printf("%d %d %d %d %d %d\n", g.kernel, g.n_mt, g.n_nt, g.ms_tail, g.n_units, g.by_feature);
     } else if (!strcmp(what, "pair")) {
       int M, N, M2, N2, K;
       if (scanf("%d %d %d %d %d", &M, &N, &M2, &N2, &K) != 5) return 1;
@@ -70,12 +70,15 @@ def items_of(shape):
 
 def test_projection_shapes_take_the_kernels_they_are_chosen_for(plan):
     got = plan("gemm", G.SHAPES)
-    assert [g[0] for g in got] == [8, 8, 8, 8, 9, 9, 128, 96, 64, 64]
+    assert [g[0] for g in got] == [8, 8, 8, 8, 9, 9, 128, 96, 64, 64, 96]
     tails = [g[3] for g in got[:6]]
     assert (tails[0], tails[1], tails[4], tails[5]) == (3, 1, 2, 1)
     assert [g[1] > 0 for g in got[:6]] == [False, True, True, False, False, True]    # full tiles beside the tail tiles
     assert all(g[4] > 256 for g in got[:1] + got[2:3] + got[5:6])                    # more than one tile per CU
-    assert [g[0] for g in plan("gemm", G.K_GROUPS)] == [65, 65, 65, 65, 97, 97, 129]
+    groups = plan("gemm", G.K_GROUPS)
+    assert [g[0] for g in groups] == [65, 65, 65, 65, 97, 97, 129, 65, 97, 129]
+    assert got[-1][5] == 1 and [g[5] for g in groups[-3:]] == [1, 1, 1]     # order of the tiles
+    assert plan("gemm", [(200, 2016, 2016)])[0][5] == 1                     # ... of a query + text projection
     assert [g[0] for g in plan("gemm", G.HALF_SLICES)] == [8, 9, 8, 65, 64]
 
 
@@ -124,3 +127,26 @@ def test_split_items_where_they_pay(plan):
     for (n, s, *rest), (n_item, bh_plain, n_split) in zip(shapes, plan("items", shapes)):
         assert 0 <= bh_plain <= n and n_item == -(-s // 256)
         assert -(-(n - bh_plain) // 8) * n_split <= 96, (n, s, rest)
+
+
+def rows_loaded(n_mt, n_nt, bm, bn, by_feature):
+    """Token and weight rows that the eight XCDs load for their contiguous runs of tiles."""
+    total = n_mt * n_nt
+    run = -(-total // 8)
+    rows = 0
+    for xcd in range(8):
+        ids = range(run * xcd, min(run * (xcd + 1), total))
+        tiles = [(i % n_mt, i // n_mt) if by_feature else (i // n_nt, i % n_nt) for i in ids]
+        rows += bm * len({m for m, n in tiles}) + bn * len({n for m, n in tiles})
+    return rows
+
+
+def test_order_of_small_tiles_loads_fewer_rows(plan):
+    """By feature (few tokens, many features) only where that halves the rows, or nearly so in the runs as they fall."""
+    by_feature = [(600, 3456, 1152), (640, 3456, 864), (512, 4608, 1152), (480, 4608, 864), (400, 4608, 1152), (400, 3456, 864), (548, 3968, 2624)]
+    by_token = [(2400, 864, 1152), (5000, 1152, 96), (1260, 2304, 576), (900, 2592, 864), (1260, 576, 576), (60, 4608, 1152), (4097, 1156, 160)]
+    for shape, (kernel, n_mt, n_nt, _, units, order) in zip(by_feature + by_token, plan("gemm", by_feature + by_token)):
+        assert kernel in (64, 65, 96, 97, 128, 129) and order == (shape in by_feature), shape
+        bm, bn = 128 if kernel >= 128 else 64, 128 if kernel >= 96 else 64
+        tokens, features = (rows_loaded(n_mt, n_nt, bm, bn, f) for f in (0, 1))
+        assert features <= 0.55 * tokens if order else features >= 0.45 * tokens, (shape, tokens, features)
