@@ -213,9 +213,13 @@ def pab_workspace_bytes(cfg: pab_config) -> int:
 def _stream(stream) -> int:
     if stream is None:
         # The current stream's handle without a Stream object around it: 0.3 us instead of 2.7, of 4.2 us that a reused
-        # call took in all.
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        # call took in all.  These two functions are not part of torch's public interface: a build without them takes the
+        # public way below.
+        try:
+            if torch.cuda.is_initialized():
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            pass
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream

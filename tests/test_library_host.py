@@ -301,3 +301,17 @@ def test_compute_argument_errors_without_device():
     assert f(5, pab.BF16, 2, 8, 4, 2, 72, 16, 16, 16, 16, None) == pab.EINVAL
     assert f(0, 3, 2, 8, 4, 2, 72, 16, 16, 16, 16, None) == pab.EINVAL
     assert f(0, pab.BF16, 0, 8, 4, 2, 72, 16, 16, 16, 16, None) == pab.EINVAL
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_stream_argument_without_torch_internals(monkeypatch, missing):
+    """A torch build that lacks the raw stream functions: calls go to the current stream all the same."""
+    import types
+    import torch
+    monkeypatch.delattr(torch._C, missing, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream" if missing == "_cuda_getDevice" else "_cuda_getDevice",
+                        lambda *a: 0, raising=False)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=1234))
+    assert pab._stream(None) == 1234
+    assert pab._stream(7) == 7
