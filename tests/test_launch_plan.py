@@ -31,7 +31,7 @@ int main() {
       int n, H, D, S, rope;
       if (scanf("%d %d %d %d %d", &n, &H, &D, &S, &rope) != 5) return 1;
       const pab::QkvPlan p = pab::plan_qkv(n, H, D, S, rope);
-      printf("%d %d %d %d\n", p.way, p.gemm.n_mt, p.gemm.ms_tail, p.gemm.n_units);
+      printf("%d %d %d %d %d\n", p.way, p.gemm.n_mt, p.gemm.ms_tail, p.gemm.n_units, p.gemm.by_feature);
     } else {
       long long n_bh; int sq, sk, D, size;
       if (scanf("%lld %d %d %d %d", &n_bh, &sq, &sk, &D, &size) != 5) return 1;
@@ -85,11 +85,12 @@ def test_projection_shapes_take_the_kernels_they_are_chosen_for(plan):
 def test_module_shapes_take_the_ways_they_are_chosen_for(plan):
     qkv = lambda shapes: plan("qkv", [(T * S, H, D, S, kind == 1) for kind, T, S, H, D in shapes])
     assert [q[0] for q in qkv([m + (72,) for m in G.MODULES])] == [1, 1, 1, 1, 0]
-    assert [q[0] for q in qkv(G.FEW_TOKENS)] == [2] * 6
+    few = qkv(G.FEW_TOKENS)
+    assert [q[0] for q in few] == [2] * 6 and {q[4] for q in few} == {0, 1}      # both orders of the tiles
     # moved tokens: in the epilogue of the large tiles, with tail tiles of which most reach back over rows of another
     moved = qkv([m + (72,) for m in G.MOVED])
-    assert all(way == 1 and ms < 4 for way, n_mt, ms, units in moved)
-    assert sum((T * S - 256 * n_mt) % (64 * ms) > 0 for (kind, T, S, H), (way, n_mt, ms, units) in zip(G.MOVED, moved)) >= 4
+    assert all(way == 1 and ms < 4 for way, n_mt, ms, *_ in moved)
+    assert sum((T * S - 256 * n_mt) % (64 * ms) > 0 for (kind, T, S, H), (way, n_mt, ms, *_) in zip(G.MOVED, moved)) >= 4
 
 
 def test_text_projection_rides_where_it_is_meant_to(plan):
