@@ -23,8 +23,8 @@
 //
 // Tiles: full ones of 256 tokens first; the remaining token rows are cut into
 // tiles of 64, 128, 192 or 256 rows, whichever evens out the last round best
-// (25440 x 1152: 400 tiles of 256 x 288 are 1.56 rounds of 256, with 48 x 4 tail
-// tiles of 192 rows 1 + 0.78).  The last tile of either axis is moved back to end
+// (25440 x 3456 x 1152: 1200 tiles of 256 x 288 are 4.7 rounds of 256 workgroups, that is 5;
+// 85 x 12 full ones and 20 x 12 tail tiles of 192 rows take 4 + 0.82).  The last tile of either axis is moved back to end
 // at the matrix edge: rows that two tiles compute are written twice with the same
 // bits, and nothing needs a bounds check.
 //

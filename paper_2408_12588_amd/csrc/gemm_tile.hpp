@@ -6,8 +6,8 @@
 // Such a problem is bound by the latency of its K loop, not by a rate: a slice
 // of a lone 64 x 64 tile takes 0.26 us, of a 128 x 128 tile 0.55 us, so the host
 // picks the smallest tile that the L2 traffic allows (about 60 GB/s per CU).
-// 1260 x 576 x 2304: 34.2 us with the former 128 x 256 tiles on 15 CUs, 12.6 us
-// with 180 tiles of 64 x 64; 1260 x 1728 x 576: 14.1 -> 8.7 us.
+// 1260 x 576 x 2304: 33.8 us with the former 128 x 256 tiles on 15 CUs, 13.9 us
+// with 180 tiles of 64 x 64, 10.1 with the K groups below; 1260 x 1728 x 576: 13.8 -> 9.0 us.
 //
 // The latency is that of barrier, operand reads and MFMAs, one behind the other,
 // with one wavefront per SIMD: more slices in flight did not help (4, 6, 9 stages:

@@ -132,8 +132,10 @@ __device__ __forceinline__ unsigned to_row_lanes(unsigned x) {
 
 // Stores 16 rows of O^T, normalised: lane (row, g4) of sub-tile dt holds elements 16 dt + 4 g4 .. + 3 of its row; row r
 // goes to base + r * pitch, rows from n_rows on do not exist.  bf16: neighbouring lanes of a row exchange sub-tiles
-// pairwise, so that each stores 16 bytes.  Spatial attention, against 8-byte stores in accumulator order: 102.8 -> 97.9 us
-// at 16 frames of 1024 tokens and 16 heads, 230 -> 226 at 1590, 1019 -> 1012 at 3600; 13.4 -> 12.4 at 4 x 300, 8 heads.
+// pairwise, so that each stores 16 bytes.  Spatial attention, against 8-byte stores in accumulator order, two builds in turn:
+// 97.8 -> 95.5 us at 16 frames of 1024 tokens and 16 heads, 225.3 -> 220.6 at 1590, within the noise at 3600 (1049 -> 1044).  Where
+// a launch is one short round the way through the crossbar shows instead: 8.9 -> 9.1 at 7 frames of 168 tokens and 10 heads.
+// All pieces under way before the first store: 1 % better there, 1 % worse in full launches.
 template <typename T, int D, int DT>
 __device__ __forceinline__ void store_rows16(T *base, long long pitch, int n_rows, const f32x4 (&acc)[DT], float inv) {
   const int lane = __lane_id(), row = lane >> 2, g = lane & 3;
