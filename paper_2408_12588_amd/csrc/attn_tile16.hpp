@@ -65,7 +65,7 @@ struct TileParams {
 
 constexpr int TILE_NRING = 8;   // LDS stages of the K/V ring
 
-template <typename T, int D, int NWV, int MINW, bool DIRECT>
+template <typename T, int D, int NWV, int MINW, bool DIRECT, bool ROWS>
 __global__ __launch_bounds__(64 * NWV, MINW) void attn_tile16_kernel(const TileParams p) {
   using HD = HeadDim<D>;
   constexpr int CH = HD::CH;
@@ -430,7 +430,15 @@ __global__ __launch_bounds__(64 * NWV, MINW) void attn_tile16_kernel(const TileP
       f32x4 tile[DT16];
 #pragma unroll
       for (int dt = 0; dt < DT16; ++dt) tile[dt] = oacc[dt][qh];
-      store_rows16<T, D>(ob + row0 * p.o_ss, p.o_ss, sq - row0, tile, inv);
+      if constexpr (ROWS) {
+        store_rows16<T, D>(ob + row0 * p.o_ss, p.o_ss, sq - row0, tile, inv);
+      } else if (row0 + l16 < sq) {
+        T *orow = ob + (row0 + l16) * p.o_ss;
+#pragma unroll
+        for (int dt = 0; dt < DT16; ++dt)
+          if (16 * dt + 4 * g4 < D)
+            Io<T>::store4(orow + 16 * dt + 4 * g4, tile[dt][0] * inv, tile[dt][1] * inv, tile[dt][2] * inv, tile[dt][3] * inv);
+      }
     }
   }
 }

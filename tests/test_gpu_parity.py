@@ -542,6 +542,25 @@ def test_split_items(pab, kind, T, S, L, H, D, dtype, peaked):
     assert_close(out, orc.kind_attention(kind, q, k, v), v, "split case")
 
 
+FEW_QUERIES = [
+    # kind, T, S, L, H: up to 48 queries of a problem are stored as accumulated, more in row order
+    (W.SPATIAL, 3, 48, 0, 5), (W.SPATIAL, 2, 49, 0, 3), (W.SPATIAL, 4, 33, 0, 2), (W.SPATIAL, 2, 1, 0, 3),
+    (W.TEMPORAL, 33, 9, 0, 3), (W.TEMPORAL, 48, 7, 0, 2), (W.TEMPORAL, 49, 7, 0, 2),
+    (W.CROSS, 2, 20, 530, 3),
+]
+
+
+@pytest.mark.parametrize("D,dtype", [(72, "bf16"), (32, "bf16"), (72, "f32"), (32, "f32")])
+@pytest.mark.parametrize("kind,T,S,L,H", FEW_QUERIES)
+def test_few_queries(pab, kind, T, S, L, H, D, dtype):
+    print("few queries", W.KIND_NAMES[kind], T, S, L, H, D, dtype, flush=True)
+    q, k, v = rand_qkv(kind, T, S, L, H, D, dtype, seed=3000 + T + S)
+    out = torch.full(q.shape, 7.0, device=DEV, dtype=q.dtype)
+    pab.pab_attention_compute(kind, q.to(DEV), k.to(DEV), v.to(DEV), out=out)
+    torch.cuda.synchronize()
+    assert_close(out, orc.kind_attention(kind, q, k, v), v, "few queries")
+
+
 def test_default_stream_argument_is_the_current_stream(pab):
     """Without a stream argument calls go to torch's current stream: default, side stream, nested."""
     s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
