@@ -58,7 +58,9 @@ inline ItemPlan plan_items(long long n_bh, int sq, int sk, int head_dim, int ele
 //      gemm_stream  3 + (rounds of 256 tiles) (slices t + e): t = 1.5, e = 6 at 256 features, t = 1.7, e = 8 at 288
 //                   (a tail tile of 64 / 128 / 192 token rows takes 0.50 / 0.66 / 0.82 of a full one)
 //      gemm_tile    base + slices max(latency, load l2) + load out, load = tiles / 256 + 0.25: a lone tile is bound by the
-//                   latency of its K loop, more tiles than CUs by L2 (about 60 GB/s per CU) and by their stores
+//                   latency of its K loop, more tiles than CUs by L2 (about 60 GB/s per CU) and by their stores; a CU
+//                   holds two tiles of 128 x 128, so that up to 512 of them take one round (16000 x 448 x 1824, 500 tiles: 31.8,
+//                   gemm_stream 40.2, the former kernel 33.8; 11000 x 768 x 1824, 516 tiles: 52.1, gemm_stream 39.5)
 //      Both sides of the line, measured in us: 2560 x 3456 x 1152 gemm_stream 24, 128 x 128 tiles 33; 6249 x 1152 x 4608
 //      83 and 66; 1350 x 3456 x 1152 128 x 128 tiles 19, 64 x 128 23; 1260 x 576 x 2304 64 x 64 tiles 12, 128 x 128 24.
 //      K groups (odd numbers) where every workgroup has a CU to itself and there are 6 slices or more: 64 x 64 tiles, three
@@ -114,7 +116,8 @@ inline void plan_tile(int kernel, int bm, int bn, double base, double latency, d
                GemmPlan *best) {
   const long long n_mt = ((long long)M + bm - 1) / bm, n_nt = (N + bn - 1) / bn;
   if ((kernel & 1) && (n_mt * n_nt > GEMM_CUS || slices < 6)) return;   // K groups: one workgroup per CU
-  const double load = n_mt * n_nt / (double)GEMM_CUS + 0.25;
+  double load = n_mt * n_nt / (double)GEMM_CUS + 0.25;
+  if (kernel == 128 && load > 1.5) load *= load <= 2.25 ? 0.8 : load <= 2.85 ? 1.1 : 1.0;   // one round of two per CU, a second begun
   const double us = base + slices * std::max(latency, load * l2) + load * out;
   if (n_mt * n_nt <= 0x7ffffff0LL && us < best->us)
     *best = GemmPlan{kernel, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), us, tile_order(bm, bn, n_mt, n_nt)};

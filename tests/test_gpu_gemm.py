@@ -19,7 +19,8 @@ SHAPES = [
     (30000, 288, 224),    # large tiles, 288 features: one feature tile, 128-row tail tiles, half slice
     (12001, 2596, 160),   # ... full and 64-row tail tiles, N = 9.01 tiles
     (4097, 1156, 160),    # 128 x 128 tiles: one token row and four features in the last tiles
-    (5000, 1152, 96),     # 64 x 128 tiles
+    (5000, 1152, 96),     # ... K = 1.5 slices
+    (1647, 1532, 224),    # 64 x 128 tiles, ragged; K = 3.5 slices
     (700, 68, 96),        # 64 x 64 tiles: four features in the last, K = 1.5 slices
     (65, 64, 32),         # ... half a slice in all
     (601, 3460, 352),     # 64 x 128 tiles, consecutive tiles along the tokens; 25 token rows and four features in the last tiles

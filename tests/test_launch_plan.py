@@ -70,7 +70,7 @@ def items_of(shape):
 
 def test_projection_shapes_take_the_kernels_they_are_chosen_for(plan):
     got = plan("gemm", G.SHAPES)
-    assert [g[0] for g in got] == [8, 8, 8, 8, 9, 9, 128, 96, 64, 64, 96]
+    assert [g[0] for g in got] == [8, 8, 8, 8, 9, 9, 128, 128, 96, 64, 64, 96]
     tails = [g[3] for g in got[:6]]
     assert (tails[0], tails[1], tails[4], tails[5]) == (3, 1, 2, 1)
     assert [g[1] > 0 for g in got[:6]] == [False, True, True, False, False, True]    # full tiles beside the tail tiles
@@ -130,6 +130,12 @@ def test_split_items_where_they_pay(plan):
         assert -(-(n - bh_plain) // 8) * n_split <= 96, (n, s, rest)
 
 
+def test_one_round_of_large_small_tiles(plan):
+    """Two 128 x 128 tiles share a CU: preferred up to 512 of them, not for the few more that begin a second round."""
+    shapes = [(16000, 448, 1824), (13838, 512, 1824), (16000, 448, 4608), (4000, 1728, 1152), (11000, 768, 1824)]
+    assert [(g[0], g[4] <= 512) for g in plan("gemm", shapes)] == [(128, True)] * 4 + [(8, True)]
+
+
 def rows_loaded(n_mt, n_nt, bm, bn, by_feature):
     """Token and weight rows that the eight XCDs load for their contiguous runs of tiles."""
     total = n_mt * n_nt
@@ -145,7 +151,7 @@ def rows_loaded(n_mt, n_nt, bm, bn, by_feature):
 def test_order_of_small_tiles_loads_fewer_rows(plan):
     """By feature (few tokens, many features) only where that halves the rows, or nearly so in the runs as they fall."""
     by_feature = [(600, 3456, 1152), (640, 3456, 864), (512, 4608, 1152), (480, 4608, 864), (400, 4608, 1152), (400, 3456, 864), (548, 3968, 2624)]
-    by_token = [(2400, 864, 1152), (5000, 1152, 96), (1260, 2304, 576), (900, 2592, 864), (1260, 576, 576), (60, 4608, 1152), (4097, 1156, 160)]
+    by_token = [(2400, 864, 1152), (1647, 1532, 224), (1260, 2304, 576), (900, 2592, 864), (1260, 576, 576), (60, 4608, 1152), (4097, 1156, 160)]
     for shape, (kernel, n_mt, n_nt, _, units, order) in zip(by_feature + by_token, plan("gemm", by_feature + by_token)):
         assert kernel in (64, 65, 96, 97, 128, 129) and order == (shape in by_feature), shape
         bm, bn = 128 if kernel >= 128 else 64, 128 if kernel >= 96 else 64
