@@ -53,6 +53,16 @@ inline ItemPlan plan_items(long long n_bh, int sq, int sk, int head_dim, int ele
   return p;
 }
 
+// Whether the tile kernel moves its results to row order on the way out (store_rows16) or stores them as accumulated.  With few
+// queries most of the eight wavefronts are idle and nothing covers the way through the LDS crossbar; it pays in larger launches,
+// the sooner where pieces of a row start on 64-byte boundaries.  As accumulated -> in row order, us: 34 frames at 200 positions,
+// 8 heads 19.5 -> 20.5, 50 at 185, 5 heads 12.6 -> 13.6, 72 at 185, 5 heads 16.4 -> 17.0, 100 frames of 96 tokens, 10 heads 20.5 -> 21.0;
+// but 80 at 1001, 5 heads 69.9 -> 66.8, 96 at 185, 8 heads 29.3 -> 27.3, 16 frames of 400 tokens, 16 heads 27.6 -> 25.6.
+inline bool store_in_row_order(long long n_bh, int sq, long long row_pitch_bytes) {
+  if (sq <= 48) return false;
+  return sq > 128 || n_bh > 2048 || (sq > 64 && row_pitch_bytes % 64 == 0);
+}
+
 // ---- which projection kernel and tile: the one with the smallest estimate, in us, fitted to shapes timed on the
 //      card (1358 of them, M 16 .. 45000, N and K 64 .. 4608: the picks take 1.006 of the best kernel's time; K slices of 64):
 //      gemm_stream  3 + (rounds of 256 tiles) (slices t + e): t = 1.5, e = 6 at 256 features, t = 1.7, e = 8 at 288

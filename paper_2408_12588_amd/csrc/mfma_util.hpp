@@ -133,10 +133,10 @@ __device__ __forceinline__ unsigned to_row_lanes(unsigned x) {
 // Stores 16 rows of O^T, normalised: lane (row, g4) of sub-tile dt holds elements 16 dt + 4 g4 .. + 3 of its row; row r
 // goes to base + r * pitch, rows from n_rows on do not exist.  bf16: neighbouring lanes of a row exchange sub-tiles
 // pairwise, so that each stores 16 bytes.  Spatial attention, against 8-byte stores in accumulator order, two builds in turn:
-// 97.8 -> 95.5 us at 16 frames of 1024 tokens and 16 heads, 225.3 -> 220.6 at 1590, within the noise at 3600 (1049 -> 1044).  Where
-// a launch is one short round the way through the crossbar shows instead, unless rows start on cache lines (8 or 16 heads of
-// 72): 8.9 -> 9.1 at 7 frames of 168 tokens and 10 heads, but 11.5 -> 10.8 at 8 of 200 and 16.
-// All pieces under way before the first store: 1 % better there, 1 % worse in full launches.
+// 97.8 -> 95.5 us at 16 frames of 1024 tokens and 16 heads, 225.3 -> 220.6 at 1590, within the noise at 3600 (1049 -> 1044).
+// Problems of few queries keep the other order (store_in_row_order in launch_plan.hpp).  Launches of one short round of more
+// pay 0.2 us, unless rows start on cache lines (8 or 16 heads of 72): 8.9 -> 9.1 at 7 frames of 168 tokens and 10 heads, but
+// 11.5 -> 10.8 at 8 of 200 and 16.  All pieces under way before the first store: 1 % better there, 1 % worse in full launches.
 template <typename T, int D, int DT>
 __device__ __forceinline__ void store_rows16(T *base, long long pitch, int n_rows, const f32x4 (&acc)[DT], float inv) {
   const int lane = __lane_id(), row = lane >> 2, g = lane & 3;

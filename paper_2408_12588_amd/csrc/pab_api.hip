@@ -70,10 +70,7 @@ int launch_tile(int n_batch, int n_head, int sq, int sk, long long q_bs, long lo
   if (grid > 0x7fffffffLL) return fail(PAB_EINVAL, "problem too large for one launch (%lld workgroups)", grid);
   p.plain_wgs = (int)plain_wgs;
   constexpr bool DIRECT = sizeof(T) == 2;   // bf16 rows go from global memory straight into LDS
-  // Few queries: two of the eight wavefronts work and store one or two dozen rows each, and the way into row order (see
-  // store_rows16) is longer than what it saves: 292 positions of 38 frames and 2 heads 10.4 us, stored as accumulated 10.0, 200 of
-  // 34 and 8 heads 20.5 and 19.5; at 56 frames even, at 64 up to 3 % the other way.
-  if (sq <= 48)
+  if (!pab::store_in_row_order(n_bh, sq, q_ss * (long long)sizeof(T)))
     hipLaunchKernelGGL((pab::attn_tile16_kernel<T, D, TILE_NWV, TILE_MINW, DIRECT, false>), dim3((unsigned)grid),
                        dim3(64 * TILE_NWV), 0, st, p);
   else

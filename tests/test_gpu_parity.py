@@ -543,10 +543,12 @@ def test_split_items(pab, kind, T, S, L, H, D, dtype, peaked):
 
 
 FEW_QUERIES = [
-    # kind, T, S, L, H: up to 48 queries of a problem are stored as accumulated, more in row order
+    # kind, T, S, L, H: up to 48 queries of a problem are stored as accumulated, in smaller launches also up to 64, and up to 128
+    # where rows (of 72-element heads) are off 64-byte boundaries; more in row order
     (W.SPATIAL, 3, 48, 0, 5), (W.SPATIAL, 2, 49, 0, 3), (W.SPATIAL, 4, 33, 0, 2), (W.SPATIAL, 2, 1, 0, 3),
     (W.TEMPORAL, 33, 9, 0, 3), (W.TEMPORAL, 48, 7, 0, 2), (W.TEMPORAL, 49, 7, 0, 2),
-    (W.CROSS, 2, 20, 530, 3),
+    (W.CROSS, 2, 20, 530, 3), (W.SPATIAL, 2, 64, 0, 4), (W.SPATIAL, 2, 65, 0, 4), (W.SPATIAL, 2, 65, 0, 5),
+    (W.SPATIAL, 1, 128, 0, 5), (W.SPATIAL, 1, 129, 0, 5), (W.TEMPORAL, 49, 700, 0, 3),
 ]
 
 

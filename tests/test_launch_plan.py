@@ -32,6 +32,10 @@ int main() {
       if (scanf("%d %d %d %d %d", &n, &H, &D, &S, &rope) != 5) return 1;
       const pab::QkvPlan p = pab::plan_qkv(n, H, D, S, rope);
       printf("%d %d %d %d %d\n", p.way, p.gemm.n_mt, p.gemm.ms_tail, p.gemm.n_units, p.gemm.by_feature);
+    } else if (!strcmp(what, "rows")) {
+      long long n_bh, pitch; int sq;
+      if (scanf("%lld %d %lld", &n_bh, &sq, &pitch) != 3) return 1;
+      printf("%d\n", pab::store_in_row_order(n_bh, sq, pitch));
     } else {
       long long n_bh; int sq, sk, D, size;
       if (scanf("%lld %d %d %d %d", &n_bh, &sq, &sk, &D, &size) != 5) return 1;
@@ -128,6 +132,15 @@ def test_split_items_where_they_pay(plan):
     for (n, s, *rest), (n_item, bh_plain, n_split) in zip(shapes, plan("items", shapes)):
         assert 0 <= bh_plain <= n and n_item == -(-s // 256)
         assert -(-(n - bh_plain) // 8) * n_split <= 96, (n, s, rest)
+
+
+def test_order_of_stores(plan):
+    accumulated = [(1600, 34, 230400), (925, 50, 133200), (925, 72, 133200), (1000, 96, 1440), (10 ** 6, 48, 2304)]
+    in_rows = [(5005, 80, 720720), (1480, 96, 213120), (256, 400, 2304), (2100, 49, 302400), (4, 129, 720)]
+    assert [r[0] for r in plan("rows", accumulated + in_rows)] == [0] * 5 + [1] * 5
+    for D, size in ((72, 2), (72, 4), (32, 2), (32, 4)):      # the GPU test has both, whatever head dim and type
+        calls = [(items_of((*s, D, ""))[:2], s[4] * (s[2] if s[0] == 1 else 1) * D * size) for s in P.FEW_QUERIES]
+        assert {r[0] for r in plan("rows", [(n, sq, pitch) for (n, sq), pitch in calls])} == {0, 1}
 
 
 def test_one_round_of_large_small_tiles(plan):
