@@ -53,6 +53,40 @@ inline ItemPlan plan_items(long long n_bh, int sq, int sk, int head_dim, int ele
   return p;
 }
 
+// Small launches take attn_short.hpp: 10 times its wavefronts plus its key groups, or 0 for the tile kernel.  A 32-query block there loads the keys for
+// itself, so its time goes with the number of blocks; the tile kernel's with the key tiles of a workgroup and the rounds of
+// workgroups, and the line between them lies at a number of blocks.  It lies higher where the tile kernel needs a second
+// workgroup per CU, higher for heads of 32 (half the bytes per block and the same arithmetic), lower for fp32 rows (twice the
+// bytes).  us, tile kernel -> short, heads of 72: 96 problems of 256 tokens (768 blocks) 11.4 -> 9.0, 40 of 700 (880)
+// 20.5 -> 15.8, 195 of 177 (1170) 10.8 -> 10.9, 256 of 150 (1280) 10.1 -> 10.7, 72 of 462 (1080) 17.2 -> 17.5; second workgroup:
+// 192 of 290 (1920) 20.6 -> 18.0, 132 of 622 (2640) 33.4 -> 37.9; heads of 32: 180 of 256 (1440) 7.9 -> 7.2; fp32: heads of 32
+// 143 of 129 (715) 7.3 -> 6.2, 195 of 182 (1170) 8.5 -> 9.4, heads of 72 60 of 217 (420) 13.3 -> 9.5, 64 of 260 (576) 15.5 -> 16.2.
+// Long sequences that are split there stay (4 of 3600, 452 blocks, 47.9 -> 56.8; 8 of 1590 19.4 -> 17.6).  Sequences of one or two
+// key tiles (clips of 33 .. 64 frames) leave most of a 256-query workgroup idle: at any number of problems 0.46 - 0.81 of the
+// time (25440 problems of 48: 346 -> 233).
+// Key groups: what a wavefront does one after the other is ntile / groups steps, the more groups the shorter, while the
+// chip is not full of wavefronts; blocks in pairs of wavefronts, or two blocks with two groups each, when it is (5 tiles, 480
+// blocks: 2 groups 6.7, 4 groups 6.6; 8 tiles, 768 blocks: 9.0, 9.5; 10 tiles, 1400 blocks: 16.3, two blocks 14.0).
+inline int plan_short(long long n_bh, int sq, int sk, int head_dim, int elem_size) {
+  const long long blk = (sq + 31) / 32, n_blocks = n_bh * blk;
+  const int ntile = (sk + 31) / 32;
+  const ItemPlan plain = plan_items(n_bh, sq, sk, head_dim, elem_size);
+  const long long per_xcd = (n_bh + 7) / 8 * plain.n_item;
+  bool take;
+  if (elem_size == 4) {
+    take = n_blocks <= (head_dim == 32 ? 800 : 450);
+  } else {
+    const long long most = per_xcd <= TILE_CUS ? (head_dim == 32 ? 1500 : 1000) : per_xcd <= 2 * TILE_CUS ? 2000 : 0;
+    take = n_blocks <= most || (ntile <= 2 && sq <= 64);
+  }
+  if (plain.n_split && ntile > 50) take = false;
+  if (!take) return 0;
+  if (ntile <= 2) return n_blocks <= 256 || ntile == 1 ? 22 : 42;
+  if (n_blocks <= 256 || (ntile >= 5 && n_blocks <= 600) || (head_dim == 32 && ntile >= 16)) return 44;
+  if (ntile == 4 || (ntile >= 5 && n_blocks > 1200) || ntile >= 16) return 42;
+  return 22;
+}
+
 // Whether the tile kernel moves its results to row order on the way out (store_rows16) or stores them as accumulated.  With few
 // queries most of the eight wavefronts are idle and nothing covers the way through the LDS crossbar; it pays in larger launches,
 // the sooner where pieces of a row start on 64-byte boundaries.  As accumulated -> in row order, us: 34 frames at 200 positions,

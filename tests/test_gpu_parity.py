@@ -563,6 +563,80 @@ def test_few_queries(pab, kind, T, S, L, H, D, dtype):
     assert_close(out, orc.kind_attention(kind, q, k, v), v, "few queries")
 
 
+SHORT_SHAPES = [
+    # kind, T, S, L, H, D, dtype: small launches, by 10 x wavefronts + key groups of a workgroup
+    (W.SPATIAL, 1, 1, 0, 1, 72, "bf16"),       # 22: a single key (the second group sees none)
+    (W.SPATIAL, 9, 33, 0, 1, 72, "bf16"),      # ... one key and one query past a tile; problems past a multiple of eight
+    (W.SPATIAL, 3, 32, 0, 5, 32, "bf16"),
+    (W.CROSS, 2, 100, 20, 3, 72, "f32"),       # ... one problem per head, many blocks
+    (W.SPATIAL, 5, 63, 0, 3, 72, "f32"),
+    (W.CROSS, 1, 70, 60, 3, 32, "f32"),
+    (W.SPATIAL, 11, 65, 0, 10, 72, "bf16"),    # ... three tiles, odd
+    (W.SPATIAL, 3, 72, 0, 3, 72, "bf16"),      # 44: fewer tiles than groups
+    (W.SPATIAL, 5, 252, 0, 8, 72, "bf16"),     # ... two tiles per group, the last ragged
+    (W.SPATIAL, 1, 513, 0, 2, 72, "bf16"),     # ... one group with a tile more, of one key
+    (W.SPATIAL, 2, 129, 0, 3, 72, "f32"),
+    (W.SPATIAL, 1, 300, 0, 3, 32, "f32"),
+    (W.SPATIAL, 3, 700, 0, 5, 32, "bf16"),
+    (W.CROSS, 1, 45, 530, 2, 72, "bf16"),
+    (W.TEMPORAL, 200, 2, 0, 3, 72, "bf16"),
+    (W.SPATIAL, 3, 128, 0, 34, 72, "bf16"),    # 42: two blocks, four whole tiles
+    (W.SPATIAL, 4, 97, 0, 20, 72, "bf16"),     # ... one query in the last block
+    (W.TEMPORAL, 33, 90, 0, 3, 72, "bf16"),    # ... the second block of a workgroup with one query
+    (W.TEMPORAL, 64, 77, 0, 2, 32, "bf16"),
+    (W.SPATIAL, 8, 60, 0, 20, 32, "f32"),
+    (W.SPATIAL, 3, 800, 0, 13, 72, "bf16"),    # ... more than 16 tiles
+]
+
+
+@pytest.mark.parametrize("peaked", [0.0, 0.05])
+@pytest.mark.parametrize("kind,T,S,L,H,D,dtype", SHORT_SHAPES)
+def test_short_launches(pab, kind, T, S, L, H, D, dtype, peaked):
+    print("short", W.KIND_NAMES[kind], T, S, L, H, D, dtype, peaked, flush=True)
+    q, k, v = rand_qkv(kind, T, S, L, H, D, dtype, seed=4000 + S + L, scale_rows=peaked)
+    out = torch.full(q.shape, 7.0, device=DEV, dtype=q.dtype)
+    pab.pab_attention_compute(kind, q.to(DEV), k.to(DEV), v.to(DEV), out=out)
+    torch.cuda.synchronize()
+    q, k, v = (t.to(torch.bfloat16).to(t.dtype) for t in (q, k, v))   # fp32 rows are rounded on load, see test_split_items
+    assert_close(out, orc.kind_attention(kind, q, k, v), v, "short launch")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_short_launch_keeps_infinite_keys_to_themselves(pab, dtype):
+    """A key whose score is -inf weighs nothing, in whichever column its infinity sits, and its neighbours are untouched."""
+    q, k, v = rand_qkv(W.SPATIAL, 1, 70, 0, 2, 72, dtype, seed=61)
+    q[..., [3, 40, 64, 71]] = -1.0
+    rest = [i for i in range(70) if i not in (0, 5, 31, 69)]
+    want = np.stack([orc.kind_attention(W.SPATIAL, q[:, i:i + 1].expand(1, len(rest), 2, 72).contiguous(), k[:, rest].contiguous(),
+                                        v[:, rest].contiguous())[:, 0] for i in range(70)], 1)
+    for key, column in ((0, 3), (5, 71), (31, 64), (69, 40)):
+        k[:, key, :, column] = float("inf")
+    out = pab.pab_attention_compute(W.SPATIAL, q.to(DEV), k.to(DEV), v.to(DEV))
+    torch.cuda.synchronize()
+    assert_close(out, want, v, "infinite keys")
+
+
+TILE_SHAPES = [
+    # kind, T, S, L, H, D, dtype: what the tile kernel keeps of the split items and of the stores as accumulated
+    (W.SPATIAL, 1, 1633, 0, 3, 72, "bf16"),    # all split: 52 key tiles, the last with one key; 33 queries in the last item
+    (W.SPATIAL, 9, 1024, 0, 8, 72, "bf16"),    # 72 problems: the last eight split
+    (W.SPATIAL, 1, 1650, 0, 3, 32, "f32"),
+    (W.TEMPORAL, 34, 150, 0, 3, 72, "f32"),    # stored as accumulated
+    (W.TEMPORAL, 34, 150, 0, 3, 32, "f32"),
+    (W.TEMPORAL, 70, 171, 0, 3, 72, "bf16"),
+]
+
+
+@pytest.mark.parametrize("kind,T,S,L,H,D,dtype", TILE_SHAPES)
+def test_tile_kernel_beside_the_short_one(pab, kind, T, S, L, H, D, dtype):
+    print("tile", W.KIND_NAMES[kind], T, S, L, H, D, dtype, flush=True)
+    q, k, v = rand_qkv(kind, T, S, L, H, D, dtype, seed=4500 + S)
+    out = torch.full(q.shape, 7.0, device=DEV, dtype=q.dtype)
+    pab.pab_attention_compute(kind, q.to(DEV), k.to(DEV), v.to(DEV), out=out)
+    torch.cuda.synchronize()
+    assert_close(out, orc.kind_attention(kind, q, k, v), v, "tile kernel")
+
+
 def test_default_stream_argument_is_the_current_stream(pab):
     """Without a stream argument calls go to torch's current stream: default, side stream, nested."""
     s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()

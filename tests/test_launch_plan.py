@@ -36,6 +36,10 @@ int main() {
       long long n_bh, pitch; int sq;
       if (scanf("%lld %d %lld", &n_bh, &sq, &pitch) != 3) return 1;
       printf("%d\n", pab::store_in_row_order(n_bh, sq, pitch));
+    } else if (!strcmp(what, "short")) {
+      long long n_bh; int sq, sk, D, size;
+      if (scanf("%lld %d %d %d %d", &n_bh, &sq, &sk, &D, &size) != 5) return 1;
+      printf("%d\n", pab::plan_short(n_bh, sq, sk, D, size));
     } else {
       long long n_bh; int sq, sk, D, size;
       if (scanf("%lld %d %d %d %d", &n_bh, &sq, &sk, &D, &size) != 5) return 1;
@@ -132,6 +136,23 @@ def test_split_items_where_they_pay(plan):
     for (n, s, *rest), (n_item, bh_plain, n_split) in zip(shapes, plan("items", shapes)):
         assert 0 <= bh_plain <= n and n_item == -(-s // 256)
         assert -(-(n - bh_plain) // 8) * n_split <= 96, (n, s, rest)
+
+
+def test_short_launches(plan):
+    """Each way of the short kernel at the shapes that are meant for it, and the tile kernel's own ways beside it."""
+    got = [r[0] for r in plan("short", [items_of(shape) for shape in P.SHORT_SHAPES])]
+    assert got == [22] * 7 + [44] * 8 + [42] * 6
+    calls = [items_of(shape) for shape in P.TILE_SHAPES]
+    assert [r[0] for r in plan("short", calls)] == [0] * len(calls)
+    split = [n_split > 0 for _, _, n_split in plan("items", calls)]
+    rows = plan("rows", [(n, sq, s[4] * (s[2] if s[0] == 1 else 1) * D * size) for s, (n, sq, _, D, size) in zip(P.TILE_SHAPES, calls)])
+    assert split[:3] == [True] * 3 and [r[0] for r in rows] == [1] * 3 + [0] * 3
+    # both sides of the line: problems, queries, keys, head dim, bytes per element
+    short = [(96, 256, 256, 72, 2), (40, 700, 700, 72, 2), (192, 290, 290, 72, 2), (180, 256, 256, 32, 2), (143, 129, 129, 32, 4),
+             (60, 217, 217, 72, 4), (25440, 48, 48, 72, 2)]
+    tile = [(195, 177, 177, 72, 2), (256, 150, 150, 72, 2), (132, 622, 622, 72, 2), (4, 3600, 3600, 72, 2), (195, 182, 182, 32, 4),
+            (64, 260, 260, 72, 4), (256, 1024, 1024, 72, 2), (256, 1590, 1590, 72, 2)]
+    assert all(r[0] for r in plan("short", short)) and not any(r[0] for r in plan("short", tile))
 
 
 def test_order_of_stores(plan):
