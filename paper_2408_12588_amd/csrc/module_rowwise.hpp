@@ -14,15 +14,26 @@
 //                        contiguous stretch of memory and a row fits in a
 //                        handful of registers.
 #pragma once
+#include <type_traits>
 #include "mfma_util.hpp"
 #include "rope_table.hpp"
 
 namespace pab {
 
+// Sum over the wavefront, in all lanes: four steps inside rows of 16 lanes by data-parallel moves, then the rows by register
+// swaps.  The LDS crossbar (__shfl_xor) takes six steps of about 100 clocks each.
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+  auto moved = [](float x, auto ctrl) {
+    return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), decltype(ctrl)::value, 0xF, 0xF, true));
+  };
+  v += moved(v, std::integral_constant<int, 0xB1>{});    // lane ^ 1
+  v += moved(v, std::integral_constant<int, 0x4E>{});    // lane ^ 2
+  v += moved(v, std::integral_constant<int, 0x141>{});   // mirrored in half a row: the other four lanes
+  v += moved(v, std::integral_constant<int, 0x140>{});   // mirrored in the row: the other eight
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 struct LnModParams {
@@ -34,7 +45,9 @@ struct LnModParams {
   float eps;
 };
 
-// NCH: 8-element chunks a lane holds (ceil(C / 512)).
+// NCH: 8-element chunks a lane holds (ceil(C / 512)).  Large: HBM (25440 x 1152 23 us, 5.1 TB/s).  Small: the chain of one
+// wavefront; with the modulation requested behind the two sums and those through the LDS crossbar 1260 x 576 took 4.0 us,
+// now 3.3 (a small clip's blocks 1722 -> 1699, module of 497 tokens and 1152 features 29.0 -> 28.3, large ones the same).
 template <int NCH>
 __global__ __launch_bounds__(256) void ln_modulate_kernel(const LnModParams p) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -42,19 +55,25 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const LnModParams p) {
   if (tok >= p.n_tok) return;
   const int C = p.C, nchunk = C >> 3;
   const bf16_t *xr = p.x + (long long)tok * C;
+  // everything is requested at the start: the modulation arrives behind the sums
+  bf16x8 x[NCH], sh[NCH], sc[NCH];
+#pragma unroll
+  for (int i = 0; i < NCH; ++i) x[i] = lane + 64 * i < nchunk ? *reinterpret_cast<const bf16x8 *>(xr + 8 * (lane + 64 * i)) : zero8();
+#pragma unroll
+  for (int i = 0; i < NCH; ++i)
+    if (lane + 64 * i < nchunk) {
+      sh[i] = *reinterpret_cast<const bf16x8 *>(p.shift + 8 * (lane + 64 * i));
+      sc[i] = *reinterpret_cast<const bf16x8 *>(p.scale + 8 * (lane + 64 * i));
+    }
   float v[NCH][8];
   float s = 0.0f;
 #pragma unroll
-  for (int i = 0; i < NCH; ++i) {
-    const int c = lane + 64 * i;
-    bf16x8 t = zero8();
-    if (c < nchunk) t = *reinterpret_cast<const bf16x8 *>(xr + 8 * c);
+  for (int i = 0; i < NCH; ++i)
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      v[i][e] = (float)t[e];
+      v[i][e] = (float)x[i][e];
       s += v[i][e];
     }
-  }
   const float mean = wave_sum(s) / (float)C;
   float ss = 0.0f;
 #pragma unroll
@@ -72,11 +91,9 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const LnModParams p) {
   for (int i = 0; i < NCH; ++i) {
     const int c = lane + 64 * i;
     if (c < nchunk) {
-      const bf16x8 sh = *reinterpret_cast<const bf16x8 *>(p.shift + 8 * c);
-      const bf16x8 sc = *reinterpret_cast<const bf16x8 *>(p.scale + 8 * c);
       bf16x8 o;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] = (bf16_t)((v[i][e] - mean) * rstd * (1.0f + (float)sc[e]) + (float)sh[e]);
+      for (int e = 0; e < 8; ++e) o[e] = (bf16_t)((v[i][e] - mean) * rstd * (1.0f + (float)sc[i][e]) + (float)sh[i][e]);
       *reinterpret_cast<bf16x8 *>(hr + 8 * c) = o;
     }
   }
@@ -109,6 +126,12 @@ __global__ __launch_bounds__(256) void qk_norm_rope_kernel(const QkNormParams p)
   const bool live = r_in_wave < RPW && row < n_rows;
   bf16_t *g0 = base + row * D + part * EPL;
 
+  bf16x8 gm[CPL], bt[CPL];                  // requested with the row, not behind its sums
+#pragma unroll
+  for (int i = 0; i < CPL; ++i) {
+    gm[i] = *reinterpret_cast<const bf16x8 *>(gamma + part * EPL + 8 * i);
+    bt[i] = *reinterpret_cast<const bf16x8 *>(beta + part * EPL + 8 * i);
+  }
   float v[EPL];
   float s = 0.0f;
 #pragma unroll
@@ -138,12 +161,9 @@ __global__ __launch_bounds__(256) void qk_norm_rope_kernel(const QkNormParams p)
   const float rstd = 1.0f / sqrtf(tot / (float)D + p.eps);
   if (!live) return;
 #pragma unroll
-  for (int i = 0; i < CPL; ++i) {
-    const bf16x8 gm = *reinterpret_cast<const bf16x8 *>(gamma + part * EPL + 8 * i);
-    const bf16x8 bt = *reinterpret_cast<const bf16x8 *>(beta + part * EPL + 8 * i);
+  for (int i = 0; i < CPL; ++i)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[8 * i + e] = (v[8 * i + e] - mean) * rstd * (float)gm[e] + (float)bt[e];
-  }
+    for (int e = 0; e < 8; ++e) v[8 * i + e] = (v[8 * i + e] - mean) * rstd * (float)gm[i][e] + (float)bt[i][e];
   if (p.rope) {
     const int pos = (int)(row / p.H / p.S);   // frame index of this row's token
 #pragma unroll
