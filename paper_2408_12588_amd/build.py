@@ -1,14 +1,16 @@
-"""Compile libpab.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Compile libpab.so (HIP, gfx950 only) in-tree with hipcc, and the CPython binding of its two hottest calls with g++."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpab.so")
 SOURCES = [os.path.join(CSRC, "pab_api.hip")]
+BINDING = os.path.join(HERE, "_binding.so")
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # packed fp32 VALU forms stay off for device code (the host pass does not know the
@@ -37,12 +39,37 @@ def build_lib(verbose: bool = False, extra_flags=()) -> str:
     if verbose and out.strip():
         print(out)
     os.replace(tmp, LIB)
+    build_binding(verbose)
     return LIB
 
 
+def build_binding(verbose: bool = False) -> str:
+    """The CPython binding (csrc/pab_binding.cpp), against the installed torch and the libpab.so beside it."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = BINDING + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I" + os.path.join(root, "include"),
+           "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"), "-I" + sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "pab_binding.cpp"), "-o", tmp, "-L" + HERE, "-l:" + os.path.basename(LIB),
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + "\n")
+        raise RuntimeError("%s failed building _binding.so" % cmd[0])
+    os.replace(tmp, BINDING)
+    return BINDING
+
+
 def ensure_built() -> str:
-    """Build the library only if none is there: callers load what is built."""
-    return LIB if os.path.exists(LIB) else build_lib()
+    """Build only what is not there: callers load what is built."""
+    if not os.path.exists(LIB):
+        return build_lib()
+    if not os.path.exists(BINDING):
+        build_binding()
+    return LIB
 
 
 def device_asm(path: str, extra_flags=()) -> str:

@@ -1,4 +1,4 @@
-"""Thin ctypes binding of libpab.so: argument marshalling only.
+"""Thin binding of libpab.so: argument marshalling only, by ctypes and, for the calls of a denoising loop, natively.
 
 Every function here has the name and meaning of the C entry point it calls
 (``include/pab.h``); tensors are torch CUDA tensors used purely as device
@@ -210,6 +210,14 @@ def pab_workspace_bytes(cfg: pab_config) -> int:
     return n
 
 
+try:
+    from . import _binding   # csrc/pab_binding.cpp
+except ImportError as e:
+    raise ImportError("_binding.so is not built (%s): run `python -m paper_2408_12588_amd.build` or "
+                      "__graft_entry__.build()" % e) from e
+_binding.bind(_check, getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None))
+
+
 def _stream(stream) -> int:
     if stream is None:
         # The current stream's handle without a Stream object around it: 0.3 us instead of 2.7, of 4.2 us that a reused
@@ -252,12 +260,16 @@ class PabContext:
         handle = ctypes.c_void_p()
         _check(lib.pab_create(ctypes.byref(cfg), workspace.data_ptr(), workspace.numel(), ctypes.byref(handle)))
         self._h = handle
+        self._address = handle.value
         self.shape = (cfg.T, cfg.S, cfg.heads, cfg.head_dim)
         self.dtype = _TORCH_DTYPE[cfg.dtype]
         self._numel = cfg.T * cfg.S * cfg.heads * cfg.head_dim
 
     def pab_attention(self, block: int, kind: int, step: int, q, k, v, stream=None):
         """-> (decision, device pointer of the slot)."""
+        done = _binding.attention(self._address, block, kind, step, q, k, v, stream)
+        if done is not NotImplemented:
+            return done
         out = ctypes.c_void_p()
         dec = _check(lib.pab_attention(self._h, block, kind, step, _ptr(q), _ptr(k), _ptr(v), _stream(stream),
                                        ctypes.byref(out)))
@@ -291,6 +303,7 @@ class PabContext:
 
     def pab_destroy(self):
         if self._h:
+            self._address = None
             _check(lib.pab_destroy(self._h))
             self._h = None
 
@@ -304,6 +317,8 @@ class PabContext:
 def pab_attention_compute(kind: int, q, k, v, out=None, L: int | None = None, stream=None):
     """One attention launch without schedule or cache.  q ``[T, S, H, D]``;
     k, v ``[T, S, H, D]`` (spatial, temporal) or ``[L, H, D]`` (cross)."""
+    if out is not None and _binding.attention_compute(kind, q, k, v, out, stream) is None:
+        return out
     T, S, H, D = q.shape
     dtype = BF16 if q.dtype == torch.bfloat16 else F32
     if q.dtype not in (torch.bfloat16, torch.float32) or k.dtype != q.dtype or v.dtype != q.dtype:

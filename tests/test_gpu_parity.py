@@ -637,6 +637,41 @@ def test_tile_kernel_beside_the_short_one(pab, kind, T, S, L, H, D, dtype):
     assert_close(out, orc.kind_attention(kind, q, k, v), v, "tile kernel")
 
 
+def test_native_binding_and_python_take_the_same_calls(pab):
+    """Plain dense tensors go through the native binding, everything else through the Python code: same results, same errors."""
+    q, k, v = (t.to(DEV) for t in rand_qkv(W.SPATIAL, 2, 40, 0, 3, 72, "bf16", seed=71))
+    out = torch.empty_like(q)
+    assert pab._binding.attention_compute(0, q, k, v, out, None) is None
+    want = pab.pab_attention_compute(0, q, k, v)                                  # no out: Python
+    side = torch.cuda.Stream()
+    other = pab.pab_attention_compute(0, q, k, v, out=torch.empty_like(q), stream=side)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want) and torch.equal(other, want)
+    bad = [(q.transpose(0, 1), k, v, out), (q, k[:1], v, out), (q, k.float(), v, out), (q.half(), k.half(), v.half(), out), (q[0], k, v, out),
+           (q, k, v, out.transpose(0, 1)), (q.cpu(), k, v, out)]
+    for args in bad:
+        assert pab._binding.attention_compute(0, *args, None) is NotImplemented
+        with pytest.raises(ValueError):
+            pab.pab_attention_compute(0, *args[:3], out=args[3])
+    with pytest.raises(ValueError):
+        pab.pab_attention_compute(2, q, k, v, out=out)                            # cross attention wants [L, H, D]
+    with pytest.raises(pab.PabError):
+        pab.pab_attention_compute(7, q, k, v, out=out)
+    cfg = pab.make_config(1, 2, 40, 1, 3, 72, pab.BF16, 4, (2, 0, 0), 0, 3)
+    ctx = pab.PabContext(cfg, DEV)
+    dec, slot = ctx.pab_attention(0, 0, 0, q, k, v)
+    assert (dec, slot) == (pab.COMPUTE, ctx.pab_slot_ptr(0, 0))
+    assert ctx.pab_attention(0, 0, 1, None, None, None) == (pab.REUSE, slot)
+    assert ctx.pab_attention(0, 0, 2, q.data_ptr(), k, v, stream=side) == (pab.COMPUTE, slot)
+    torch.cuda.synchronize()
+    assert torch.equal(ctx.slot_tensor(0, 0), want)
+    with pytest.raises(ValueError):
+        ctx.pab_attention(0, 0, 3, q.transpose(0, 1), k, v)
+    ctx.pab_destroy()
+    with pytest.raises(pab.PabError):
+        ctx.pab_attention(0, 0, 3, q, k, v)
+
+
 def test_default_stream_argument_is_the_current_stream(pab):
     """Without a stream argument calls go to torch's current stream: default, side stream, nested."""
     s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()

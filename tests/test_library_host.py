@@ -315,3 +315,38 @@ def test_stream_argument_without_torch_internals(monkeypatch, missing):
     monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=1234))
     assert pab._stream(None) == 1234
     assert pab._stream(7) == 7
+
+
+def test_native_binding_leaves_the_unusual_to_python():
+    """The native binding takes plain numbers and dense device tensors and hands back everything else; errors are the same."""
+    import torch
+    b = pab._binding
+    cfg = pab.config_of(W.TINY)
+    rc, h = _create(cfg, 0x10000000, pab.pab_workspace_bytes(cfg))
+    assert rc == pab.OK
+    for args in [(3, 0, 0), (0, 3, 0), (2, 0, 0), (0, 0, 10), (0, 0, -1)]:     # out of range: raised, not handed back
+        block, kind, step = args
+        with pytest.raises(pab.PabError) as e:
+            b.attention(h.value, block, kind, step, 16, 16, 16, 0)
+        assert e.value.status == pab.EINVAL
+    with pytest.raises(pab.PabError) as e:
+        b.attention(h.value, 0, 0, 3, None, None, None, 0)
+    assert e.value.status == pab.ESTATE and "needs the output of step 2" in str(e.value)
+    with pytest.raises(pab.PabError) as e:
+        b.attention(None, 0, 0, 0, 16, 16, 16, 0)                              # a destroyed context
+    assert e.value.status == pab.EINVAL
+
+    class Sub(torch.Tensor):
+        pass
+    t = torch.zeros(4, 64, 4, 32)
+    for odd in (t, t.as_subclass(Sub), torch.nn.Parameter(t), torch.zeros(4, 64, 4, 32, device="meta"), 1.0, "x", 2 ** 70):
+        assert b.attention(h.value, 0, 0, 0, odd, 16, 16, 0) is NotImplemented, odd
+        assert b.attention_compute(0, odd, odd, odd, odd, 0) is NotImplemented, odd
+    for odd in (1.0, True, None, 2 ** 70):
+        assert b.attention(h.value, odd, 0, 0, 16, 16, 16, 0) is NotImplemented, odd
+    assert b.attention(h.value, 0, 0, 0, 16, 16, 16, None) is NotImplemented   # no device tensor: which stream, Python decides
+    assert b.attention(h.value, 0, 0, 0, 16, 16, 16, object()) is NotImplemented
+    for wrong in ((), (1,) * 7, (1,) * 9):
+        with pytest.raises(TypeError):
+            b.attention(*wrong)
+    pab.lib.pab_destroy(h)
