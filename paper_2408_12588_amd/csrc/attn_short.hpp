@@ -8,11 +8,13 @@
 // its K and V tiles into LDS of its own (the next K while the softmax runs, the next V at the end of the step) and meets the
 // other key groups of its query tile at one barrier, behind which all of them take a share of the rows: partial sums with the
 // denominator and the maximum beside them, read, weighed, added and stored 16 bytes per lane in row order.
-// 10.3 -> 7.4 us there; 4 frames of 128 tokens and 8 heads 7.0 -> 4.6, 4 of 500 and 8 13.1 -> 10.1, 4 of 64 and 4 (heads of
-// 32, fp32) 4.3 -> 3.2, 48 frames at 1590 positions, 16 heads 346 -> 233.
+// 10.3 -> 7.2 us there; 4 frames of 128 tokens and 8 heads 7.0 -> 4.4, 4 of 500 and 8 13.1 -> 9.8, 4 of 64 and 4 (heads of
+// 32, fp32) 4.3 -> 3.0, 48 frames at 1590 positions, 16 heads 350 -> 166, cross attention of 1000 tokens and 8 heads to 300 keys
+// 16.3 -> 6.2.
 //
 // The price is that a K/V tile serves 32 queries instead of 256: with many query tiles the copies (about 200 cache lines per
-// tile and head, 64 bytes per clock and CU) take longer than the arithmetic.  plan_short in launch_plan.hpp has the line.
+// tile and head, 64 bytes per clock and CU) take longer than the arithmetic.  plan_short and
+// plan_short_cross in launch_plan.hpp have the lines.
 #pragma once
 #include "mfma_util.hpp"
 
@@ -22,8 +24,8 @@ struct ShortParams {
   const void *q, *k, *v;
   void *o;
   int sq, sk, n_head;
-  int n_bh;                      // (batch, head) problems
   int n_blk;                     // workgroups of a problem
+  int n_work;                    // ... of all (batch, head) problems
   unsigned blk_magic, head_magic;  // ceil(2^32 / n_blk), ceil(2^32 / n_head): quotients by a high product
   long long q_bs, kv_bs;         // batch strides of q / o and of k / v, elements
   int q_ss, kv_ss;               // sequence strides, elements
@@ -84,11 +86,12 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 2 : 4) void attn_short_ke
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, g4 = lane >> 4;
   const int qt = wave / G, kg = wave % G;
-  // every eighth workgroup runs on the same XCD: whole problems per XCD
-  const unsigned xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const unsigned pr = p.n_blk == 1 ? slot : __umulhi(slot, p.blk_magic), blk = slot - pr * p.n_blk;
-  const unsigned bh = 8 * pr + xcd;
-  if (bh >= (unsigned)p.n_bh) return;
+  // workgroup ids go round-robin over the 8 XCDs: each takes a contiguous eighth of the blocks, so that the blocks of a problem
+  // share an L2 copy of its keys and no XCD has more to do than another (against every eighth problem 0.94 of the time over 274
+  // shapes, 0.6 where problems are few and not a multiple of 8)
+  const unsigned per = gridDim.x >> 3, id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (id >= (unsigned)p.n_work) return;
+  const unsigned bh = p.n_blk == 1 ? id : __umulhi(id, p.blk_magic), blk = id - bh * p.n_blk;
   const unsigned batch = p.n_head == 1 ? bh : __umulhi(bh, p.head_magic), head = bh - batch * p.n_head;
   const T *qb = reinterpret_cast<const T *>(p.q) + batch * p.q_bs + head * D;
   const T *kb = reinterpret_cast<const T *>(p.k) + batch * p.kv_bs + head * D;

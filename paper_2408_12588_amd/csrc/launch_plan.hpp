@@ -53,38 +53,58 @@ inline ItemPlan plan_items(long long n_bh, int sq, int sk, int head_dim, int ele
   return p;
 }
 
-// Small launches take attn_short.hpp: 10 times its wavefronts plus its key groups, or 0 for the tile kernel.  A 32-query block there loads the keys for
-// itself, so its time goes with the number of blocks; the tile kernel's with the key tiles of a workgroup and the rounds of
-// workgroups, and the line between them lies at a number of blocks.  It lies higher where the tile kernel needs a second
-// workgroup per CU, higher for heads of 32 (half the bytes per block and the same arithmetic), lower for fp32 rows (twice the
-// bytes).  us, tile kernel -> short, heads of 72: 96 problems of 256 tokens (768 blocks) 11.4 -> 9.0, 40 of 700 (880)
-// 20.5 -> 15.8, 195 of 177 (1170) 10.8 -> 10.9, 256 of 150 (1280) 10.1 -> 10.7, 72 of 462 (1080) 17.2 -> 17.5; second workgroup:
-// 192 of 290 (1920) 20.6 -> 18.0, 132 of 622 (2640) 33.4 -> 37.9; heads of 32: 180 of 256 (1440) 7.9 -> 7.2; fp32: heads of 32
-// 143 of 129 (715) 7.3 -> 6.2, 195 of 182 (1170) 8.5 -> 9.4, heads of 72 60 of 217 (420) 13.3 -> 9.5, 64 of 260 (576) 15.5 -> 16.2.
-// Long sequences that are split there stay (4 of 3600, 452 blocks, 47.9 -> 56.8; 8 of 1590 19.4 -> 17.6).  Sequences of one or two
-// key tiles (clips of 33 .. 64 frames) leave most of a 256-query workgroup idle: at any number of problems 0.46 - 0.81 of the
-// time (25440 problems of 48: 346 -> 233).
-// Key groups: what a wavefront does one after the other is ntile / groups steps, the more groups the shorter, while the
-// chip is not full of wavefronts; blocks in pairs of wavefronts, or two blocks with two groups each, when it is (5 tiles, 480
-// blocks: 2 groups 6.7, 4 groups 6.6; 8 tiles, 768 blocks: 9.0, 9.5; 10 tiles, 1400 blocks: 16.3, two blocks 14.0).
+// Small launches take attn_short.hpp: 10 times its wavefronts plus its key groups, or 0 for another kernel.
+//
+// Key groups: what a wavefront does one after the other is ntile / groups steps, the more groups the shorter, while the chip is
+// not full of wavefronts; then blocks in pairs of wavefronts, two blocks with two groups each, four blocks without groups.  us,
+// heads of 72: 15 tiles, 360 blocks 22: 10.2, 44: 9.2; 8 tiles, 1040 blocks 22: 10.5, 42: 10.8, 44: 11.6; 9 blocks of a problem,
+// 1440 in all 22: 13.4, 42: 11.5; 256 problems of 225 tokens 22: 16.5, 42: 16.3, 41: 14.0.
+inline int short_groups(long long n_blocks, long long blk, int ntile, int head_dim) {
+  if (ntile <= 2) return n_blocks <= 256 || ntile == 1 ? 22 : 42;
+  if (n_blocks <= 256 || (ntile >= 5 && n_blocks <= 650) || (head_dim == 32 && ntile >= 16)) return 44;
+  if (n_blocks > 1450 && (blk % 4 == 0 || blk >= 32)) return 41;
+  if (ntile == 4 || ntile >= 16 || (n_blocks > 1200 && (blk % 2 == 0 || blk >= 9))) return 42;
+  return 22;
+}
+
+// A 32-query block there loads the keys for itself, so its time goes with the number of blocks; the tile kernel's with the key
+// tiles of a workgroup and the rounds of workgroups: the line between them lies at a number of blocks.  It lies higher where the
+// tile kernel needs a second workgroup per CU, higher for heads of 32 (half the bytes per block and the same arithmetic), lower for
+// fp32 rows (twice the bytes).  us, tile kernel -> short, heads of 72: 96 problems of 256 tokens (768 blocks) 11.4 -> 8.6, 40 of
+// 700 (880) 20.4 -> 15.3, 224 of 150 (1120) 9.9 -> 9.9, 256 of 225 (2048, one workgroup each) 15.0 -> 14.0, 72 of 462 (1080)
+// 17.2 -> 16.8, 36 of 1000 (1152) 27.5 -> 25.7, 36 of 1189 (1368) 33.2 -> 35.1; second workgroup: 400 of 150 (2000) 15.9 -> 13.6, 132 of 622 (2640) 34.0 -> 36.6; heads of 32: 180 of 256 (1440)
+// 8.0 -> 7.1, 12 of 2400 (900) 39.1 -> 23.9; fp32: heads of 32 143 of 129 (715) 7.3 -> 6.0, 195 of 182 (1170) 8.3 -> 9.1, heads of
+// 72 78 of 379 (936) 21.3 -> 18.8, 88 of 415 (1144) 25.2 -> 33.3.  Long sequences of heads of 72 that are split there stay (6 of
+// 3600, 678 blocks, 48.4 -> 55.9; 12 of 1590 28.1 -> 24.4).  Sequences of one or two key tiles (clips of 33 .. 64 frames) leave most
+// of a 256-query workgroup idle: at any number of problems 0.4 - 0.6 of the time (25440 problems of 48: 350 -> 166), fp32 rows
+// 0.8 (2532 blocks 11.4 -> 9.3).
 inline int plan_short(long long n_bh, int sq, int sk, int head_dim, int elem_size) {
   const long long blk = (sq + 31) / 32, n_blocks = n_bh * blk;
   const int ntile = (sk + 31) / 32;
   const ItemPlan plain = plan_items(n_bh, sq, sk, head_dim, elem_size);
   const long long per_xcd = (n_bh + 7) / 8 * plain.n_item;
+  const bool clip = ntile <= 2 && sq <= 64;
   bool take;
   if (elem_size == 4) {
-    take = n_blocks <= (head_dim == 32 ? 800 : 450);
+    take = n_blocks <= (clip ? 2600 : head_dim == 32 ? 900 : 850);
   } else {
-    const long long most = per_xcd <= TILE_CUS ? (head_dim == 32 ? 1500 : 1000) : per_xcd <= 2 * TILE_CUS ? 2000 : 0;
-    take = n_blocks <= most || (ntile <= 2 && sq <= 64);
+    const long long most = per_xcd > 2 * TILE_CUS ? 0 : per_xcd > TILE_CUS ? 2000 : head_dim == 32 || plain.n_item == 1 ? 2048 : ntile <= 24 ? 1320 : 1200;
+    take = n_blocks <= most || clip;
   }
-  if (plain.n_split && ntile > 50) take = false;
-  if (!take) return 0;
-  if (ntile <= 2) return n_blocks <= 256 || ntile == 1 ? 22 : 42;
-  if (n_blocks <= 256 || (ntile >= 5 && n_blocks <= 600) || (head_dim == 32 && ntile >= 16)) return 44;
-  if (ntile == 4 || (ntile >= 5 && n_blocks > 1200) || ntile >= 16) return 42;
-  return 22;
+  if (head_dim == 72 && plain.n_split && ntile > 50) take = false;
+  return take ? short_groups(n_blocks, blk, ntile, head_dim) : 0;
+}
+
+// Cross attention (bf16): the cross kernels stage all keys of a head per workgroup and give every wavefront whole query tiles,
+// of which few tokens have too few.  us, cross kernel -> short, heads of 72: 500 tokens, 8 heads and 200 keys 13.0 -> 5.1, 2000
+// tokens and 300 keys 16.7 -> 8.0, 3500 tokens, 12 heads (1320 blocks) 16.8 -> 13.5, 4000 tokens, 16 heads (2000) 17.6 -> 16.9, 6000
+// tokens, 12 heads (2256) 17.9 -> 20.7; up to 128 keys only the smallest: 700 tokens, 7 heads and 90 keys (154 blocks) 4.5 -> 4.2,
+// 1000 tokens, 16 heads (512) 4.7 -> 5.6, heads of 32 there 4.3 -> 3.8 with 120 keys; up to 64 keys none.
+inline int plan_short_cross(int n_tok, int L, int n_head, int head_dim) {
+  const long long blk = (n_tok + 31LL) / 32, n_blocks = n_head * blk;
+  const int ntile = (L + 31) / 32;
+  const long long most = ntile > 4 ? 2000 : ntile < 3 ? 0 : head_dim == 32 ? 512 : 256;
+  return n_blocks <= most ? short_groups(n_blocks, blk, ntile, head_dim) : 0;
 }
 
 // Whether the tile kernel moves its results to row order on the way out (store_rows16) or stores them as accumulated.  With few

@@ -586,7 +586,26 @@ SHORT_SHAPES = [
     (W.TEMPORAL, 64, 77, 0, 2, 32, "bf16"),
     (W.SPATIAL, 8, 60, 0, 20, 32, "f32"),
     (W.SPATIAL, 3, 800, 0, 13, 72, "bf16"),    # ... more than 16 tiles
+    (W.SPATIAL, 23, 100, 0, 16, 72, "bf16"),   # 41: no groups, four blocks
 ]
+
+SHORT_CROSS = [
+    # few tokens against the keys that the cross kernels would hold: plan, T, S, L, H, D
+    (44, 1, 45, 129, 2, 72), (44, 2, 333, 300, 7, 72), (44, 1, 100, 512, 3, 72), (44, 1, 70, 65, 3, 72), (44, 1, 1, 97, 1, 72),
+    (44, 2, 200, 128, 4, 32), (44, 1, 300, 500, 5, 32), (22, 3, 1000, 161, 8, 72), (42, 3, 1000, 128, 5, 32), (42, 2, 1550, 300, 13, 72),
+    (41, 2, 1550, 150, 16, 72), (41, 3, 1300, 330, 12, 32),
+]
+LONG_CROSS = [(3, 1371, L, 16, D) for L in (129, 224, 290, 512) for D in (72, 32)]   # ... and enough tokens for the cross kernel
+
+
+@pytest.mark.parametrize("T,S,L,H,D", [s[1:] for s in SHORT_CROSS] + LONG_CROSS)
+def test_cross_attention_of_few_and_of_many_tokens(pab, T, S, L, H, D):
+    print("cross", T, S, L, H, D, flush=True)
+    q, k, v = rand_qkv(W.CROSS, T, S, L, H, D, "bf16", seed=4700 + S + L)
+    out = torch.full(q.shape, 7.0, device=DEV, dtype=q.dtype)
+    pab.pab_attention_compute(W.CROSS, q.to(DEV), k.to(DEV), v.to(DEV), out=out)
+    torch.cuda.synchronize()
+    assert_close(out, orc.kind_attention(W.CROSS, q, k, v), v, "cross")
 
 
 @pytest.mark.parametrize("peaked", [0.0, 0.05])
@@ -620,9 +639,9 @@ TILE_SHAPES = [
     # kind, T, S, L, H, D, dtype: what the tile kernel keeps of the split items and of the stores as accumulated
     (W.SPATIAL, 1, 1633, 0, 3, 72, "bf16"),    # all split: 52 key tiles, the last with one key; 33 queries in the last item
     (W.SPATIAL, 9, 1024, 0, 8, 72, "bf16"),    # 72 problems: the last eight split
-    (W.SPATIAL, 1, 1650, 0, 3, 32, "f32"),
-    (W.TEMPORAL, 34, 150, 0, 3, 72, "f32"),    # stored as accumulated
-    (W.TEMPORAL, 34, 150, 0, 3, 32, "f32"),
+    (W.SPATIAL, 1, 1650, 0, 3, 72, "f32"),
+    (W.TEMPORAL, 34, 440, 0, 3, 72, "f32"),    # stored as accumulated
+    (W.TEMPORAL, 34, 440, 0, 3, 32, "f32"),
     (W.TEMPORAL, 70, 171, 0, 3, 72, "bf16"),
 ]
 

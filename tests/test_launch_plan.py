@@ -40,6 +40,10 @@ int main() {
       long long n_bh; int sq, sk, D, size;
       if (scanf("%lld %d %d %d %d", &n_bh, &sq, &sk, &D, &size) != 5) return 1;
       printf("%d\n", pab::plan_short(n_bh, sq, sk, D, size));
+    } else if (!strcmp(what, "cross")) {
+      int n, L, H, D;
+      if (scanf("%d %d %d %d", &n, &L, &H, &D) != 4) return 1;
+      printf("%d\n", pab::plan_short_cross(n, L, H, D));
     } else {
       long long n_bh; int sq, sk, D, size;
       if (scanf("%lld %d %d %d %d", &n_bh, &sq, &sk, &D, &size) != 5) return 1;
@@ -141,18 +145,27 @@ def test_split_items_where_they_pay(plan):
 def test_short_launches(plan):
     """Each way of the short kernel at the shapes that are meant for it, and the tile kernel's own ways beside it."""
     got = [r[0] for r in plan("short", [items_of(shape) for shape in P.SHORT_SHAPES])]
-    assert got == [22] * 7 + [44] * 8 + [42] * 6
+    assert got == [22] * 7 + [44] * 8 + [42] * 6 + [41]
     calls = [items_of(shape) for shape in P.TILE_SHAPES]
     assert [r[0] for r in plan("short", calls)] == [0] * len(calls)
     split = [n_split > 0 for _, _, n_split in plan("items", calls)]
     rows = plan("rows", [(n, sq, s[4] * (s[2] if s[0] == 1 else 1) * D * size) for s, (n, sq, _, D, size) in zip(P.TILE_SHAPES, calls)])
     assert split[:3] == [True] * 3 and [r[0] for r in rows] == [1] * 3 + [0] * 3
     # both sides of the line: problems, queries, keys, head dim, bytes per element
-    short = [(96, 256, 256, 72, 2), (40, 700, 700, 72, 2), (192, 290, 290, 72, 2), (180, 256, 256, 32, 2), (143, 129, 129, 32, 4),
-             (60, 217, 217, 72, 4), (25440, 48, 48, 72, 2)]
-    tile = [(195, 177, 177, 72, 2), (256, 150, 150, 72, 2), (132, 622, 622, 72, 2), (4, 3600, 3600, 72, 2), (195, 182, 182, 32, 4),
-            (64, 260, 260, 72, 4), (256, 1024, 1024, 72, 2), (256, 1590, 1590, 72, 2)]
+    short = [(96, 256, 256, 72, 2), (40, 700, 700, 72, 2), (192, 290, 290, 72, 2), (256, 225, 225, 72, 2), (72, 462, 462, 72, 2),
+             (400, 150, 150, 72, 2), (12, 1590, 1590, 72, 2), (180, 256, 256, 32, 2), (12, 2400, 2400, 32, 2), (143, 129, 129, 32, 4),
+             (60, 217, 217, 72, 4), (25440, 48, 48, 72, 2), (1266, 56, 56, 32, 4)]
+    tile = [(132, 622, 622, 72, 2), (6, 3600, 3600, 72, 2), (195, 182, 182, 32, 4), (88, 415, 415, 72, 4), (128, 500, 500, 72, 2),
+            (256, 400, 400, 72, 2), (256, 1024, 1024, 72, 2), (256, 1590, 1590, 72, 2)]
     assert all(r[0] for r in plan("short", short)) and not any(r[0] for r in plan("short", tile))
+
+
+def test_cross_attention_of_few_tokens(plan):
+    ask = lambda shapes: [r[0] for r in plan("cross", [(T * S, L, H, D) for T, S, L, H, D in shapes])]
+    assert ask([s[1:] for s in P.SHORT_CROSS]) == [s[0] for s in P.SHORT_CROSS]
+    assert ask(P.LONG_CROSS) == [0] * len(P.LONG_CROSS)
+    full = [(16, 1590, 120, 16, 72), (17, 1024, 300, 16, 72), (1, 1000, 120, 16, 72), (1, 100, 64, 2, 72), (1, 700, 120, 30, 32), (12, 500, 300, 12, 72)]
+    assert ask(full) == [0] * len(full)
 
 
 def test_order_of_stores(plan):
