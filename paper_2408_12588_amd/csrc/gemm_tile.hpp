@@ -18,6 +18,7 @@
 #pragma once
 #include <type_traits>
 #include "gemm_common.hpp"
+#include "rope_table.hpp"
 
 namespace pab {
 
@@ -28,7 +29,6 @@ __global__ __launch_bounds__(64 * WM * WN * KG, KG > 1 ? WM * WN * KG / 4 : 2) v
   constexpr int ROUNDS = ROWS / 8, MYR = ROUNDS / NW, TOKR = BM / 8 / NW;   // copy rounds: all, per wavefront, of token rows
   constexpr int SEG = NS >= 4 ? 64 : 32;                 // features stored at a time
   static_assert(ROUNDS % NW == 0 && (BM / 8) % NW == 0, "copy rounds must deal evenly to the wavefronts");
-  static_assert(EPI != GEMM_NORM, "tiles of whole heads only");
   static_assert(NS % 2 == 0 && (NS == 2 || NS % 4 == 0), "sub-tiles come in pairs");
   static_assert(NST >= 2 && NST <= 3 && (NST - 2) * MYR < 16, "vmcnt immediates");
   constexpr int PART = 1024 * MS * NS * NW;              // bytes of a group's sums
@@ -150,6 +150,64 @@ __global__ __launch_bounds__(64 * WM * WN * KG, KG > 1 ? WM * WN * KG / 4 : 2) v
       for (int a = 0; a < MS; ++a)
 #pragma unroll
         for (int b = 0; b < NS; ++b) acc[a][b] += *(lds_ptr_f4)(size_t)(part + PART * g + 1024 * (NS * a + b));
+  }
+
+  if constexpr (EPI == GEMM_NORM) {
+    // query / key / value projection, heads of 32: a pair of sub-tiles is one head of 16 tokens, 8 consecutive elements in each
+    // of the four lanes of a token
+    auto across = [](float x) {   // sum over those lanes (lane bits 4 and 5)
+      const auto u = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+      x = __uint_as_float(u[0]) + __uint_as_float(u[1]);
+      const auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+      return __uint_as_float(v[0]) + __uint_as_float(v[1]);
+    };
+    f32x2 turn[MS][4];
+    if (p.rope) {
+#pragma unroll
+      for (int a = 0; a < MS; ++a) {
+        const int m = m0 + 16 * (wm * MS + a) + l16;
+        int frame = (int)__umulhi((unsigned)m, p.S_magic);   // m / S or one less
+        frame += m - frame * p.S >= p.S;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) turn[a][e] = rope_factor<32>(frame, 4 * q16 + e);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < NS / 2; ++u) {
+      const int n = n0 + wn * 16 * NS + 32 * u, plane = (n >= p.n_split) + (n >= 2 * p.n_split);
+      if (plane > 1) continue;
+      const bf16x8 g8 = *reinterpret_cast<const bf16x8 *>((plane ? p.gk : p.gq) + 8 * q16);
+      const bf16x8 b8 = *reinterpret_cast<const bf16x8 *>((plane ? p.bk : p.bq) + 8 * q16);
+#pragma unroll
+      for (int a = 0; a < MS; ++a) {
+        float v[8], s = 0.0f, ss = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          v[e] = acc[a][2 * u + (e >> 2)][e & 3];
+          s += v[e];
+        }
+        const float mean = across(s) * (1.0f / 32);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          v[e] -= mean;
+          ss += v[e] * v[e];
+        }
+        const float rstd = 1.0f / sqrtf(across(ss) * (1.0f / 32) + p.eps);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = v[e] * rstd * (float)g8[e] + (float)b8[e];
+        if (p.rope) {
+#pragma unroll
+          for (int e = 0; e < 8; e += 2) {
+            const f32x2 f = turn[a][e / 2];
+            const float x = v[e], y = v[e + 1];
+            v[e] = x * f[0] - y * f[1];
+            v[e + 1] = x * f[1] + y * f[0];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[a][2 * u + (e >> 2)][e & 3] = v[e];
+      }
+    }
   }
 
   // ---- activation, stores: 16 tokens x SEG features at a time through 2 KB per wavefront (the ring is free) ----

@@ -189,15 +189,15 @@ inline void plan_tile(int kernel, int bm, int bn, double base, double latency, d
 
 // gemm_heads (estimate fitted like those above, whole temporal modules in us, separate pass -> gemm_heads): 1260 tokens of 576
 // 28.0 -> 23.8, 800 of 864 31.0 -> 27.2, 630 of 1152 35.3 -> 31.0; but 250 of 1152 26.2 -> 26.9, 60 of 864 22.0 -> 23.2.
-inline void plan_heads(int D, int M, int N, int slices, GemmPlan *best) {
-  const int bn = D == 72 ? 144 : 96;
+inline void plan_heads(int M, int N, int slices, GemmPlan *best) {
+  const int bn = 144;
   const long long n_mt = (M + 63LL) / 64, n_nt = (N + bn - 1) / bn;
   if (n_mt * n_nt > GEMM_CUS) return;
   *best = GemmPlan{bn, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), 5.5 + 0.3 * slices + n_mt * n_nt / (double)GEMM_CUS,
                    tile_order(64, bn, n_mt, n_nt)};
 }
 
-inline GemmPlan plan_gemm(int M, int N, int K) {
+inline GemmPlan plan_tiles(int M, int N, int K) {
   GemmPlan best{0, 0, 0, 0, 0, 1e30, 0};
   const int slices = (K + 63) / 64;
   plan_tile(64, 64, 64, 2.9, 0.26, 0.25, 0.55, M, N, slices, &best);
@@ -206,6 +206,12 @@ inline GemmPlan plan_gemm(int M, int N, int K) {
   plan_tile(97, 64, 128, 3.2, 0.285, 0.24, 1.1, M, N, slices, &best);
   plan_tile(128, 128, 128, 3.5, 0.55, 0.52, 2.2, M, N, slices, &best);
   plan_tile(129, 128, 128, 3.6, 0.48, 0.45, 1.6, M, N, slices, &best);
+  return best;
+}
+
+inline GemmPlan plan_gemm(int M, int N, int K) {
+  GemmPlan best = plan_tiles(M, N, K);
+  const int slices = (K + 63) / 64;
   plan_stream(8, M, N, slices, &best);
   plan_stream(9, M, N, slices, &best);
   return best;
@@ -244,8 +250,11 @@ inline PairPlan plan_pair(int M, int N, int M2, int N2, int K) {
 // q, k, v projections of a self-attention module with layernorm2 (+ rotation) of q and k, whichever is estimated fastest:
 //   the best plain projection and a pass over q and k (each read and written once at 4.8 TB/s, 3 us at least);
 //   heads of 72: in the epilogue of the large-tile projection (it costs a tile 3 us);
-//   few tokens, one tile of two (heads of 32: three) heads per CU: in the epilogue of gemm_heads.
-enum { QKV_PASS = 0, QKV_STREAM = 1, QKV_HEADS = 2 };
+//   in the epilogue of small tiles: heads of 72, few tokens, one tile of two heads per CU: gemm_heads; heads of 32, which are a
+//   pair of sub-tiles: gemm_tile (it costs a launch 0.8 us and a round of tiles as much; whole modules in us, pass -> epilogue:
+//   2880 tokens of 256 24.0 -> 18.4, 3696 of 256 31.4 -> 25.3, 29715 of 384 98.9 -> 90.8, 38288 of 512 428 -> 417; gemm_heads,
+//   three heads per tile, took 13.8 at 189 of 128 where this takes 12.7, 14.0 -> 12.9 at 282 of 128).
+enum { QKV_PASS = 0, QKV_STREAM = 1, QKV_SMALL = 2 };
 struct QkvPlan {
   int way;
   GemmPlan gemm;
@@ -253,12 +262,17 @@ struct QkvPlan {
 
 inline QkvPlan plan_qkv(int n_tok, int H, int D, int S, int rope) {
   const int C = H * D, slices = (C + 63) / 64;
-  GemmPlan plain = plan_gemm(n_tok, 3 * C, C), fused{0, 0, 0, 0, 0, 1e30, 0}, heads{0, 0, 0, 0, 0, 1e30, 0};
+  GemmPlan plain = plan_gemm(n_tok, 3 * C, C), fused{0, 0, 0, 0, 0, 1e30, 0}, small{0, 0, 0, 0, 0, 1e30, 0};
   if (D == 72 && C % 288 == 0 && (!rope || S >= 64)) plan_stream(9, n_tok, 3 * C, slices, &fused);
   fused.us += 3.0 * (fused.n_units / (double)GEMM_CUS + 0.5);
-  plan_heads(D, n_tok, 3 * C, slices, &heads);
+  if (D == 72) {
+    plan_heads(n_tok, 3 * C, slices, &small);
+  } else {
+    small = plan_tiles(n_tok, 3 * C, C);
+    small.us += 0.8 + 0.8 * small.n_units / (double)GEMM_CUS * (small.kernel >= 128 ? 1.0 : small.kernel >= 96 ? 0.5 : 0.25);
+  }
   plain.us += 3.0 + 8e-6 * n_tok * C / 4.8;
-  if (heads.kernel && heads.us < std::min(fused.us, plain.us)) return {QKV_HEADS, heads};
+  if (small.kernel && small.us < std::min(fused.us, plain.us)) return {QKV_SMALL, small};
   if (fused.kernel && fused.us < plain.us) return {QKV_STREAM, fused};
   return {QKV_PASS, plain};
 }

@@ -336,15 +336,17 @@ size_t module_plane_bytes(int T, int S, int L, int H, int D) {
 template <int EPI>
 void launch_gemm_kernel(const GemmPlan &g, const pab::GemmParams &p, hipStream_t st) {
   const dim3 persistent((unsigned)std::min(g.n_units, GEMM_CUS)), tiles((unsigned)((g.n_units + 7) / 8 * 8));
+  if constexpr (EPI != pab::GEMM_NORM) {
+    if (g.kernel == 8) hipLaunchKernelGGL((pab::gemm_stream_kernel<8, 4, EPI>), persistent, dim3(512), 0, st, p);
+    if (g.kernel == 9) hipLaunchKernelGGL((pab::gemm_stream_kernel<9, 3, EPI>), persistent, dim3(512), 0, st, p);
+  }
   switch (g.kernel) {
-    case 8: hipLaunchKernelGGL((pab::gemm_stream_kernel<8, 4, EPI>), persistent, dim3(512), 0, st, p); break;
-    case 9: hipLaunchKernelGGL((pab::gemm_stream_kernel<9, 3, EPI>), persistent, dim3(512), 0, st, p); break;
     case 64: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 2, 2, 3, 1, EPI>), tiles, dim3(256), 0, st, p); break;
     case 65: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 2, 2, 3, 3, EPI>), tiles, dim3(768), 0, st, p); break;
     case 96: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 4, 2, 2, 3, 1, EPI>), tiles, dim3(512), 0, st, p); break;
     case 97: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 4, 2, 2, 3, 2, EPI>), tiles, dim3(1024), 0, st, p); break;
     case 128: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 4, 4, 2, 1, EPI>), tiles, dim3(256), 0, st, p); break;
-    default: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 4, 4, 2, 2, EPI>), tiles, dim3(512), 0, st, p); break;
+    case 129: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 4, 4, 2, 2, EPI>), tiles, dim3(512), 0, st, p); break;
   }
 }
 
@@ -367,7 +369,7 @@ int gemm_params(pab::GemmParams *p, int M, int N, int K, const void *A, const vo
   p->M = M; p->N = N; p->K = K; p->ldc = ldc;
   p->n_split = n_split; p->plane_stride = plane_stride;
   p->gq = p->bq = p->gk = p->bk = nullptr;
-  p->S = 1; p->rope = 0; p->eps = 0.0f;
+  p->S = 1; p->S_magic = ~0u; p->rope = 0; p->eps = 0.0f;
   p->A2 = p->W2 = p->bias2 = nullptr; p->C2 = nullptr;
   p->M2 = p->N2 = p->n_nt2 = p->n_units2 = p->ms2 = 0;
   p->n_inner2 = 1;
@@ -466,10 +468,11 @@ int launch_qkv(int n_tok, int H, int D, int S, int rope, const void *h, const pa
   p.gq = static_cast<const pab::bf16_t *>(w->gamma_q); p.bq = static_cast<const pab::bf16_t *>(w->beta_q);
   p.gk = static_cast<const pab::bf16_t *>(w->gamma_k); p.bk = static_cast<const pab::bf16_t *>(w->beta_k);
   p.S = S; p.rope = rope; p.eps = 1e-6f;
-  if (plan.way == pab::QKV_HEADS) {
-    const dim3 tiles((unsigned)((p.n_units + 7) / 8 * 8)), block(768);
-    if (D == 72) hipLaunchKernelGGL((pab::gemm_heads_kernel<2, 3, 2, 3, 3, 2, 72>), tiles, block, 0, st, p);
-    else hipLaunchKernelGGL((pab::gemm_heads_kernel<2, 3, 2, 2, 3, 2, 32>), tiles, block, 0, st, p);
+  p.S_magic = S == 1 ? ~0u : (unsigned)((1ULL << 32) / S);
+  if (plan.way == pab::QKV_SMALL) {
+    if (D == 72)
+      hipLaunchKernelGGL((pab::gemm_heads_kernel<2, 3, 2, 3, 3, 2, 72>), dim3((unsigned)((p.n_units + 7) / 8 * 8)), dim3(768), 0, st, p);
+    else launch_gemm_kernel<pab::GEMM_NORM>(plan.gemm, p, st);
     return PAB_OK;
   }
   if (plan.way == pab::QKV_STREAM) {

@@ -218,6 +218,24 @@ FEW_TOKENS = [
 ]
 
 
+HEADS_OF_32 = [
+    # kernel, kind, T, S, heads: sizes at which gemm_tile normalises (and rotates) q and k, by its tile and K groups
+    (64, 1, 7, 5, 3),        # planes that begin inside a tile, half a slice, frames shorter than a sub-tile
+    (64, 1, 70, 1, 5),       # one token per frame, frame indices beyond 63
+    (64, 0, 1, 700, 8),
+    (65, 1, 11, 30, 16),
+    (96, 1, 2, 679, 16),
+    (97, 1, 20, 37, 16),
+    (128, 1, 16, 351, 12),
+    (129, 0, 3, 667, 16),
+]
+
+
+@pytest.mark.parametrize("kind,T,S,heads,D", [s[1:] + (32,) for s in HEADS_OF_32])
+def test_norm_and_rotation_of_heads_of_32(kind, T, S, heads, D):
+    test_norm_and_rotation_few_tokens(kind, T, S, heads, D)
+
+
 @pytest.mark.parametrize("kind,T,S,heads,D", FEW_TOKENS)
 def test_norm_and_rotation_few_tokens(kind, T, S, heads, D):
     """Whole outputs against the oracle, 1e-2 of the largest output as for the modules elsewhere."""

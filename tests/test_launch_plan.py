@@ -31,7 +31,7 @@ int main() {
       int n, H, D, S, rope;
       if (scanf("%d %d %d %d %d", &n, &H, &D, &S, &rope) != 5) return 1;
       const pab::QkvPlan p = pab::plan_qkv(n, H, D, S, rope);
-      printf("%d %d %d %d %d\n", p.way, p.gemm.n_mt, p.gemm.ms_tail, p.gemm.n_units, p.gemm.by_feature);
+      printf("%d %d %d %d %d %d\n", p.way, p.gemm.n_mt, p.gemm.ms_tail, p.gemm.n_units, p.gemm.by_feature, p.gemm.kernel);
     } else if (!strcmp(what, "rows")) {
       long long n_bh, pitch; int sq;
       if (scanf("%lld %d %lld", &n_bh, &sq, &pitch) != 3) return 1;
@@ -103,6 +103,11 @@ def test_module_shapes_take_the_ways_they_are_chosen_for(plan):
     moved = qkv([m + (72,) for m in G.MOVED])
     assert all(way == 1 and ms < 4 for way, n_mt, ms, *_ in moved)
     assert sum((T * S - 256 * n_mt) % (64 * ms) > 0 for (kind, T, S, H), (way, n_mt, ms, *_) in zip(G.MOVED, moved)) >= 4
+
+
+def test_heads_of_32_are_normalised_in_the_tiles_meant_for_them(plan):
+    got = plan("qkv", [(T * S, H, 32, S, kind == 1) for _, kind, T, S, H in G.HEADS_OF_32])
+    assert [(g[0], g[5]) for g in got] == [(2, shape[0]) for shape in G.HEADS_OF_32]
 
 
 def test_text_projection_rides_where_it_is_meant_to(plan):
