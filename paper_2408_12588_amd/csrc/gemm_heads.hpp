@@ -5,7 +5,9 @@
 // The groups' sums meet in LDS as one fp32 tile.  A head's elements lie across several wavefronts; its statistics are taken
 // by four lanes per (token, head), and what leaves is 16 bytes per lane with consecutive lanes on consecutive chunks of a
 // row.  The separate pass over q and k that this replaces is a launch of 4 - 5 us: temporal module of 1260 tokens and 576
-// features 28.0 -> 23.8 us, a small clip's blocks 1996 -> 1845.
+// features 28.0 -> 23.8 us, a small clip's blocks 1996 -> 1845.  Tiles of 128 tokens (two LDS stages per group instead of three)
+// take what has more 64-token tiles than CUs: spatial module of 2400 tokens and 576 features 40.7 -> 35.8, 1280 of 1152
+// 53.8 -> 47.5, 4000 of 288 31.2 -> 27.2.
 #pragma once
 #include "gemm_common.hpp"
 #include "rope_table.hpp"
@@ -21,7 +23,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, WM * WN * KG / 4) void gemm_head
   constexpr int HPT = BN / HD, STATS = 4 * BM * CP;      // heads of a tile; byte offset of the statistics behind the tile
   constexpr int CPT = BN / 8, THREADS = 64 * NW * KG;    // 16-byte chunks of a tile row
   static_assert(BM % 8 == 0 && BN % HD == 0 && HD % 8 == 0, "tiles of whole heads");
-  static_assert(NST == 3 && MYR < 16, "vmcnt immediates");
+  static_assert((NST == 2 || NST == 3) && MYR < 16, "vmcnt immediates");
   static_assert(STATS + 8 * BM * HPT <= KG * NST * STAGE, "the epilogue must fit the rings");
   static_assert(4 * BM * HPT % 64 == 0, "whole wavefronts take the statistics");
 
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, WM * WN * KG / 4) void gemm_head
   int stage = 0, next = npre % NST;
   for (int s = 0; s < n_step; ++s) {
     // slice s of the group has landed (this wavefront's share); one more may be in flight
-    if (s + 1 < n_mine) __builtin_amdgcn_s_waitcnt(0x0F70 | MYR);
+    if (NST == 3 && s + 1 < n_mine) __builtin_amdgcn_s_waitcnt(0x0F70 | MYR);
     else __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();                        // ... everyone's share; all are done with slice s - 1
     if (s + NST - 1 < n_mine) {

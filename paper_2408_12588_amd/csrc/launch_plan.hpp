@@ -188,13 +188,15 @@ inline void plan_tile(int kernel, int bm, int bn, double base, double latency, d
 }
 
 // gemm_heads (estimate fitted like those above, whole temporal modules in us, separate pass -> gemm_heads): 1260 tokens of 576
-// 28.0 -> 23.8, 800 of 864 31.0 -> 27.2, 630 of 1152 35.3 -> 31.0; but 250 of 1152 26.2 -> 26.9, 60 of 864 22.0 -> 23.2.
-inline void plan_heads(int M, int N, int slices, GemmPlan *best) {
-  const int bn = 144;
-  const long long n_mt = (M + 63LL) / 64, n_nt = (N + bn - 1) / bn;
-  if (n_mt * n_nt > GEMM_CUS) return;
-  *best = GemmPlan{bn, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), 5.5 + 0.3 * slices + n_mt * n_nt / (double)GEMM_CUS,
-                   tile_order(64, bn, n_mt, n_nt)};
+// 28.0 -> 23.8, 800 of 864 31.0 -> 27.2, 630 of 1152 35.3 -> 31.0; but 250 of 1152 26.2 -> 26.9, 60 of 864 22.0 -> 23.2.  145, tiles
+// of 128 tokens: 1432 of 576 29.0 -> 27.2, 1760 of 864 41.4 -> 36.9, 1005 of 1152 39.9 -> 38.9, 4200 of 288 30.4 -> 28.0; past one
+// tile per CU it does not go (2000 of 864, 288 tiles, 42.4 with the separate pass).
+inline void plan_heads(int kernel, double base, double slice, double out, int M, int N, int slices, GemmPlan *best) {
+  const int bm = kernel == 145 ? 128 : 64, bn = 144;
+  const long long n_mt = ((long long)M + bm - 1) / bm, n_nt = (N + bn - 1) / bn;
+  const double us = base + slice * slices + out * n_mt * n_nt / (double)GEMM_CUS;
+  if (n_mt * n_nt <= GEMM_CUS && us < best->us)
+    *best = GemmPlan{kernel, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), us, tile_order(bm, bn, n_mt, n_nt)};
 }
 
 inline GemmPlan plan_tiles(int M, int N, int K) {
@@ -250,7 +252,7 @@ inline PairPlan plan_pair(int M, int N, int M2, int N2, int K) {
 // q, k, v projections of a self-attention module with layernorm2 (+ rotation) of q and k, whichever is estimated fastest:
 //   the best plain projection and a pass over q and k (each read and written once at 4.8 TB/s, 3 us at least);
 //   heads of 72: in the epilogue of the large-tile projection (it costs a tile 3 us);
-//   in the epilogue of small tiles: heads of 72, few tokens, one tile of two heads per CU: gemm_heads; heads of 32, which are a
+//   in the epilogue of small tiles: heads of 72, few tokens, one tile of two heads and 64 or 128 tokens per CU: gemm_heads; heads of 32, which are a
 //   pair of sub-tiles: gemm_tile (it costs a launch 0.8 us and a round of tiles as much; whole modules in us, pass -> epilogue:
 //   2880 tokens of 256 24.0 -> 18.4, 3696 of 256 31.4 -> 25.3, 29715 of 384 98.9 -> 90.8, 38288 of 512 428 -> 417; gemm_heads,
 //   three heads per tile, took 13.8 at 189 of 128 where this takes 12.7, 14.0 -> 12.9 at 282 of 128).
@@ -266,7 +268,8 @@ inline QkvPlan plan_qkv(int n_tok, int H, int D, int S, int rope) {
   if (D == 72 && C % 288 == 0 && (!rope || S >= 64)) plan_stream(9, n_tok, 3 * C, slices, &fused);
   fused.us += 3.0 * (fused.n_units / (double)GEMM_CUS + 0.5);
   if (D == 72) {
-    plan_heads(n_tok, 3 * C, slices, &small);
+    plan_heads(144, 5.5, 0.3, 1.0, n_tok, 3 * C, slices, &small);
+    plan_heads(145, 7.0, 0.5, 1.5, n_tok, 3 * C, slices, &small);
   } else {
     small = plan_tiles(n_tok, 3 * C, C);
     small.us += 0.8 + 0.8 * small.n_units / (double)GEMM_CUS * (small.kernel >= 128 ? 1.0 : small.kernel >= 96 ? 0.5 : 0.25);

@@ -470,8 +470,9 @@ int launch_qkv(int n_tok, int H, int D, int S, int rope, const void *h, const pa
   p.S = S; p.rope = rope; p.eps = 1e-6f;
   p.S_magic = S == 1 ? ~0u : (unsigned)((1ULL << 32) / S);
   if (plan.way == pab::QKV_SMALL) {
-    if (D == 72)
-      hipLaunchKernelGGL((pab::gemm_heads_kernel<2, 3, 2, 3, 3, 2, 72>), dim3((unsigned)((p.n_units + 7) / 8 * 8)), dim3(768), 0, st, p);
+    const dim3 tiles((unsigned)((p.n_units + 7) / 8 * 8)), block(768);
+    if (plan.gemm.kernel == 144) hipLaunchKernelGGL((pab::gemm_heads_kernel<2, 3, 2, 3, 3, 2, 72>), tiles, block, 0, st, p);
+    else if (plan.gemm.kernel == 145) hipLaunchKernelGGL((pab::gemm_heads_kernel<2, 3, 4, 3, 2, 2, 72>), tiles, block, 0, st, p);
     else launch_gemm_kernel<pab::GEMM_NORM>(plan.gemm, p, st);
     return PAB_OK;
   }

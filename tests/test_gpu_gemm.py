@@ -231,6 +231,20 @@ HEADS_OF_32 = [
 ]
 
 
+HEADS_128 = [
+    # kind, T, S, heads (of 72): gemm_heads with tiles of 128 tokens
+    (0, 1, 1025, 16),        # one token in the last tile
+    (1, 70, 45, 4),          # several frames per tile, frame indices beyond 63; 4.5 slices
+    (1, 13, 117, 12),        # 13.5 slices: the half slice with the second group
+    (1, 4, 358, 8),
+]
+
+
+@pytest.mark.parametrize("kind,T,S,heads", HEADS_128)
+def test_norm_and_rotation_of_128_token_tiles(kind, T, S, heads):
+    test_norm_and_rotation_few_tokens(kind, T, S, heads, 72)
+
+
 @pytest.mark.parametrize("kind,T,S,heads,D", [s[1:] + (32,) for s in HEADS_OF_32])
 def test_norm_and_rotation_of_heads_of_32(kind, T, S, heads, D):
     test_norm_and_rotation_few_tokens(kind, T, S, heads, D)

@@ -108,6 +108,9 @@ def test_module_shapes_take_the_ways_they_are_chosen_for(plan):
 def test_heads_of_32_are_normalised_in_the_tiles_meant_for_them(plan):
     got = plan("qkv", [(T * S, H, 32, S, kind == 1) for _, kind, T, S, H in G.HEADS_OF_32])
     assert [(g[0], g[5]) for g in got] == [(2, shape[0]) for shape in G.HEADS_OF_32]
+    got = plan("qkv", [(T * S, H, 72, S, kind == 1) for kind, T, S, H in G.HEADS_128])
+    assert [(g[0], g[5]) for g in got] == [(2, 145)] * len(got)
+    assert {g[5] for g in plan("qkv", [(T * S, H, D, S, kind == 1) for kind, T, S, H, D in G.FEW_TOKENS if D == 72])} == {144}
 
 
 def test_text_projection_rides_where_it_is_meant_to(plan):
