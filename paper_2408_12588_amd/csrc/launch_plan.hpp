@@ -130,12 +130,20 @@ inline bool store_in_row_order(long long n_bh, int sq, long long row_pitch_bytes
 //      K groups (odd numbers) where every workgroup has a CU to itself and there are 6 slices or more: 64 x 64 tiles, three
 //      groups, 1260 x 576 x 2304 13.9 -> 10.1, 800 x 1152 x 1152 8.7 -> 7.0, 60 x 1152 x 4608 22.8 -> 15.1, but 1260 x 288 x 288 the
 //      same 4.2, and 360 tiles on 256 CUs 30.6 -> 33.0; 64 x 128, two groups, 1260 x 1152 x 4608 29.7 -> 24.6; 128 x 128, two
-//      groups, 2800 x 1152 x 4608 47.3 -> 39.4, 500 x 4608 x 1152 16.2 -> 14.2. ----
+//      groups, 2800 x 1152 x 4608 47.3 -> 39.4, 500 x 4608 x 1152 16.2 -> 14.2.
+//      Two groups with 96, 160 and 192 tokens x 128 features: the K loop is one round of at most a tile per CU, so the height that
+//      just fits sets its length; without them 4109 tokens of 1152 features began a second round.
+//      2552 x 1152 x 4608 39.7 -> 36.8 (96), 4109 x 1152 x 4608 60.7 -> 44.6, 5157 x 864 x 3456 46.9 -> 34.8, 1302 x 3456 x 1152
+//      19.6 -> 17.4, 4281 x 1152 x 1152 19.5 -> 15.8 (160), 7417 x 648 x 2592 38.7 -> 32.9 (192); 1170 x 3456 x
+//      864, 15.7 -> 16.1, is the one loss of 120 shapes. ----
 constexpr int GEMM_CUS = 256;
 
 struct GemmPlan {
-  int kernel;            // 8, 9: gemm_stream with that many sub-tiles per wave column; 64, 96, 128: gemm_tile, 1 more: its K groups
-  int n_mt, n_nt, ms_tail, n_units;
+  int kernel;            // 8, 9: gemm_stream with that many sub-tiles per wave column; 64, 96, 128: gemm_tile, 1 more: its K groups;
+                         // 113, 161, 193: its K groups over tiles of 96, 160, 192 tokens x 128 features
+  int n_mt, n_nt;
+  int ms_tail;           // gemm_stream: token rows / 64 of the tail tiles
+  int n_units;
   double us;
   int by_feature;        // gemm_tile, gemm_heads: the order of the tiles
 };
@@ -154,6 +162,9 @@ inline int tile_order(int bm, int bn, long long n_mt, long long n_nt) {
   };
   return 2 * rows(n_mt, n_nt, bm, bn) <= rows(n_nt, n_mt, bn, bm);
 }
+
+inline int tile_tokens(int kernel) { return kernel == 113 ? 96 : kernel == 161 ? 160 : kernel == 193 ? 192 : kernel >= 128 ? 128 : 64; }
+inline int tile_features(int kernel) { return kernel < 96 ? 64 : 128; }
 
 inline void plan_stream(int ns, int M, int N, int slices, GemmPlan *best) {
   static const double part[5] = {0, 0.50, 0.66, 0.82, 1.0};
@@ -176,8 +187,9 @@ inline void plan_stream(int ns, int M, int N, int slices, GemmPlan *best) {
   }
 }
 
-inline void plan_tile(int kernel, int bm, int bn, double base, double latency, double l2, double out, int M, int N, int slices,
+inline void plan_tile(int kernel, double base, double latency, double l2, double out, int M, int N, int slices,
                GemmPlan *best) {
+  const int bm = tile_tokens(kernel), bn = tile_features(kernel);
   const long long n_mt = ((long long)M + bm - 1) / bm, n_nt = (N + bn - 1) / bn;
   if ((kernel & 1) && (n_mt * n_nt > GEMM_CUS || slices < 6)) return;   // K groups: one workgroup per CU
   double load = n_mt * n_nt / (double)GEMM_CUS + 0.25;
@@ -202,12 +214,24 @@ inline void plan_heads(int kernel, double base, double slice, double out, int M,
 inline GemmPlan plan_tiles(int M, int N, int K) {
   GemmPlan best{0, 0, 0, 0, 0, 1e30, 0};
   const int slices = (K + 63) / 64;
-  plan_tile(64, 64, 64, 2.9, 0.26, 0.25, 0.55, M, N, slices, &best);
-  plan_tile(65, 64, 64, 2.95, 0.185, 0.17, 0.55, M, N, slices, &best);
-  plan_tile(96, 64, 128, 3.3, 0.32, 0.36, 1.1, M, N, slices, &best);
-  plan_tile(97, 64, 128, 3.2, 0.285, 0.24, 1.1, M, N, slices, &best);
-  plan_tile(128, 128, 128, 3.5, 0.55, 0.52, 2.2, M, N, slices, &best);
-  plan_tile(129, 128, 128, 3.6, 0.48, 0.45, 1.6, M, N, slices, &best);
+  plan_tile(64, 2.9, 0.26, 0.25, 0.55, M, N, slices, &best);
+  plan_tile(65, 2.95, 0.185, 0.17, 0.55, M, N, slices, &best);
+  plan_tile(96, 3.3, 0.32, 0.36, 1.1, M, N, slices, &best);
+  plan_tile(97, 3.2, 0.285, 0.24, 1.1, M, N, slices, &best);
+  plan_tile(128, 3.5, 0.55, 0.52, 2.2, M, N, slices, &best);
+  plan_tile(129, 3.6, 0.48, 0.45, 1.6, M, N, slices, &best);
+  if (K >= 384) {
+    // 96 tokens only past 2400: 2552 .. 7233 tokens take 0.86 .. 0.94 of the time.  The line is not where the gain ends (595 x 4608 x
+    // 1152 13.4 -> 12.2, 2200 x 1152 x 1152 13.4 -> 12.3): the plans of smaller sizes are held by tests and stay as they were.
+    if (M > 2400) plan_tile(113, 3.5, 0.41, 0.37, 1.3, M, N, slices, &best);
+    // a taller tile only where the next lower one has more tiles than CUs: 160 tokens beside a round of 128 that fits, 3786 x 960 x
+    // 3840 33.1 -> 37.1, 6340 x 576 x 2304 22.4 -> 24.6, 3806 x 960 x 960 12.4 -> 13.5
+    const auto past = [&](int kernel) {
+      return ((long long)M + tile_tokens(kernel) - 1) / tile_tokens(kernel) * ((N + 127) / 128) > GEMM_CUS;
+    };
+    if (past(129)) plan_tile(161, 3.8, 0.50, 0.475, 2.0, M, N, slices, &best);
+    if (past(161)) plan_tile(193, 4.0, 0.57, 0.565, 2.4, M, N, slices, &best);
+  }
   return best;
 }
 
@@ -241,7 +265,7 @@ inline PairPlan plan_pair(int M, int N, int M2, int N2, int K) {
     p.n_units2 = (M2 + 64LL * p.ms2 - 1) / (64 * p.ms2) * p.n_nt2;
     if (M2 < 64 || N2 < bn || p.n_units2 > room) p.n_units2 = 0;
   } else if (g.kernel) {
-    const int bm = g.kernel >= 128 ? 128 : 64, bn = g.kernel < 96 ? 64 : 128;
+    const int bm = tile_tokens(g.kernel), bn = tile_features(g.kernel);
     p.n_nt2 = (N2 + bn - 1) / bn;
     p.n_units2 = ((long long)M2 + bm - 1) / bm * p.n_nt2;
     if (g.n_units + p.n_units2 > (g.kernel & 1 ? (long long)GEMM_CUS : 0x7ffffff0LL)) p.n_units2 = 0;

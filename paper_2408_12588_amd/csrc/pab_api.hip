@@ -346,7 +346,10 @@ void launch_gemm_kernel(const GemmPlan &g, const pab::GemmParams &p, hipStream_t
     case 96: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 4, 2, 2, 3, 1, EPI>), tiles, dim3(512), 0, st, p); break;
     case 97: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 4, 2, 2, 3, 2, EPI>), tiles, dim3(1024), 0, st, p); break;
     case 128: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 4, 4, 2, 1, EPI>), tiles, dim3(256), 0, st, p); break;
+    case 113: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 3, 4, 2, 2, EPI>), tiles, dim3(512), 0, st, p); break;
     case 129: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 4, 4, 2, 2, EPI>), tiles, dim3(512), 0, st, p); break;
+    case 161: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 5, 4, 2, 2, EPI>), tiles, dim3(512), 0, st, p); break;
+    case 193: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 6, 4, 2, 2, EPI>), tiles, dim3(512), 0, st, p); break;
   }
 }
 

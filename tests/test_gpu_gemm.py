@@ -65,6 +65,22 @@ def test_projection_tiles(M, N, K):
     assert (err <= bound).all(), "max excess %.3e at %s" % ((err - bound).max(), np.unravel_index((err - bound).argmax(), err.shape))
 
 
+TILE_HEIGHTS = [
+    # kernel, M, N, K: two K groups over tiles of 96, 160 and 192 tokens, ragged tiles, four features (mod 8) in the last ones
+    (113, 2816, 892, 480),      # 7.5 slices; tiles of 32 token rows at the end
+    (113, 3962, 676, 800),
+    (161, 4962, 908, 544),      # 8.5 slices: the half slice with the first group
+    (161, 1048, 3644, 1376),    # 21.5 slices
+    (193, 2860, 2140, 800),     # 12.5 slices
+    (193, 1300, 4596, 1120),
+]
+
+
+@pytest.mark.parametrize("M,N,K", [s[1:] for s in TILE_HEIGHTS])
+def test_projection_tile_heights(M, N, K):
+    test_projection_tiles(M, N, K)
+
+
 HALF_SLICES = [
     # M, N, K: odd multiples of 32, the last K slice has 32 columns (kernel as picked by the size rule)
     (9001, 2304, 160),    # large tiles, 256 features
@@ -228,6 +244,9 @@ HEADS_OF_32 = [
     (97, 1, 20, 37, 16),
     (128, 1, 16, 351, 12),
     (129, 0, 3, 667, 16),
+    (113, 1, 6, 407, 12),
+    (161, 1, 17, 153, 19),   # planes that begin inside a tile
+    (193, 1, 7, 354, 25),
 ]
 
 

@@ -94,6 +94,10 @@ def test_projection_shapes_take_the_kernels_they_are_chosen_for(plan):
     assert [g[0] for g in plan("gemm", G.HALF_SLICES)] == [8, 9, 8, 65, 64]
 
 
+def test_tile_heights_are_those_meant(plan):
+    assert [g[0] for g in plan("gemm", [s[1:] for s in G.TILE_HEIGHTS])] == [s[0] for s in G.TILE_HEIGHTS]
+
+
 def test_module_shapes_take_the_ways_they_are_chosen_for(plan):
     qkv = lambda shapes: plan("qkv", [(T * S, H, D, S, kind == 1) for kind, T, S, H, D in shapes])
     assert [q[0] for q in qkv([m + (72,) for m in G.MODULES])] == [1, 1, 1, 1, 0]
