@@ -9,8 +9,8 @@
 //                group g takes the key tiles t = g (mod G), so the item is done in 1/G of the steps,
 //                and the partial results (running maximum, O^T with its denominator row) are combined
 //                through LDS at the end: four times as many workgroups, each a quarter as long, at 1.3 times the
-//                work.  The host takes them for small launches, which would leave CUs empty, and for the problems
-//                that would make some CUs hold a workgroup more than the others (the rule and its figures:
+//                work.  The host takes them for launches that would leave CUs empty (the smallest of those go to
+//                attn_short.hpp) and for the problems that would make some CUs hold a workgroup more than the others (the rule and its figures:
 //                plan_items in launch_plan.hpp).
 // Each wavefront keeps the q operands of its 32 queries in registers.  Keys and values stream through
 // a ring of NRING LDS stages, one 32-key tile per stage, rows packed as in memory (for bf16 inputs the

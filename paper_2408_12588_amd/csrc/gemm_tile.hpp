@@ -15,6 +15,10 @@
 // CU to itself, KG groups of WM x WN wavefronts share it: group g takes the
 // slices g (mod KG) through a ring of its own, and the groups' fp32 sums are added
 // through LDS at the end (1260 x 576 x 2304 13.9 -> 10.1 us with three groups).
+// Two groups also take tiles of 96, 160 and 192 tokens x 128 features: the loop is one
+// round, so its length is that of the tile; the next height up costs less than a second
+// round of 128 tokens (4413 x 1008 x 4032 53.6 -> 39.7 us with 160, 5709 x 1024 x 4096
+// 54.8 -> 45.3 with 192).
 #pragma once
 #include <type_traits>
 #include "gemm_common.hpp"
