@@ -16,6 +16,7 @@
 // tile and head, 64 bytes per clock and CU) take longer than the arithmetic.  plan_short and
 // plan_short_cross in launch_plan.hpp have the lines.
 #pragma once
+#include "attn_short_layout.hpp"
 #include "mfma_util.hpp"
 
 namespace pab {
@@ -70,7 +71,7 @@ template <typename T, int D, int NW, int G>
 __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 2 : 4) void attn_short_kernel(const ShortParams p) {
   constexpr int CH = D / 8;                  // 8-element chunks of a row
   constexpr int QT = NW / G;                 // query tiles of a workgroup
-  constexpr int RP = D + 8;                  // pitch of K and V rows in LDS: 40 (20) banks, which no 16-byte operand read conflicts on
+  constexpr int RP = SHORT_PITCH<D>;         // pitch of K and V rows in LDS
   constexpr int DT16 = (D + 1 + 15) / 16;
   constexpr int OP = D + 4;                  // floats of a partial row: D sums, denominator, maximum, two unused
   constexpr int KV_BYTES = 2 * 32 * RP * 2, O_BYTES = 32 * OP * 4;
@@ -170,7 +171,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 2 : 4) void attn_short_ke
   }
   const float c = p.c, thr = 8.0f / c;
   const bf16_t *k_src = kt + l16 * RP + 8 * g4, *kr_src = kt + l16 * RP + 32 * KS + 4 * g4;
-  const bf16_t *v_src = vt + (4 * g4 + (l16 >> 2)) * RP + 4 * (l16 & 3);
+  const bf16_t *v_row = vt + (4 * g4 + (l16 >> 2)) * RP;
 
   for (int t = kg; t < ntile; t += G) {
     // what was requested has landed (the copies are invisible to the compiler)
@@ -261,7 +262,8 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 2 : 4) void attn_short_ke
           pf[qh][4 * kh + r] = (bf16_t)__builtin_amdgcn_exp2f(__builtin_fmaf(S[kh][qh][r], c, m_negc[qh]));
 #pragma unroll
     for (int dt = 0; dt < DT16; ++dt) {
-      const bf16x4 lo = lds_read_tr4(v_src + 16 * dt), hi = lds_read_tr4(v_src + 16 * dt + 16 * RP);
+      const bf16_t *v_src = v_row + short_v_column<D>(dt, l16 & 3);
+      const bf16x4 lo = lds_read_tr4(v_src), hi = lds_read_tr4(v_src + 16 * RP);
       bf16x8 vf;
       vf[0] = lo[0]; vf[1] = lo[1]; vf[2] = lo[2]; vf[3] = lo[3];
       vf[4] = hi[0]; vf[5] = hi[1]; vf[6] = hi[2]; vf[7] = hi[3];
