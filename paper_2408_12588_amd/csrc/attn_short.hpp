@@ -242,10 +242,12 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 2 : 4) void attn_short_ke
 #pragma unroll
       for (int qh = 0; qh < 2; ++qh) {
         const float m_new = fmaxf(m_run[qh], max_quad16(mx[qh]));
-        const float alpha = __builtin_amdgcn_exp2f((m_run[qh] - m_new) * c);
+        // another query of the wavefront grows; this one may have seen no key but of score -inf: it weighs nothing and stays 0
+        const bool none = m_new == -INFINITY;
+        const float alpha = none ? 1.0f : __builtin_amdgcn_exp2f((m_run[qh] - m_new) * c);
         m_run[qh] = m_new;
         m_thr[qh] = m_new + thr;
-        m_negc[qh] = -m_new * c;
+        m_negc[qh] = none ? 0.0f : -m_new * c;
 #pragma unroll
         for (int dt = 0; dt < DT16; ++dt)
 #pragma unroll

@@ -635,6 +635,32 @@ def test_short_launch_keeps_infinite_keys_to_themselves(pab, dtype):
     assert_close(out, want, v, "infinite keys")
 
 
+# small launches, every way of the short kernel: 10 x wavefronts + key groups, kind, T, S, L, H, D, dtype
+SHORT_EXTREMES = [
+    (22, W.SPATIAL, 2, 33, 0, 2, 72, "bf16"), (22, W.SPATIAL, 2, 33, 0, 2, 32, "f32"), (44, W.SPATIAL, 1, 97, 0, 3, 72, "f32"),
+    (44, W.SPATIAL, 1, 180, 0, 2, 72, "bf16"), (42, W.SPATIAL, 4, 97, 0, 20, 72, "bf16"), (41, W.SPATIAL, 23, 97, 0, 16, 72, "bf16"),
+]
+SHORT_CROSS_EXTREMES = [
+    (44, W.CROSS, 1, 70, 97, 3, 72, "bf16"), (44, W.CROSS, 1, 70, 300, 3, 32, "bf16"),
+]
+
+
+@pytest.mark.parametrize("kind,T,S,L,H,D,dtype", [s[1:] for s in SHORT_EXTREMES + SHORT_CROSS_EXTREMES])
+def test_short_launch_with_key_tiles_that_some_queries_do_not_see(pab, kind, T, S, L, H, D, dtype):
+    """Scores of -inf (products past the range of fp32) for some queries and finite ones for their neighbours, in all keys of the
+    last tile, then of the first: a key group or a first tile without any weight for a query leaves the rest of it as it is."""
+    keys = L if kind == W.CROSS else S
+    for hit in (range(keys // 32 * 32 if keys % 32 else keys - 32, keys), range(32)):
+        print("unseen", W.KIND_NAMES[kind], T, S, L, H, D, dtype, hit, flush=True)
+        q, k, v = rand_qkv(kind, T, S, L, H, D, dtype, seed=4800 + S + L)
+        q[:, 0::2, :, 5], q[:, 1::2, :, 5] = 10.0, 1e-30
+        k[..., 5] = 0.0
+        k[..., list(hit), :, 5] = -3e38
+        out = pab.pab_attention_compute(kind, q.to(DEV), k.to(DEV), v.to(DEV))
+        torch.cuda.synchronize()
+        assert_close(out, orc.kind_attention(kind, q, k, v), v, "unseen keys")
+
+
 TILE_SHAPES = [
     # kind, T, S, L, H, D, dtype: what the tile kernel keeps of the split items and of the stores as accumulated
     (W.SPATIAL, 1, 1633, 0, 3, 72, "bf16"),    # all split: 52 key tiles, the last with one key; 33 queries in the last item

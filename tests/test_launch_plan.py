@@ -180,6 +180,12 @@ def test_cross_attention_of_few_tokens(plan):
     assert ask(full) == [0] * len(full)
 
 
+def test_extreme_inputs_of_the_short_kernel_take_every_way_of_it(plan):
+    assert [r[0] for r in plan("short", [items_of(s[1:]) for s in P.SHORT_EXTREMES])] == [s[0] for s in P.SHORT_EXTREMES]
+    cross = [(T * S, L, H, D) for _, _, T, S, L, H, D, _ in P.SHORT_CROSS_EXTREMES]
+    assert [r[0] for r in plan("cross", cross)] == [s[0] for s in P.SHORT_CROSS_EXTREMES]
+
+
 def test_order_of_stores(plan):
     accumulated = [(1600, 34, 230400), (925, 50, 133200), (925, 72, 133200), (1000, 96, 1440), (10 ** 6, 48, 2304)]
     in_rows = [(5005, 80, 720720), (1480, 96, 213120), (256, 400, 2304), (2100, 49, 302400), (4, 129, 720)]
