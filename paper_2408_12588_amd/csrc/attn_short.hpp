@@ -219,6 +219,12 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 2 : 4) void attn_short_ke
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (t + G < ntile) request(kb, t + G, false);
     if (32 * t + 32 > sk) {
+      // rows past the last key are copies of it and weigh 0: zeros in V, or an infinity of that key would become NaN.  Two
+      // lanes per row, the chunk in the middle twice
+      if (32 * t + (lane >> 1) >= sk) {
+#pragma unroll
+        for (int i = 0; i < (CH + 1) / 2; ++i) *reinterpret_cast<bf16x8 *>(vt + (lane >> 1) * RP + 8 * (i + (lane & 1) * (CH / 2))) = zero8();
+      }
 #pragma unroll
       for (int kh = 0; kh < 2; ++kh)
 #pragma unroll

@@ -661,6 +661,22 @@ def test_short_launch_with_key_tiles_that_some_queries_do_not_see(pab, kind, T, 
         assert_close(out, orc.kind_attention(kind, q, k, v), v, "unseen keys")
 
 
+@pytest.mark.parametrize("kind,T,S,L,H,D,dtype", [s[1:] for s in SHORT_EXTREMES + SHORT_CROSS_EXTREMES])
+def test_short_launch_with_an_infinite_last_value(pab, kind, T, S, L, H, D, dtype):
+    """An infinity in the last key's values gives that infinity in its column, no NaN there and nothing elsewhere: the rows that fill the
+    last tile weigh 0, and 0 times a copy of that row would not be 0."""
+    print("infinite value", W.KIND_NAMES[kind], T, S, L, H, D, dtype, flush=True)
+    q, k, v = rand_qkv(kind, T, S, L, H, D, dtype, seed=4900 + S + L)
+    want = orc.kind_attention(kind, q, k, v)
+    bad = v.clone()
+    bad[..., -1, :, 3], bad[..., -1, :, D - 1] = float("inf"), float("-inf")
+    out = pab.pab_attention_compute(kind, q.to(DEV), k.to(DEV), bad.to(DEV)).cpu()
+    torch.cuda.synchronize()
+    assert bool((out[..., 3] == float("inf")).all()) and bool((out[..., D - 1] == float("-inf")).all())
+    rest = [d for d in range(D) if d not in (3, D - 1)]
+    assert_close(out[..., rest], want[..., rest], v, "beside an infinite value")
+
+
 TILE_SHAPES = [
     # kind, T, S, L, H, D, dtype: what the tile kernel keeps of the split items and of the stores as accumulated
     (W.SPATIAL, 1, 1633, 0, 3, 72, "bf16"),    # all split: 52 key tiles, the last with one key; 33 queries in the last item
