@@ -334,11 +334,17 @@ size_t module_plane_bytes(int T, int S, int L, int H, int D) {
 }
 
 template <int EPI>
-void launch_gemm_kernel(const GemmPlan &g, const pab::GemmParams &p, hipStream_t st) {
+int launch_gemm_kernel(const GemmPlan &g, const pab::GemmParams &p, hipStream_t st) {
   const dim3 persistent((unsigned)std::min(g.n_units, GEMM_CUS)), tiles((unsigned)((g.n_units + 7) / 8 * 8));
   if constexpr (EPI != pab::GEMM_NORM) {
-    if (g.kernel == 8) hipLaunchKernelGGL((pab::gemm_stream_kernel<8, 4, EPI>), persistent, dim3(512), 0, st, p);
-    if (g.kernel == 9) hipLaunchKernelGGL((pab::gemm_stream_kernel<9, 3, EPI>), persistent, dim3(512), 0, st, p);
+    if (g.kernel == 8) {
+      hipLaunchKernelGGL((pab::gemm_stream_kernel<8, 4, EPI>), persistent, dim3(512), 0, st, p);
+      return PAB_OK;
+    }
+    if (g.kernel == 9) {
+      hipLaunchKernelGGL((pab::gemm_stream_kernel<9, 3, EPI>), persistent, dim3(512), 0, st, p);
+      return PAB_OK;
+    }
   }
   switch (g.kernel) {
     case 64: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 2, 2, 3, 1, EPI>), tiles, dim3(256), 0, st, p); break;
@@ -350,7 +356,9 @@ void launch_gemm_kernel(const GemmPlan &g, const pab::GemmParams &p, hipStream_t
     case 129: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 4, 4, 2, 2, EPI>), tiles, dim3(512), 0, st, p); break;
     case 161: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 5, 4, 2, 2, EPI>), tiles, dim3(512), 0, st, p); break;
     case 193: hipLaunchKernelGGL((pab::gemm_tile_kernel<2, 2, 6, 4, 2, 2, EPI>), tiles, dim3(512), 0, st, p); break;
+    default: return fail(PAB_EINVAL, "no projection kernel %d", g.kernel);
   }
+  return PAB_OK;
 }
 
 int gemm_params(pab::GemmParams *p, int M, int N, int K, const void *A, const void *W, const void *bias, void *C,
@@ -394,8 +402,8 @@ int launch_gemm(int M, int N, int K, const void *A, const void *W, const void *b
   if (rc != PAB_OK) return rc;
   const GemmPlan g = pab::plan_gemm(M, N, K);
   if ((rc = gemm_planned(g, &p)) != PAB_OK) return rc;
-  if (act) launch_gemm_kernel<pab::GEMM_GELU>(g, p, st);
-  else launch_gemm_kernel<pab::GEMM_PLAIN>(g, p, st);
+  rc = act ? launch_gemm_kernel<pab::GEMM_GELU>(g, p, st) : launch_gemm_kernel<pab::GEMM_PLAIN>(g, p, st);
+  if (rc != PAB_OK) return rc;
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(PAB_EDEVICE, "kernel launch failed: %s", hipGetErrorString(e));
   return PAB_OK;
@@ -418,8 +426,7 @@ int launch_gemm_pair(int M, int N, int K, const void *A, const void *W, const vo
   GemmPlan g = pair.first;
   g.n_units += p.n_units2;
   p.n_inner2 = g.by_feature ? p.n_units2 / p.n_nt2 : p.n_nt2;
-  if ((rc = gemm_planned(g, &p)) != PAB_OK) return rc;
-  launch_gemm_kernel<pab::GEMM_PLAIN>(g, p, st);
+  if ((rc = gemm_planned(g, &p)) != PAB_OK || (rc = launch_gemm_kernel<pab::GEMM_PLAIN>(g, p, st)) != PAB_OK) return rc;
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(PAB_EDEVICE, "kernel launch failed: %s", hipGetErrorString(e));
   return PAB_OK;
@@ -476,7 +483,7 @@ int launch_qkv(int n_tok, int H, int D, int S, int rope, const void *h, const pa
     const dim3 tiles((unsigned)((p.n_units + 7) / 8 * 8)), block(768);
     if (plan.gemm.kernel == 144) hipLaunchKernelGGL((pab::gemm_heads_kernel<2, 3, 2, 3, 3, 2, 72>), tiles, block, 0, st, p);
     else if (plan.gemm.kernel == 145) hipLaunchKernelGGL((pab::gemm_heads_kernel<2, 3, 4, 3, 2, 2, 72>), tiles, block, 0, st, p);
-    else launch_gemm_kernel<pab::GEMM_NORM>(plan.gemm, p, st);
+    else return launch_gemm_kernel<pab::GEMM_NORM>(plan.gemm, p, st);
     return PAB_OK;
   }
   if (plan.way == pab::QKV_STREAM) {
@@ -484,7 +491,7 @@ int launch_qkv(int n_tok, int H, int D, int S, int rope, const void *h, const pa
                        dim3(512), 0, st, p);
     return PAB_OK;
   }
-  launch_gemm_kernel<pab::GEMM_PLAIN>(plan.gemm, p, st);
+  if ((rc = launch_gemm_kernel<pab::GEMM_PLAIN>(plan.gemm, p, st)) != PAB_OK) return rc;
   return launch_qk_norm(n_tok, H, D, S, rope, q, static_cast<pab::bf16_t *>(q) + plane_elems, w, st);
 }
 

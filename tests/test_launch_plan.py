@@ -2,6 +2,7 @@
 tests of the kernels choose their shapes for the path that they run; here that choice is held, so that a change of a
 planner's constant cannot silently empty one of them."""
 import os
+import re
 import subprocess
 
 import pytest
@@ -96,6 +97,21 @@ def test_projection_shapes_take_the_kernels_they_are_chosen_for(plan):
 
 def test_tile_heights_are_those_meant(plan):
     assert [g[0] for g in plan("gemm", [s[1:] for s in G.TILE_HEIGHTS])] == [s[0] for s in G.TILE_HEIGHTS]
+
+
+def test_every_planned_projection_kernel_is_launched(plan):
+    """Each number that the planners give has a case in launch_gemm_kernel (those of large tiles only without the norm), and any
+    other one is an error, not a call without a launch."""
+    source = open(os.path.join(ROOT, "paper_2408_12588_amd", "csrc", "pab_api.hip")).read()
+    body = source[source.index("launch_gemm_kernel(const GemmPlan"):]
+    body = body[:body.index("\n}\n")]
+    cases = {int(n) for n in re.findall(r"case (\d+): hipLaunch", body)}
+    assert re.search(r"default: return fail\(", body)
+    sizes = sorted({int(round(16 * 1.17 ** i)) for i in range(51)})
+    gemm = {g[0] for g in plan("gemm", [(m, n, k) for m in sizes for n in (64, 288, 576, 1152, 3456, 4608) for k in (32, 288, 576, 1152, 4608)])}
+    assert gemm <= cases | {8, 9} and {8, 9, 64, 97, 129, 161, 193} <= gemm, gemm
+    qkv = plan("qkv", [(m, h, 32, 64, 1) for m in sizes for h in (1, 3, 4, 9, 16, 25, 36)])
+    assert {q[5] for q in qkv if q[0] == 2} <= cases
 
 
 def test_module_shapes_take_the_ways_they_are_chosen_for(plan):
