@@ -9,9 +9,13 @@ import, and every step of the path runs in the library's HIP kernels.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
+import warnings
 
 import torch
+
+from .build import binding_path
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libpab.so")
@@ -210,12 +214,33 @@ def pab_workspace_bytes(cfg: pab_config) -> int:
     return n
 
 
-try:
-    from . import _binding   # csrc/pab_binding.cpp
-except ImportError as e:
-    raise ImportError("_binding.so is not built (%s): run `python -m paper_2408_12588_amd.build` or "
-                      "__graft_entry__.build()" % e) from e
-_binding.bind(_check, getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None))
+class _NoBinding:
+    """In the place of the native binding: hands every call back to the Python code."""
+
+    @staticmethod
+    def attention(*args):
+        return NotImplemented
+
+    attention_compute = attention
+
+
+def _load_binding():
+    """csrc/pab_binding.cpp as built for this Python and this torch; without it the same calls are marshalled here, by ctypes."""
+    path = binding_path(torch.__version__)
+    if not os.path.exists(path):
+        return _NoBinding
+    try:
+        spec = importlib.util.spec_from_file_location(__package__ + "._binding", path)
+        binding = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(binding)
+    except ImportError as e:
+        warnings.warn("%s does not load: calls go through ctypes (%s)" % (os.path.basename(path), e))
+        return _NoBinding
+    binding.bind(_check, getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None))
+    return binding
+
+
+_binding = _load_binding()
 
 
 def _stream(stream) -> int:

@@ -350,3 +350,56 @@ def test_native_binding_leaves_the_unusual_to_python():
         with pytest.raises(TypeError):
             b.attention(*wrong)
     pab.lib.pab_destroy(h)
+
+
+def _package_copy(tmp_path, binding):
+    """This package with libpab.so and, unless None, `binding` as the content of its native binding."""
+    import shutil
+    import torch
+    here = os.path.dirname(pab.__file__)
+    there = tmp_path / os.path.basename(here)
+    there.mkdir()
+    for name in os.listdir(here):
+        if name.endswith(".py") or name == "libpab.so":
+            shutil.copy(os.path.join(here, name), there / name)
+    if binding is not None:
+        (there / os.path.basename(pab.binding_path(torch.__version__))).write_bytes(binding)
+    return there
+
+
+@pytest.mark.parametrize("binding", [None, b"built for another machine"])
+def test_package_works_without_the_native_binding(tmp_path, binding):
+    """libpab.so alone is enough: without the binding, or with one that does not load, calls take the Python path."""
+    import subprocess
+    import sys
+    code = ("from %s import pab\n"
+            "import os, sys; assert pab.__file__.startswith(sys.argv[1])\n"
+            "assert pab._binding.attention(0, 0, 0, 0, None, None, None, None) is NotImplemented\n"
+            "assert pab._binding.attention_compute(0, None, None, None, None, None) is NotImplemented\n"
+            "assert pab.pab_schedule(0, 3, 2, 8, 2) == pab.REUSE\n") % os.path.basename(os.path.dirname(pab.__file__))
+    _package_copy(tmp_path, binding)
+    res = subprocess.run([sys.executable, "-c", code, str(tmp_path)], cwd=tmp_path, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr
+    assert ("does not load" in res.stderr) == (binding is not None)
+
+
+def test_library_builds_without_what_the_binding_needs(tmp_path, monkeypatch, capsys):
+    """libpab.so needs hipcc only; a binding that cannot be built is said and not an error of its callers.  One that was built for
+    another torch or Python does not count as built."""
+    from paper_2408_12588_amd import build
+    hipcc = tmp_path / "hipcc"
+    hipcc.write_text("#!/bin/sh\nwhile [ \"$1\" != -o ]; do shift; done\ntouch \"$2\"\n")
+    hipcc.chmod(0o755)
+    monkeypatch.setenv("HIPCC", str(hipcc))
+    monkeypatch.setenv("CXX", "false")
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "libpab.so"))
+    assert build.build_lib() == build.LIB and os.path.exists(build.LIB)
+    assert build.ensure_built() == build.LIB
+    assert "binding is not built" in capsys.readouterr().err
+    with pytest.raises(RuntimeError):
+        build.build_binding()
+    assert sorted(os.listdir(tmp_path)) == ["hipcc", "libpab.so"]
+    import sysconfig
+    here = build.binding_path()
+    assert here.endswith(sysconfig.get_config_var("EXT_SUFFIX")) and here != build.binding_path("2.0.0")
