@@ -187,15 +187,22 @@ inline void plan_stream(int ns, int M, int N, int slices, GemmPlan *best) {
   }
 }
 
-inline void plan_tile(int kernel, double base, double latency, double l2, double out, int M, int N, int slices,
-               GemmPlan *best) {
+// tiles of a problem
+inline long long count_tiles(int kernel, int M, int N) {
   const int bm = tile_tokens(kernel), bn = tile_features(kernel);
-  const long long n_mt = ((long long)M + bm - 1) / bm, n_nt = (N + bn - 1) / bn;
-  if ((kernel & 1) && (n_mt * n_nt > GEMM_CUS || slices < 6)) return;   // K groups: one workgroup per CU
-  double load = n_mt * n_nt / (double)GEMM_CUS + 0.25;
+  return ((long long)M + bm - 1) / bm * ((N + bn - 1) / bn);
+}
+
+// M2, N2: a second problem in the same launch (plan_pair), M2 = 0: none
+inline void plan_tile(int kernel, double base, double latency, double l2, double out, int M, int N, int slices,
+               GemmPlan *best, int M2 = 0, int N2 = 0) {
+  const int bm = tile_tokens(kernel), bn = tile_features(kernel);
+  const long long n_mt = ((long long)M + bm - 1) / bm, n_nt = (N + bn - 1) / bn, all = n_mt * n_nt + count_tiles(kernel, M2, N2);
+  if ((kernel & 1) && (all > GEMM_CUS || slices < 6)) return;   // K groups: one workgroup per CU
+  double load = all / (double)GEMM_CUS + 0.25;
   if (kernel == 128 && load > 1.5) load *= load <= 2.25 ? 0.8 : load <= 2.85 ? 1.1 : 1.0;   // one round of two per CU, a second begun
   const double us = base + slices * std::max(latency, load * l2) + load * out;
-  if (n_mt * n_nt <= 0x7ffffff0LL && us < best->us)
+  if (all <= 0x7ffffff0LL && us < best->us)
     *best = GemmPlan{kernel, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), us, tile_order(bm, bn, n_mt, n_nt)};
 }
 
@@ -211,26 +218,24 @@ inline void plan_heads(int kernel, double base, double slice, double out, int M,
     *best = GemmPlan{kernel, (int)n_mt, (int)n_nt, 0, (int)(n_mt * n_nt), us, tile_order(bm, bn, n_mt, n_nt)};
 }
 
-inline GemmPlan plan_tiles(int M, int N, int K) {
+inline GemmPlan plan_tiles(int M, int N, int K, int M2 = 0, int N2 = 0) {
   GemmPlan best{0, 0, 0, 0, 0, 1e30, 0};
   const int slices = (K + 63) / 64;
-  plan_tile(64, 2.9, 0.26, 0.25, 0.55, M, N, slices, &best);
-  plan_tile(65, 2.95, 0.185, 0.17, 0.55, M, N, slices, &best);
-  plan_tile(96, 3.3, 0.32, 0.36, 1.1, M, N, slices, &best);
-  plan_tile(97, 3.2, 0.285, 0.24, 1.1, M, N, slices, &best);
-  plan_tile(128, 3.5, 0.55, 0.52, 2.2, M, N, slices, &best);
-  plan_tile(129, 3.6, 0.48, 0.45, 1.6, M, N, slices, &best);
+  plan_tile(64, 2.9, 0.26, 0.25, 0.55, M, N, slices, &best, M2, N2);
+  plan_tile(65, 2.95, 0.185, 0.17, 0.55, M, N, slices, &best, M2, N2);
+  plan_tile(96, 3.3, 0.32, 0.36, 1.1, M, N, slices, &best, M2, N2);
+  plan_tile(97, 3.2, 0.285, 0.24, 1.1, M, N, slices, &best, M2, N2);
+  plan_tile(128, 3.5, 0.55, 0.52, 2.2, M, N, slices, &best, M2, N2);
+  plan_tile(129, 3.6, 0.48, 0.45, 1.6, M, N, slices, &best, M2, N2);
   if (K >= 384) {
     // 96 tokens only past 2400: 2552 .. 7233 tokens take 0.86 .. 0.94 of the time.  The line is not where the gain ends (595 x 4608 x
     // 1152 13.4 -> 12.2, 2200 x 1152 x 1152 13.4 -> 12.3): the plans of smaller sizes are held by tests and stay as they were.
-    if (M > 2400) plan_tile(113, 3.5, 0.41, 0.37, 1.3, M, N, slices, &best);
+    if (M > 2400) plan_tile(113, 3.5, 0.41, 0.37, 1.3, M, N, slices, &best, M2, N2);
     // a taller tile only where the next lower one has more tiles than CUs: 160 tokens beside a round of 128 that fits, 3786 x 960 x
     // 3840 33.1 -> 37.1, 6340 x 576 x 2304 22.4 -> 24.6, 3806 x 960 x 960 12.4 -> 13.5
-    const auto past = [&](int kernel) {
-      return ((long long)M + tile_tokens(kernel) - 1) / tile_tokens(kernel) * ((N + 127) / 128) > GEMM_CUS;
-    };
-    if (past(129)) plan_tile(161, 3.8, 0.50, 0.475, 2.0, M, N, slices, &best);
-    if (past(161)) plan_tile(193, 4.0, 0.57, 0.565, 2.4, M, N, slices, &best);
+    const auto past = [&](int kernel) { return count_tiles(kernel, M, N) + count_tiles(kernel, M2, N2) > GEMM_CUS; };
+    if (past(129)) plan_tile(161, 3.8, 0.50, 0.475, 2.0, M, N, slices, &best, M2, N2);
+    if (past(161)) plan_tile(193, 4.0, 0.57, 0.565, 2.4, M, N, slices, &best, M2, N2);
   }
   return best;
 }
@@ -249,6 +254,10 @@ inline GemmPlan plan_gemm(int M, int N, int K) {
 // is launched by itself (25440 and 120 tokens: 7 units of room for 18).  Cross modules in us, two launches -> one: 17408 and 300
 // tokens of 1152 features 149 -> 144, 34000 and 120 of 864 147 -> 143; 2048 and 120 of 1152 39.5 -> 33.0, 6000 and 300 of 864
 // 59.4 -> 54.1, 1260 and 60 of 576 20.0 -> 15.4.
+// Tiles of 96, 160 and 192 tokens are the best ones for the first problem where they just fill the chip, and a launch of its own for the
+// second costs more than they gain: there the pair is planned, the best tiles for both against two launches.  Cross modules in us, best
+// for the first alone -> for both: 2448 and 300 tokens of 1152 features 45.1 -> 40.1, 3339 and 64 of 864 35.7 -> 30.6, 4719 and 90 of 576
+// 31.6 -> 27.4, 7881 and 200 of 576 41.6 -> 38.0, 4188 and 40 of 1152 46.8 -> 41.1, 5130 and 300 of 1152 63.3 -> 58.5.
 struct PairPlan {
   GemmPlan first;        // n_units: those of the first problem
   int n_nt2, ms2;
@@ -257,7 +266,12 @@ struct PairPlan {
 
 inline PairPlan plan_pair(int M, int N, int M2, int N2, int K) {
   PairPlan p{plan_gemm(M, N, K), 0, 0, 0};
-  const GemmPlan &g = p.first;
+  GemmPlan &g = p.first;
+  const auto in_tiles = [&] {
+    p.n_nt2 = (N2 + tile_features(g.kernel) - 1) / tile_features(g.kernel);
+    p.n_units2 = count_tiles(g.kernel, M2, N2);
+    if (g.n_units + p.n_units2 > (g.kernel & 1 ? (long long)GEMM_CUS : 0x7ffffff0LL)) p.n_units2 = 0;
+  };
   if (g.kernel == 8 || g.kernel == 9) {
     const int bn = 32 * g.kernel, room = (GEMM_CUS - g.n_units % GEMM_CUS) % GEMM_CUS;
     p.ms2 = M2 >= 128 ? 2 : 1;
@@ -265,10 +279,14 @@ inline PairPlan plan_pair(int M, int N, int M2, int N2, int K) {
     p.n_units2 = (M2 + 64LL * p.ms2 - 1) / (64 * p.ms2) * p.n_nt2;
     if (M2 < 64 || N2 < bn || p.n_units2 > room) p.n_units2 = 0;
   } else if (g.kernel) {
-    const int bm = tile_tokens(g.kernel), bn = tile_features(g.kernel);
-    p.n_nt2 = (N2 + bn - 1) / bn;
-    p.n_units2 = ((long long)M2 + bm - 1) / bm * p.n_nt2;
-    if (g.n_units + p.n_units2 > (g.kernel & 1 ? (long long)GEMM_CUS : 0x7ffffff0LL)) p.n_units2 = 0;
+    in_tiles();
+    if (!p.n_units2 && (g.kernel == 113 || g.kernel == 161 || g.kernel == 193)) {
+      const GemmPlan both = plan_tiles(M, N, K, M2, N2);
+      if (both.kernel && both.us < g.us + plan_gemm(M2, N2, K).us) {
+        g = both;
+        in_tiles();
+      }
+    }
   }
   return p;
 }

@@ -205,6 +205,18 @@ CROSS_PAIR_PATHS = [(65, 0, True), (64, 0, True), (128, 0, True), (97, 0, True),
                     (9, 1, True), (9, 2, True), (8, 0, False), (8, 0, False), (8, 0, False), (8, 0, False), (8, 0, False), (97, 0, False)]
 
 
+HEIGHT_PAIRS = [
+    # kernel, T, S, L, heads: sizes where tiles of 96, 160 or 192 tokens are the best ones for the queries alone.  Without room for the text:
+    (129, 1, 2448, 300, 16), (129, 1, 3339, 64, 12), (129, 1, 4719, 90, 8), (128, 1, 7881, 200, 8), (193, 1, 4188, 40, 16), (128, 1, 5130, 300, 16),
+    (113, 1, 3762, 40, 8), (161, 1, 3899, 16, 16), (193, 1, 8169, 64, 8),   # with room
+]
+
+
+@pytest.mark.parametrize("T,S,L,heads", [s[1:] for s in HEIGHT_PAIRS])
+def test_query_and_text_projection_of_tile_heights(T, S, L, heads):
+    test_query_and_text_projection(T, S, L, heads)
+
+
 @pytest.mark.parametrize("T,S,L,heads", CROSS_PAIRS)
 def test_query_and_text_projection(T, S, L, heads):
     """Cross modules are independent per token: some against the oracle, 1e-2 of the largest output as elsewhere."""

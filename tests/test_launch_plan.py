@@ -141,6 +141,19 @@ def test_text_projection_rides_where_it_is_meant_to(plan):
             assert units % 256 + units2 <= 256
 
 
+def test_text_projection_rides_beside_the_tile_heights_too(plan):
+    """Tiles that just fill the chip with the queries do not push the text into a launch of its own: bands of sizes, and both sides of them."""
+    got = plan("pair", [(T * S, 72 * H, L, 144 * H, 72 * H) for _, T, S, L, H in G.HEIGHT_PAIRS])
+    assert [(g[0], g[3] > 0) for g in got] == [(s[0], True) for s in G.HEIGHT_PAIRS]
+    alone = {g[0] for g in plan("gemm", [(T * S, 72 * H, 72 * H) for _, T, S, L, H in G.HEIGHT_PAIRS])}
+    assert alone == {113, 161, 193}
+    bands = [(m, 1152, 120) for m in range(2446, 2630, 20)] + [(m, 864, 120) for m in range(3300, 3423, 20)] + [
+        (m, 576, 120) for m in range(4764, 4887, 20)] + [(m, 384, 120) for m in range(7997, 8120, 20)] + [(m, 1152, 120) for m in range(4215, 4460, 20)] + [
+        (m, 864, L) for m in range(2690, 3423, 50) for L in (200, 300)]
+    for shape, (kernel, units, _, units2) in zip(bands, plan("pair", [(m, C, L, 2 * C, C) for m, C, L in bands])):
+        assert units2 > 0 and (kernel % 2 == 0 or units + units2 <= 256), shape
+
+
 def test_split_shapes_are_split(plan):
     part = {(0, 7, 700, 0, 12, 72, "bf16"): 4, (0, 9, 513, 0, 11, 32, "f32"): 19}
     calls = [items_of(shape) for shape in P.SPLIT_SHAPES]
