@@ -229,8 +229,9 @@ inline GemmPlan plan_tiles(int M, int N, int K, int M2 = 0, int N2 = 0) {
   plan_tile(129, 3.6, 0.48, 0.45, 1.6, M, N, slices, &best, M2, N2);
   if (K >= 384) {
     // 96 tokens only past 2400: 2552 .. 7233 tokens take 0.86 .. 0.94 of the time.  The line is not where the gain ends (595 x 4608 x
-    // 1152 13.4 -> 12.2, 2200 x 1152 x 1152 13.4 -> 12.3): the plans of smaller sizes are held by tests and stay as they were.
-    if (M > 2400) plan_tile(113, 3.5, 0.41, 0.37, 1.3, M, N, slices, &best, M2, N2);
+    // 1152 13.4 -> 12.2, 2200 x 1152 x 1152 13.4 -> 12.3): the plans of smaller sizes are held by tests and stay as they were.  Nor
+    // beside 64 x 64 tiles where those are the best of the others, about two per CU: 3291 x 576 x 576 6.4 -> 7.3, 5921 x 288 x 1152 9.6 -> 10.7.
+    if (M > 2400 && best.kernel != 64) plan_tile(113, 3.5, 0.41, 0.37, 1.3, M, N, slices, &best, M2, N2);
     // a taller tile only where the next lower one has more tiles than CUs: 160 tokens beside a round of 128 that fits, 3786 x 960 x
     // 3840 33.1 -> 37.1, 6340 x 576 x 2304 22.4 -> 24.6, 3806 x 960 x 960 12.4 -> 13.5
     const auto past = [&](int kernel) { return count_tiles(kernel, M, N) + count_tiles(kernel, M2, N2) > GEMM_CUS; };

@@ -114,6 +114,12 @@ def test_every_planned_projection_kernel_is_launched(plan):
     assert {q[5] for q in qkv if q[0] == 2} <= cases
 
 
+def test_tiles_of_96_tokens_leave_what_two_small_tiles_per_cu_do_faster(plan):
+    small, tall = [(3291, 576, 576), (3459, 576, 576), (5921, 288, 1152), (6080, 288, 1152)], [(3680, 576, 576), (6120, 288, 1152)]
+    assert [g[0] for g in plan("gemm", small + tall)] == [64] * 4 + [113] * 2
+    assert plan("pair", [(3419, 576, 16, 1152, 576)])[0][0] == 64
+
+
 def test_module_shapes_take_the_ways_they_are_chosen_for(plan):
     qkv = lambda shapes: plan("qkv", [(T * S, H, D, S, kind == 1) for kind, T, S, H, D in shapes])
     assert [q[0] for q in qkv([m + (72,) for m in G.MODULES])] == [1, 1, 1, 1, 0]
