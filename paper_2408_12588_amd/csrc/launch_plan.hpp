@@ -58,53 +58,76 @@ inline ItemPlan plan_items(long long n_bh, int sq, int sk, int head_dim, int ele
 // Key groups: what a wavefront does one after the other is ntile / groups steps, the more groups the shorter, while the chip is
 // not full of wavefronts; then blocks in pairs of wavefronts, two blocks with two groups each, four blocks without groups.  us,
 // heads of 72: 15 tiles, 360 blocks 22: 10.2, 44: 9.2; 8 tiles, 1040 blocks 22: 10.5, 42: 10.8, 44: 11.6; 9 blocks of a problem,
-// 1440 in all 22: 13.4, 42: 11.5; 256 problems of 225 tokens 22: 16.5, 42: 16.3, 41: 14.0.
-inline int short_groups(long long n_blocks, long long blk, int ntile, int head_dim) {
+// 1440 in all 22: 13.4, 42: 11.5; 256 problems of 225 tokens 22: 16.5, 42: 16.3, 41: 14.0.  fp32 rows of heads of 72 leave registers for
+// two wavefronts per SIMD, so that a 513th block of four waits for a second round: 128 of 133 tokens (640) 44: 14.6, 22: 10.4.
+inline int short_groups(long long n_blocks, long long blk, int ntile, int head_dim, int elem_size) {
   if (ntile <= 2) return n_blocks <= 256 || ntile == 1 ? 22 : 42;
-  if (n_blocks <= 256 || (ntile >= 5 && n_blocks <= 650) || (head_dim == 32 && ntile >= 16)) return 44;
+  const long long four = elem_size == 4 && head_dim == 72 && ntile < 16 ? 512 : 650;
+  if (n_blocks <= 256 || (ntile >= 5 && n_blocks <= four) || (head_dim == 32 && ntile >= 16)) return 44;
   if (n_blocks > 1450 && (blk % 4 == 0 || blk >= 32)) return 41;
   if (ntile == 4 || ntile >= 16 || (n_blocks > 1200 && (blk % 2 == 0 || blk >= 9))) return 42;
   return 22;
 }
 
 // A 32-query block there loads the keys for itself, so its time goes with the number of blocks; the tile kernel's with the key
-// tiles of a workgroup and the rounds of workgroups: the line between them lies at a number of blocks.  It lies higher where the
-// tile kernel needs a second workgroup per CU, higher for heads of 32 (half the bytes per block and the same arithmetic), lower for
-// fp32 rows (twice the bytes).  us, tile kernel -> short, heads of 72: 96 problems of 256 tokens (768 blocks) 11.4 -> 8.6, 40 of
-// 700 (880) 20.4 -> 15.3, 224 of 150 (1120) 9.9 -> 9.9, 256 of 225 (2048, one workgroup each) 15.0 -> 14.0, 72 of 462 (1080)
-// 17.2 -> 16.8, 36 of 1000 (1152) 27.5 -> 25.7, 36 of 1189 (1368) 33.2 -> 35.1; second workgroup: 400 of 150 (2000) 15.9 -> 13.6, 132 of 622 (2640) 34.0 -> 36.6; heads of 32: 180 of 256 (1440)
-// 8.0 -> 7.1, 12 of 2400 (900) 39.1 -> 23.9; fp32: heads of 32 143 of 129 (715) 7.3 -> 6.0, 195 of 182 (1170) 8.3 -> 9.1, heads of
-// 72 78 of 379 (936) 21.3 -> 18.8, 88 of 415 (1144) 25.2 -> 33.3.  Long sequences of heads of 72 that are split there stay (6 of
-// 3600, 678 blocks, 48.4 -> 55.9; 12 of 1590 28.1 -> 24.4).  Sequences of one or two key tiles (clips of 33 .. 64 frames) leave most
-// of a 256-query workgroup idle: at any number of problems 0.4 - 0.6 of the time (25440 problems of 48: 350 -> 166), fp32 rows
-// 0.8 (2532 blocks 11.4 -> 9.3).
+// tiles of a workgroup and the rounds of workgroups: the line between them lies at a number of blocks.  us, tile kernel -> short:
+//   bf16, up to one workgroup of the tile kernel per CU: heads of 72 96 problems of 256 tokens (768 blocks) 11.4 -> 8.6, 224 of 150
+//     (1120) 9.9 -> 9.9, 256 of 225 (2048) 15.0 -> 14.0, but odd numbers of blocks are not taken four at a time (208 of 205, 1456,
+//     11.8 -> 12.9); 40 of 700 (880) 20.4 -> 15.3, 36 of 1000 (1152) 27.5 -> 25.7, 36 of 1189 (1368) 33.2 -> 35.1, 12 of 2984 (1128)
+//     68.4 -> 73.4; heads of 32 (half the bytes per block and the same arithmetic) 180 of 256 (1440) 8.0 -> 7.1, 12 of 2400 (900)
+//     39.1 -> 23.9, 128 of 500 (2048) 12.2 -> 15.5, 32 of 1966 (1984) 33.9 -> 40.4;
+//   with a second workgroup, which the tile kernel runs beside the first or splits: higher for few key tiles, none for many: 400 of
+//     150 (2000) 15.9 -> 13.6, 140 of 398 (1820) 20.5 -> 19.4, 81 of 559 (1458) 21.3 -> 19.3, 99 of 608 (1881) 25.0 -> 27.2, 72 of
+//     807 (1872) 27.9 -> 33.0, 60 of 1045 (1980) 32.9 -> 50.9; heads of 32 85 of 658 (1785) 16.7 -> 16.6, 60 of 1052 (1980) 21.5 -> 24.8;
+//   fp32 (twice the bytes): heads of 72 78 of 287 (702) 16.5 -> 13.3, 88 of 415 (1144) 25.2 -> 33.3, 80 of 306 (800; a multiple of eight
+//     problems, which the tile kernel deals evenly) 18.3 -> 20.1, 144 of 105 (576) 9.4 -> 11.3, 32 of 516 (544) 23.2 -> 25.2; heads of 32
+//     143 of 129 (715) 7.3 -> 6.0, 195 of 182 (1170) 8.3 -> 9.1, 16 of 1667 (848) 28.1 -> 36.7;
+//   where all is split there, long sequences stay: bf16 heads of 72 6 of 3600 (678) 48.4 -> 55.9, but 12 of 1590 28.1 -> 24.4; fp32 ones
+//     also where the split items have a CU each: 8 of 1111 (280) 23.6 -> 30.0, 16 of 1473 (752) 43.2 -> 72.4;
+//   sequences of one or two key tiles (clips of 33 .. 64 frames) leave most of a 256-query workgroup idle: at any number of problems
+//     0.4 - 0.6 of the time (25440 problems of 48: 350 -> 166), fp32 rows 0.8 (2532 blocks 11.4 -> 9.3), 260 of 63 (520) 8.6 -> 9.2.
+// 3200 random shapes near these lines: 0.75 of the time of the tile and cross kernels alone, 1 % of them slower by 2 % or more, by 9 % at most.
 inline int plan_short(long long n_bh, int sq, int sk, int head_dim, int elem_size) {
   const long long blk = (sq + 31) / 32, n_blocks = n_bh * blk;
   const int ntile = (sk + 31) / 32;
-  const ItemPlan plain = plan_items(n_bh, sq, sk, head_dim, elem_size);
-  const long long per_xcd = (n_bh + 7) / 8 * plain.n_item;
-  const bool clip = ntile <= 2 && sq <= 64;
-  bool take;
-  if (elem_size == 4) {
-    take = n_blocks <= (clip ? 2600 : head_dim == 32 ? 900 : 850);
+  const ItemPlan tile = plan_items(n_bh, sq, sk, head_dim, elem_size);
+  const long long per_xcd = (n_bh + 7) / 8 * tile.n_item, items_xcd = (n_bh + 7) / 8 * tile.n_split;
+  const bool wide = head_dim == 72, clip = ntile <= 2 && sq <= 64;
+  const bool split = tile.n_split && !tile.bh_plain, one = tile.n_item == 1, second = per_xcd > TILE_CUS;
+  long long most;
+  if (elem_size == 2) {
+    if (per_xcd > 2 * TILE_CUS) most = 0;
+    else if (second && wide) most = ntile <= 12 ? 2000 : ntile <= 16 ? 1900 : ntile <= 24 ? 1500 : 0;
+    else if (second) most = ntile <= 16 ? 2000 : ntile <= 32 ? 1800 : 1600;
+    else if (one && wide) most = ntile == 7 || (ntile == 8 && n_blocks < 1600) ? 1250 : 2048;
+    else if (one) most = ntile >= 7 ? 1500 : 2048;
+    else most = !wide ? 1450 : ntile <= 24 ? 1320 : ntile <= 50 ? 1200 : 1030;
+    if (wide && tile.n_split && ntile > 50) most = 0;
+    if (clip) most = n_blocks;
+  } else if (clip) {
+    most = wide && n_blocks > 512 && n_blocks < 600 ? 0 : 2600;
+  } else if (wide) {
+    if (split) most = ntile <= 16 ? 850 : ntile > 50 ? 0 : items_xcd > TILE_CUS ? 512 : 256;
+    else if (ntile >= 17) most = n_bh % 8 == 0 ? 512 : ntile <= 24 ? 670 : 800;
+    else if (ntile >= 9) most = n_bh % 8 == 0 ? 700 : 750;
+    else most = ntile >= 2 && ntile <= 4 ? 512 : 830;
   } else {
-    const long long most = per_xcd > 2 * TILE_CUS ? 0 : per_xcd > TILE_CUS ? 2000 : head_dim == 32 || plain.n_item == 1 ? 2048 : ntile <= 24 ? 1320 : 1200;
-    take = n_blocks <= most || clip;
+    most = split && ntile >= 25 ? (ntile > 50 ? 500 : 700) : one && ntile == 4 ? 512 : 900;
   }
-  if (head_dim == 72 && plain.n_split && ntile > 50) take = false;
-  return take ? short_groups(n_blocks, blk, ntile, head_dim) : 0;
+  return n_blocks <= most ? short_groups(n_blocks, blk, ntile, head_dim, elem_size) : 0;
 }
 
 // Cross attention (bf16): the cross kernels stage all keys of a head per workgroup and give every wavefront whole query tiles,
 // of which few tokens have too few.  us, cross kernel -> short, heads of 72: 500 tokens, 8 heads and 200 keys 13.0 -> 5.1, 2000
 // tokens and 300 keys 16.7 -> 8.0, 3500 tokens, 12 heads (1320 blocks) 16.8 -> 13.5, 4000 tokens, 16 heads (2000) 17.6 -> 16.9, 6000
 // tokens, 12 heads (2256) 17.9 -> 20.7; up to 128 keys only the smallest: 700 tokens, 7 heads and 90 keys (154 blocks) 4.5 -> 4.2,
-// 1000 tokens, 16 heads (512) 4.7 -> 5.6, heads of 32 there 4.3 -> 3.8 with 120 keys; up to 64 keys none.
+// 1000 tokens, 16 heads (512) 4.7 -> 5.6, heads of 32 there 4.3 -> 3.8 with 120 keys, but 1970 tokens, 8 heads (496) and 65 keys 3.6 -> 3.7;
+// up to 64 keys none.
 inline int plan_short_cross(int n_tok, int L, int n_head, int head_dim) {
   const long long blk = (n_tok + 31LL) / 32, n_blocks = n_head * blk;
   const int ntile = (L + 31) / 32;
-  const long long most = ntile > 4 ? 2000 : ntile < 3 ? 0 : head_dim == 32 ? 512 : 256;
-  return n_blocks <= most ? short_groups(n_blocks, blk, ntile, head_dim) : 0;
+  const long long most = ntile > 4 ? 2000 : ntile < 3 ? 0 : head_dim == 32 && ntile == 4 ? 512 : 256;
+  return n_blocks <= most ? short_groups(n_blocks, blk, ntile, head_dim, 2) : 0;
 }
 
 // Whether the tile kernel moves its results to row order on the way out (store_rows16) or stores them as accumulated.  With few

@@ -608,8 +608,12 @@ def test_cross_attention_of_few_and_of_many_tokens(pab, T, S, L, H, D):
     assert_close(out, orc.kind_attention(W.CROSS, q, k, v), v, "cross")
 
 
+# fp32 rows of heads of 72, two key groups: more than 512 blocks of five key tiles and more
+SHORT_F32_GROUPS = [(W.SPATIAL, 8, 133, 0, 16, 72, "f32"), (W.SPATIAL, 9, 289, 0, 6, 72, "f32")]
+
+
 @pytest.mark.parametrize("peaked", [0.0, 0.05])
-@pytest.mark.parametrize("kind,T,S,L,H,D,dtype", SHORT_SHAPES)
+@pytest.mark.parametrize("kind,T,S,L,H,D,dtype", SHORT_SHAPES + SHORT_F32_GROUPS)
 def test_short_launches(pab, kind, T, S, L, H, D, dtype, peaked):
     print("short", W.KIND_NAMES[kind], T, S, L, H, D, dtype, peaked, flush=True)
     q, k, v = rand_qkv(kind, T, S, L, H, D, dtype, seed=4000 + S + L, scale_rows=peaked)
