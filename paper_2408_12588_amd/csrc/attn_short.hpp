@@ -66,8 +66,9 @@ __device__ __forceinline__ float max_quad16(float x) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// NW wavefronts: NW / G query tiles with G key groups each
-template <typename T, int D, int NW, int G>
+// NW wavefronts: NW / G query tiles with G key groups each.  ZERO: V rows past the last key are zeros, as in the cross kernels, whose
+// small launches these are; else copies of that key's row, as in the tile kernel
+template <typename T, int D, int NW, int G, bool ZERO>
 __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 2 : 4) void attn_short_kernel(const ShortParams p) {
   constexpr int CH = D / 8;                  // 8-element chunks of a row
   constexpr int QT = NW / G;                 // query tiles of a workgroup
@@ -219,9 +220,9 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 2 : 4) void attn_short_ke
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (t + G < ntile) request(kb, t + G, false);
     if (32 * t + 32 > sk) {
-      // rows past the last key are copies of it and weigh 0: zeros in V, or an infinity of that key would become NaN.  Two
-      // lanes per row, the chunk in the middle twice
-      if (32 * t + (lane >> 1) >= sk) {
+      // rows past the last key are copies of it and weigh 0: zeros, or an infinity of that key would become NaN.  Two lanes per
+      // row, the chunk in the middle twice.  0.1 us of a launch
+      if (ZERO && 32 * t + (lane >> 1) >= sk) {
 #pragma unroll
         for (int i = 0; i < (CH + 1) / 2; ++i) *reinterpret_cast<bf16x8 *>(vt + (lane >> 1) * RP + 8 * (i + (lane & 1) * (CH / 2))) = zero8();
       }

@@ -48,18 +48,18 @@ using pab::TILE_NWV;
 using pab::TILE_SPLIT_G;
 constexpr int TILE_MINW = 4;   // wavefronts per SIMD the register budget is sized for
 
-template <typename T, int D, int NW, int G>
+template <typename T, int D, int NW, int G, bool ZERO>
 void launch_short_groups(pab::ShortParams p, int n_bh, hipStream_t st) {
   p.n_blk = (p.sq + 32 * (NW / G) - 1) / (32 * (NW / G));
   p.n_work = n_bh * p.n_blk;
   p.blk_magic = (unsigned)(((1ULL << 32) + p.n_blk - 1) / p.n_blk);
   p.head_magic = (unsigned)(((1ULL << 32) + p.n_head - 1) / p.n_head);
-  hipLaunchKernelGGL((pab::attn_short_kernel<T, D, NW, G>), dim3((unsigned)((p.n_work + 7) / 8 * 8)), dim3(64 * NW), 0, st, p);
+  hipLaunchKernelGGL((pab::attn_short_kernel<T, D, NW, G, ZERO>), dim3((unsigned)((p.n_work + 7) / 8 * 8)), dim3(64 * NW), 0, st, p);
 }
 
-// Small launches: whether the short kernel took the call, planned by plan_short or plan_short_cross.  Its offsets inside a (batch, head) problem are 32-bit, and quotients
-// by high products are exact while dividend times divisor stays below 2^32.
-template <typename T, int D>
+// Small launches: whether the short kernel took the call, planned by plan_short or (ZERO) plan_short_cross.  Its offsets inside a
+// (batch, head) problem are 32-bit, and quotients by high products are exact while dividend times divisor stays below 2^32.
+template <typename T, int D, bool ZERO>
 bool launch_short(int plan, long long n_bh, int n_head, int sq, int sk, long long q_bs, long long q_ss, long long kv_bs, long long kv_ss,
                   const void *q, const void *k, const void *v, void *o, hipStream_t st) {
   const long long blk = (sq + 31) / 32;
@@ -72,10 +72,10 @@ bool launch_short(int plan, long long n_bh, int n_head, int sq, int sk, long lon
   p.q_bs = q_bs; p.kv_bs = kv_bs; p.q_ss = (int)q_ss; p.kv_ss = (int)kv_ss;
   p.c = (float)(1.4426950408889634 / std::sqrt((double)D));
   switch (plan) {
-    case 22: launch_short_groups<T, D, 2, 2>(p, (int)n_bh, st); break;
-    case 41: launch_short_groups<T, D, 4, 1>(p, (int)n_bh, st); break;
-    case 42: launch_short_groups<T, D, 4, 2>(p, (int)n_bh, st); break;
-    default: launch_short_groups<T, D, 4, 4>(p, (int)n_bh, st); break;
+    case 22: launch_short_groups<T, D, 2, 2, ZERO>(p, (int)n_bh, st); break;
+    case 41: launch_short_groups<T, D, 4, 1, ZERO>(p, (int)n_bh, st); break;
+    case 42: launch_short_groups<T, D, 4, 2, ZERO>(p, (int)n_bh, st); break;
+    default: launch_short_groups<T, D, 4, 4, ZERO>(p, (int)n_bh, st); break;
   }
   return true;
 }
@@ -93,7 +93,7 @@ int launch_tile(int n_batch, int n_head, int sq, int sk, long long q_bs, long lo
   if (32 * TILE_SPLIT_G * kv_ss * (long long)sizeof(T) >= (1LL << 32)) return fail(PAB_EINVAL, "sequence stride too large");
   const long long n_bh = (long long)n_batch * n_head;
   if (n_bh > 0x3fffffffLL) return fail(PAB_EINVAL, "problem too large for one launch");
-  if (launch_short<T, D>(pab::plan_short(n_bh, sq, sk, D, sizeof(T)), n_bh, n_head, sq, sk, q_bs, q_ss, kv_bs, kv_ss, q, k, v, o, st)) return PAB_OK;
+  if (launch_short<T, D, false>(pab::plan_short(n_bh, sq, sk, D, sizeof(T)), n_bh, n_head, sq, sk, q_bs, q_ss, kv_bs, kv_ss, q, k, v, o, st)) return PAB_OK;
   const pab::ItemPlan items = pab::plan_items(n_bh, sq, sk, D, sizeof(T));
   p.n_item = items.n_item;
   p.bh_plain = (int)items.bh_plain;
@@ -207,9 +207,11 @@ int launch_kind(int kind, int T_, int S, int L, int H, const void *q, const void
     default: {          // cross: every video token against the L text tokens
       const long long tok = (long long)T_ * S;
       if (tok > 0x7fffffffLL) return fail(PAB_EINVAL, "too many tokens");
-      if (sizeof(T) == 2 && L <= CROSSL_MAX_L &&
-          launch_short<T, D>(pab::plan_short_cross((int)tok, L, H, D), H, H, (int)tok, L, 0, row, 0, row, q, k, v, o, st))
-        return PAB_OK;
+      if constexpr (sizeof(T) == 2) {
+        if (L <= CROSSL_MAX_L &&
+            launch_short<T, D, true>(pab::plan_short_cross((int)tok, L, H, D), H, H, (int)tok, L, 0, row, 0, row, q, k, v, o, st))
+          return PAB_OK;
+      }
       if (sizeof(T) == 2 && L <= 128 && H <= 512) return launch_cross<D>((int)tok, L, H, q, k, v, o, st);
       if (sizeof(T) == 2 && L <= CROSSL_MAX_L && H <= 512) return launch_cross_long<D>((int)tok, L, H, q, k, v, o, st);
       return launch_tile<T, D>(1, H, (int)tok, L, 0, row, 0, row, q, k, v, o, st);

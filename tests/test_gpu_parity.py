@@ -647,6 +647,10 @@ SHORT_EXTREMES = [
 SHORT_CROSS_EXTREMES = [
     (44, W.CROSS, 1, 70, 97, 3, 72, "bf16"), (44, W.CROSS, 1, 70, 300, 3, 32, "bf16"),
 ]
+SHORT_CROSS_RAGGED = [
+    (22, W.CROSS, 3, 1000, 161, 8, 72, "bf16"), (42, W.CROSS, 2, 1550, 300, 13, 72, "bf16"), (41, W.CROSS, 2, 1550, 150, 16, 72, "bf16"),
+    (44, W.CROSS, 1, 33, 511, 1, 72, "bf16"), (0, W.CROSS, 3, 1371, 300, 16, 72, "bf16"), (0, W.CROSS, 3, 1371, 97, 16, 72, "bf16"),   # the last two: many tokens
+]
 
 
 @pytest.mark.parametrize("kind,T,S,L,H,D,dtype", [s[1:] for s in SHORT_EXTREMES + SHORT_CROSS_EXTREMES])
@@ -665,10 +669,10 @@ def test_short_launch_with_key_tiles_that_some_queries_do_not_see(pab, kind, T, 
         assert_close(out, orc.kind_attention(kind, q, k, v), v, "unseen keys")
 
 
-@pytest.mark.parametrize("kind,T,S,L,H,D,dtype", [s[1:] for s in SHORT_EXTREMES + SHORT_CROSS_EXTREMES])
+@pytest.mark.parametrize("kind,T,S,L,H,D,dtype", [s[1:] for s in SHORT_CROSS_EXTREMES + SHORT_CROSS_RAGGED])
 def test_short_launch_with_an_infinite_last_value(pab, kind, T, S, L, H, D, dtype):
-    """An infinity in the last key's values gives that infinity in its column, no NaN there and nothing elsewhere: the rows that fill the
-    last tile weigh 0, and 0 times a copy of that row would not be 0."""
+    """Cross attention of few tokens: an infinity in the last key's values gives that infinity in its column, no NaN there and nothing
+    elsewhere, as with many tokens: the rows that fill the last tile weigh 0, and 0 times a copy of that row would not be 0."""
     print("infinite value", W.KIND_NAMES[kind], T, S, L, H, D, dtype, flush=True)
     q, k, v = rand_qkv(kind, T, S, L, H, D, dtype, seed=4900 + S + L)
     want = orc.kind_attention(kind, q, k, v)

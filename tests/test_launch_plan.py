@@ -233,8 +233,8 @@ def test_cross_attention_of_few_tokens(plan):
 
 def test_extreme_inputs_of_the_short_kernel_take_every_way_of_it(plan):
     assert [r[0] for r in plan("short", [items_of(s[1:]) for s in P.SHORT_EXTREMES])] == [s[0] for s in P.SHORT_EXTREMES]
-    cross = [(T * S, L, H, D) for _, _, T, S, L, H, D, _ in P.SHORT_CROSS_EXTREMES]
-    assert [r[0] for r in plan("cross", cross)] == [s[0] for s in P.SHORT_CROSS_EXTREMES]
+    extremes = P.SHORT_CROSS_EXTREMES + P.SHORT_CROSS_RAGGED
+    assert [r[0] for r in plan("cross", [(T * S, L, H, D) for _, _, T, S, L, H, D, _ in extremes])] == [s[0] for s in extremes]
 
 
 def test_order_of_stores(plan):
