@@ -70,50 +70,49 @@ inline int short_groups(long long n_blocks, long long blk, int ntile, int head_d
 }
 
 // A 32-query block there loads the keys for itself, so its time goes with the number of blocks; the tile kernel's with the key
-// tiles of a workgroup and the rounds of workgroups: the line between them lies at a number of blocks.  us, tile kernel -> short:
-//   bf16, up to one workgroup of the tile kernel per CU: heads of 72 96 problems of 256 tokens (768 blocks) 11.4 -> 8.6, 224 of 150
-//     (1120) 9.9 -> 9.9, 256 of 225 (2048) 15.0 -> 14.0, but odd numbers of blocks are not taken four at a time (208 of 205, 1456,
-//     11.8 -> 12.9); 40 of 700 (880) 20.4 -> 15.3, 36 of 1000 (1152) 27.5 -> 25.7, 36 of 1189 (1368) 33.2 -> 35.1, 12 of 2984 (1128)
-//     68.4 -> 73.4; heads of 32 (half the bytes per block and the same arithmetic) 180 of 256 (1440) 8.0 -> 7.1, 12 of 2400 (900)
-//     39.1 -> 23.9, 128 of 500 (2048) 12.2 -> 15.5, 32 of 1966 (1984) 33.9 -> 40.4;
-//   with a second workgroup, which the tile kernel runs beside the first or splits: higher for few key tiles, none for many: 400 of
-//     150 (2000) 15.9 -> 13.6, 140 of 398 (1820) 20.5 -> 19.4, 81 of 559 (1458) 21.3 -> 19.3, 99 of 608 (1881) 25.0 -> 27.2, 72 of
-//     807 (1872) 27.9 -> 33.0, 60 of 1045 (1980) 32.9 -> 50.9; heads of 32 85 of 658 (1785) 16.7 -> 16.6, 60 of 1052 (1980) 21.5 -> 24.8;
-//   fp32 (twice the bytes): heads of 72 78 of 287 (702) 16.5 -> 13.3, 88 of 415 (1144) 25.2 -> 33.3, 80 of 306 (800; a multiple of eight
-//     problems, which the tile kernel deals evenly) 18.3 -> 20.1, 144 of 105 (576) 9.4 -> 11.3, 32 of 516 (544) 23.2 -> 25.2; heads of 32
-//     143 of 129 (715) 7.3 -> 6.0, 195 of 182 (1170) 8.3 -> 9.1, 16 of 1667 (848) 28.1 -> 36.7;
-//   where all is split there, long sequences stay: bf16 heads of 72 6 of 3600 (678) 48.4 -> 55.9, but 12 of 1590 28.1 -> 24.4; fp32 ones
-//     also where the split items have a CU each: 8 of 1111 (280) 23.6 -> 30.0, 16 of 1473 (752) 43.2 -> 72.4;
-//   sequences of one or two key tiles (clips of 33 .. 64 frames) leave most of a 256-query workgroup idle: at any number of problems
-//     0.4 - 0.6 of the time (25440 problems of 48: 350 -> 166), fp32 rows 0.8 (2532 blocks 11.4 -> 9.3), 260 of 63 (520) 8.6 -> 9.2.
-// 3200 random shapes near these lines: 0.75 of the time of the tile and cross kernels alone, 1 % of them slower by 2 % or more, by 9 % at most.
-inline int plan_short(long long n_bh, int sq, int sk, int head_dim, int elem_size) {
+// tiles of a workgroup, the rounds of workgroups on the fullest XCD and, where problems are split, the split items.  The line is a
+// number of blocks, lower for what the tile kernel does well.  us, tile kernel -> short:
+//   bf16, heads of 72: 96 problems of 256 tokens (768 blocks) 11.4 -> 8.6, 40 of 700 (880) 20.4 -> 15.3, 224 of 150 (1120) 9.9 -> 9.9,
+//     256 of 225 (2048) 15.0 -> 14.0, 36 of 1000 (1152) 27.5 -> 25.7, 36 of 1189 (1368) 33.2 -> 35.1, 12 of 2984 (1128) 68.4 -> 73.4;
+//     seven blocks do not come in fours (208 of 205, 1456, 11.8 -> 12.9); a second workgroup per CU 400 of 150 (2000) 15.9 -> 13.6,
+//     132 of 622 (2640) 34.0 -> 36.6; problems past a whole number of workgroups per CU, which are split there: 81 of 559 (1458)
+//     21.3 -> 19.3, 99 of 608 (1881) 25.0 -> 27.2, 72 of 807 (1872) 27.9 -> 33.0, 60 of 1045 (1980) 32.9 -> 50.9; all split, long: 6 of
+//     3600 (678) 48.4 -> 55.9, but 12 of 1590 28.1 -> 24.4.  Few problems leave XCDs idle there: 1 of 10401 (326) 342 -> 78, 4 of
+//     9867 (1236) 331 -> 191.
+//   Heads of 32, half the bytes per block and the same arithmetic: 180 of 256 (1440) 8.0 -> 7.1, 12 of 2400 (900) 39.1 -> 23.9, 9 of
+//     5850 (1647) 127 -> 81; where the XCDs have about as many problems each (on average eight tenths of the most) 128 of
+//     500 (2048) 12.2 -> 15.5, 32 of 1966 (1984) 33.9 -> 40.4, 60 of 1052 (1980) 21.5 -> 24.8.
+//   fp32 rows, twice the bytes: heads of 32 143 of 129 (715) 7.3 -> 6.0, 195 of 182 (1170) 8.3 -> 9.1, 223 of 127 (892) 6.0 -> 6.4, 16 of
+//     1667 (848) 28.1 -> 36.7; heads of 72 78 of 287 (702) 16.5 -> 13.3, 88 of 415 (1144) 25.2 -> 33.3, 144 of 105 (576) 9.4 -> 11.3;
+//     from nine tiles by the pitch of the rows, which are read four times as often as there: whole cache lines apart (every fourth head
+//     count) they fall on the same channels: 24 of 550, H = 6 17.5 -> 14.2, H = 8 1.00 - 1.02, 12 of 880, H = 6 0.84, H = 4 1.19, 16 of
+//     1473, H = 16 43.2 -> 72.4, 80 of 306, H = 16 18.3 -> 20.1.
+//   Sequences of one or two key tiles (clips of 33 .. 64 frames) leave most of a 256-query workgroup idle: at any number of problems
+//     0.4 - 0.6 of the time (25440 problems of 48: 350 -> 166), fp32 rows 0.8 (2532 blocks 11.4 -> 9.3).
+// 2600 random shapes below 2000 blocks: 0.76 of the tile kernel's time; 0.8 % of them slower by 3 % or more (at most 10 %).
+inline int plan_short(long long n_bh, int sq, int sk, int head_dim, int elem_size, long long kv_pitch_bytes = 0) {
   const long long blk = (sq + 31) / 32, n_blocks = n_bh * blk;
   const int ntile = (sk + 31) / 32;
   const ItemPlan tile = plan_items(n_bh, sq, sk, head_dim, elem_size);
-  const long long per_xcd = (n_bh + 7) / 8 * tile.n_item, items_xcd = (n_bh + 7) / 8 * tile.n_split;
-  const bool wide = head_dim == 72, clip = ntile <= 2 && sq <= 64;
-  const bool split = tile.n_split && !tile.bh_plain, one = tile.n_item == 1, second = per_xcd > TILE_CUS;
+  const long long xcd_bh = (n_bh + 7) / 8, per_xcd = xcd_bh * tile.n_item;
+  const bool wide = head_dim == 72, clip = ntile <= 2 && sq <= 64, one = tile.n_item == 1;
+  const bool all_split = tile.n_split && !tile.bh_plain, part_split = tile.n_split && tile.bh_plain;
   long long most;
+  const auto at_most = [&](bool where, long long n) { if (where) most = std::min(most, n); };
   if (elem_size == 2) {
-    if (per_xcd > 2 * TILE_CUS) most = 0;
-    else if (second && wide) most = ntile <= 12 ? 2000 : ntile <= 16 ? 1900 : ntile <= 24 ? 1500 : 0;
-    else if (second) most = ntile <= 16 ? 2000 : ntile <= 32 ? 1800 : 1600;
-    else if (one && wide) most = ntile == 7 || (ntile == 8 && n_blocks < 1600) ? 1250 : 2048;
-    else if (one) most = ntile >= 7 ? 1500 : 2048;
-    else most = !wide ? 1450 : ntile <= 24 ? 1320 : ntile <= 50 ? 1200 : 1030;
-    if (wide && tile.n_split && ntile > 50) most = 0;
-    if (clip) most = n_blocks;
-  } else if (clip) {
-    most = wide && n_blocks > 512 && n_blocks < 600 ? 0 : 2600;
-  } else if (wide) {
-    if (split) most = ntile <= 16 ? 850 : ntile > 50 ? 0 : items_xcd > TILE_CUS ? 512 : 256;
-    else if (ntile >= 17) most = n_bh % 8 == 0 ? 512 : ntile <= 24 ? 670 : 800;
-    else if (ntile >= 9) most = n_bh % 8 == 0 ? 700 : 750;
-    else most = ntile >= 2 && ntile <= 4 ? 512 : 830;
+    most = clip ? n_blocks : per_xcd > 2 * TILE_CUS ? 0 : per_xcd > TILE_CUS ? 2000 : !wide || one ? 2048 : ntile <= 24 ? 1320 : ntile <= 80 ? 1200 : 1080;
+    at_most(wide && one && ntile == 7 && per_xcd <= TILE_CUS, 1300);
+    at_most(wide && part_split && ntile >= 13, ntile <= 16 ? 1900 : 1500);
+    at_most(!wide && ntile >= 7 && 10 * n_bh >= 64 * xcd_bh && (per_xcd <= TILE_CUS || (part_split && ntile > 16)), 1550);
   } else {
-    most = split && ntile >= 25 ? (ntile > 50 ? 500 : 700) : one && ntile == 4 ? 512 : 900;
+    const bool lines = kv_pitch_bytes % 128 == 0 && n_bh > 4;
+    most = clip ? 2600 : wide ? 850 : 900;
+    at_most(one && !clip && (ntile == 4 || (wide && ntile == 3)), 512);
+    at_most(wide && lines && ntile >= 9, ntile <= 16 ? 780 : all_split ? 256 : 512);
+    at_most(wide && n_bh > 4 && all_split && xcd_bh * tile.n_split > TILE_CUS, 512);
+    at_most(!wide && all_split && ntile >= 25, ntile <= 50 ? 700 : 500);
   }
+  at_most(wide && tile.n_split && ntile > 50, 0);
   return n_blocks <= most ? short_groups(n_blocks, blk, ntile, head_dim, elem_size) : 0;
 }
 

@@ -93,7 +93,8 @@ int launch_tile(int n_batch, int n_head, int sq, int sk, long long q_bs, long lo
   if (32 * TILE_SPLIT_G * kv_ss * (long long)sizeof(T) >= (1LL << 32)) return fail(PAB_EINVAL, "sequence stride too large");
   const long long n_bh = (long long)n_batch * n_head;
   if (n_bh > 0x3fffffffLL) return fail(PAB_EINVAL, "problem too large for one launch");
-  if (launch_short<T, D, false>(pab::plan_short(n_bh, sq, sk, D, sizeof(T)), n_bh, n_head, sq, sk, q_bs, q_ss, kv_bs, kv_ss, q, k, v, o, st)) return PAB_OK;
+  const int short_plan = pab::plan_short(n_bh, sq, sk, D, sizeof(T), kv_ss * (long long)sizeof(T));
+  if (launch_short<T, D, false>(short_plan, n_bh, n_head, sq, sk, q_bs, q_ss, kv_bs, kv_ss, q, k, v, o, st)) return PAB_OK;
   const pab::ItemPlan items = pab::plan_items(n_bh, sq, sk, D, sizeof(T));
   p.n_item = items.n_item;
   p.bh_plain = (int)items.bh_plain;

@@ -41,6 +41,10 @@ int main() {
       long long n_bh; int sq, sk, D, size;
       if (scanf("%lld %d %d %d %d", &n_bh, &sq, &sk, &D, &size) != 5) return 1;
       printf("%d\n", pab::plan_short(n_bh, sq, sk, D, size));
+    } else if (!strcmp(what, "pitched")) {
+      long long n_bh, pitch; int sq, sk, D, size;
+      if (scanf("%lld %d %d %d %d %lld", &n_bh, &sq, &sk, &D, &size, &pitch) != 6) return 1;
+      printf("%d\n", pab::plan_short(n_bh, sq, sk, D, size, pitch));
     } else if (!strcmp(what, "cross")) {
       int n, L, H, D;
       if (scanf("%d %d %d %d", &n, &L, &H, &D) != 4) return 1;
@@ -211,14 +215,18 @@ def test_long_sequences_stay_with_the_tile_kernel_where_it_is_faster(plan):
     """Problems, queries, keys, head dim, bytes per element that the short kernel makes slower (figures at the rule), and neighbours that it
     makes faster."""
     tile = [(60, 1045, 1045, 72, 2), (50, 1164, 1164, 72, 2), (72, 807, 807, 72, 2), (99, 608, 608, 72, 2), (208, 205, 205, 72, 2), (12, 2984, 2984, 72, 2),
-            (18, 1902, 1902, 72, 2), (128, 500, 500, 32, 2), (32, 1966, 1966, 32, 2), (60, 1052, 1052, 32, 2), (16, 1473, 1473, 72, 4), (20, 1180, 1180, 72, 4),
-            (8, 1401, 1401, 72, 4), (8, 1111, 1111, 72, 4), (80, 306, 306, 72, 4), (144, 105, 105, 72, 4), (32, 516, 516, 72, 4), (4, 5391, 533, 72, 4),
-            (8, 2504, 55, 72, 4), (16, 1667, 1667, 32, 4), (223, 127, 127, 32, 4)]
-    short = [(81, 559, 559, 72, 2), (140, 398, 398, 72, 2), (176, 205, 205, 72, 2), (238, 240, 240, 72, 2), (20, 1523, 1523, 72, 2), (85, 658, 658, 32, 2),
-             (18, 2711, 2711, 32, 2), (11, 1118, 1118, 72, 4), (10, 1467, 1467, 72, 4), (6, 910, 910, 72, 4), (78, 287, 287, 72, 4), (126, 107, 107, 72, 4),
-             (30, 597, 597, 72, 4), (128, 133, 133, 72, 4), (22, 968, 968, 32, 4)]
+            (128, 500, 500, 32, 2), (32, 1966, 1966, 32, 2), (60, 1052, 1052, 32, 2), (16, 1473, 1473, 72, 4), (20, 1180, 1180, 72, 4),
+            (8, 1401, 1401, 72, 4), (8, 1111, 1111, 72, 4), (80, 306, 306, 72, 4), (144, 105, 105, 72, 4), (32, 516, 516, 72, 4), (16, 1667, 1667, 32, 4),
+            (223, 127, 127, 32, 4)]
+    short = [(1, 10401, 10401, 72, 2), (4, 9867, 9867, 72, 2), (81, 559, 559, 72, 2), (140, 398, 398, 72, 2), (176, 205, 205, 72, 2), (238, 240, 240, 72, 2),
+             (20, 1523, 1523, 72, 2), (12, 5109, 521, 72, 2), (84, 551, 551, 32, 2), (18, 2711, 2711, 32, 2), (9, 5850, 5850, 32, 2), (6, 910, 910, 72, 4),
+             (78, 287, 287, 72, 4), (126, 107, 107, 72, 4), (128, 133, 133, 72, 4), (3, 8976, 91, 72, 4), (22, 968, 968, 32, 4)]
     assert [r[0] for r in plan("short", tile)] == [0] * len(tile)
     assert all(r[0] for r in plan("short", short))
+    # long sequences of fp32 rows of 72: also by the heads, four of which are a whole number of cache lines
+    by_heads = lambda H: [r[0] > 0 for r in plan("pitched", [(24, 551, 551, 72, 4, 288 * H), (20, 560, 560, 72, 4, 288 * H), (32, 657, 657, 72, 4, 288 * H),
+                                                             (16, 680, 680, 72, 4, 288 * H)])]
+    assert by_heads(6) == by_heads(1) == [True] * 4 and by_heads(8) == by_heads(16) == [False] * 4
     assert [r[0] for r in plan("short", [items_of(s) for s in P.SHORT_F32_GROUPS])] == [22] * len(P.SHORT_F32_GROUPS)
     assert [r[0] for r in plan("cross", [(1970, 65, 8, 32), (504, 65, 8, 32)])] == [0, 44]
 
