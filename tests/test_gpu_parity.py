@@ -38,14 +38,15 @@ def assert_close(got: torch.Tensor, want: np.ndarray, v: torch.Tensor, what=""):
 
 
 SHAPES = [
-    # kind, T, S, L, H, D, dtype
-    (W.SPATIAL, 2, 300, 0, 2, 72, "bf16"),     # 2 query blocks (256 + 44), 5 key blocks, ragged tail
-    (W.SPATIAL, 1, 64, 0, 1, 72, "bf16"),      # exactly one key block
-    (W.SPATIAL, 1, 65, 0, 3, 72, "bf16"),      # one key past a block edge
-    (W.SPATIAL, 3, 513, 0, 3, 72, "bf16"),     # more (batch, head) pairs than one per XCD round
+    # kind, T, S, L, H, D, dtype.  Small launches take the short kernel; the edges of the tile and cross kernels are in TILE_SHAPES and
+    # LONG_CROSS as well
+    (W.SPATIAL, 2, 300, 0, 2, 72, "bf16"),     # ragged last query and key tile
+    (W.SPATIAL, 1, 64, 0, 1, 72, "bf16"),      # whole tiles
+    (W.SPATIAL, 1, 65, 0, 3, 72, "bf16"),      # one key past a tile edge
+    (W.SPATIAL, 3, 513, 0, 3, 72, "bf16"),     # more (batch, head) pairs than XCDs
     (W.SPATIAL, 1, 1, 0, 1, 72, "bf16"),       # single token
-    (W.SPATIAL, 1, 256, 0, 2, 72, "bf16"),     # one full query block, eight whole key tiles: steady loop, no ragged tile
-    (W.SPATIAL, 1, 257, 0, 2, 32, "bf16"),     # one query and one key past the block: a workgroup with a single live row
+    (W.SPATIAL, 1, 256, 0, 2, 72, "bf16"),     # eight whole tiles
+    (W.SPATIAL, 1, 257, 0, 2, 32, "bf16"),     # one query and one key past them
     (W.SPATIAL, 2, 200, 0, 2, 32, "bf16"),
     (W.SPATIAL, 2, 130, 0, 2, 72, "f32"),
     (W.SPATIAL, 4, 64, 0, 4, 32, "f32"),       # the Tiny configuration's spatial call
@@ -59,7 +60,7 @@ SHAPES = [
     (W.TEMPORAL, 32, 11, 0, 2, 72, "bf16"),    # full 32x32 tile
     (W.TEMPORAL, 24, 13, 0, 2, 72, "bf16"),    # last clip length of the 24-row staging variant
     (W.TEMPORAL, 25, 13, 0, 2, 72, "f32"),     # first of the 32-row variant
-    (W.TEMPORAL, 33, 7, 0, 2, 72, "bf16"),     # beyond the wavefront-resident kernel: tiled fallback
+    (W.TEMPORAL, 33, 7, 0, 2, 72, "bf16"),     # beyond the wavefront-resident kernel: strides exchanged
     (W.TEMPORAL, 5, 300, 0, 16, 72, "f32"),
     (W.TEMPORAL, 16, 33, 0, 2, 32, "bf16"),
     (W.CROSS, 2, 300, 120, 2, 72, "bf16"),
@@ -67,20 +68,20 @@ SHAPES = [
     (W.CROSS, 1, 70, 1, 2, 72, "bf16"),        # one text key: output = its value
     (W.CROSS, 4, 64, 16, 4, 32, "f32"),        # Tiny
     (W.CROSS, 2, 129, 64, 1, 72, "f32"),
-    (W.CROSS, 5, 101, 128, 3, 72, "bf16"),     # exactly four key tiles, ragged token tail, odd head count
+    (W.CROSS, 5, 101, 128, 3, 72, "bf16"),     # exactly four key tiles, ragged token tail, odd head count (short kernel)
     (W.CROSS, 1, 31, 33, 16, 72, "bf16"),      # fewer tokens than one tile, one key past a tile edge
     (W.CROSS, 7, 333, 97, 8, 72, "bf16"),      # many tiles per wavefront, heads spread over the XCDs
     (W.CROSS, 3, 200, 60, 2, 32, "bf16"),
-    (W.CROSS, 2, 150, 129, 2, 72, "bf16"),     # one key too many for the single-pass kernel: online softmax, K/V in LDS
+    (W.CROSS, 2, 150, 129, 2, 72, "bf16"),     # one key past four tiles (short kernel, as all of these up to 512 keys)
     (W.CROSS, 17, 90, 300, 16, 72, "bf16"),    # config 4's text length: ten key tiles, the last ragged
-    (W.CROSS, 3, 77, 192, 3, 72, "bf16"),      # fills the 6-tile LDS variant exactly
-    (W.CROSS, 2, 100, 193, 2, 72, "bf16"),     # first length of the 8-tile variant
-    (W.CROSS, 2, 61, 257, 5, 32, "bf16"),      # 10-tile variant, head dim 32
-    (W.CROSS, 1, 45, 320, 2, 72, "bf16"),      # fills the 10-tile variant
-    (W.CROSS, 2, 150, 321, 2, 72, "bf16"),     # 16-tile variant, 11 tiles in use
-    (W.CROSS, 1, 40, 512, 2, 72, "bf16"),      # longest text the LDS-resident kernel takes
-    (W.CROSS, 1, 40, 513, 2, 72, "bf16"),      # beyond it: streaming tile kernel
-    (W.CROSS, 2, 64, 200, 2, 72, "f32"),       # fp32 rows: streaming tile kernel
+    (W.CROSS, 3, 77, 192, 3, 72, "bf16"),      # six whole key tiles
+    (W.CROSS, 2, 100, 193, 2, 72, "bf16"),     # one key past them
+    (W.CROSS, 2, 61, 257, 5, 32, "bf16"),      # nine tiles, head dim 32
+    (W.CROSS, 1, 45, 320, 2, 72, "bf16"),      # ten whole key tiles
+    (W.CROSS, 2, 150, 321, 2, 72, "bf16"),     # one key past them
+    (W.CROSS, 1, 40, 512, 2, 72, "bf16"),      # sixteen whole key tiles
+    (W.CROSS, 1, 40, 513, 2, 72, "bf16"),      # one key past them
+    (W.CROSS, 2, 64, 200, 2, 72, "f32"),       # fp32 rows
 ]
 
 
@@ -467,9 +468,9 @@ def test_video_with_window_from_preset_and_timesteps(pab):
 
 
 def test_long_spatial_and_long_text_shapes(pab):
-    """Seeded shapes where the steady loops of the tiled kernels run many times: spatial attention with up to
-    2600 tokens (both dtypes, both head dims, 5% of the query rows scaled x8 in some of the bf16 cases), and cross
-    attention over 129..512 text tokens, each compared in full with the oracle."""
+    """Seeded shapes with long key loops: spatial attention of one or two heads with up to 2600 tokens (both dtypes, both head dims,
+    5% of the query rows scaled x8 in some of the bf16 cases), the longest with heads of 72 as split items of the tile kernel and the others on
+    the short one, and cross attention of few tokens over 129..512 text tokens, each compared in full with the oracle."""
     rng = np.random.default_rng(20241128)
     worst = 0.0
     cases = []
@@ -489,8 +490,8 @@ def test_long_spatial_and_long_text_shapes(pab):
 
 
 def test_seeded_random_shapes(pab):
-    """Sixty seeded shapes across kinds, dtypes, head dims and all kernel variants (tile, temporal 16/24/32-row and
-    tiled fallback, cross single-pass / LDS-resident online / tiled), each compared in full with the oracle."""
+    """Sixty seeded shapes across kinds, dtypes and head dims, launches of up to a few hundred query blocks (the short kernel, temporal
+    16/24/32-row, cross single-pass), each compared in full with the oracle."""
     rng = np.random.default_rng(20241127)
     worst = 0.0
     for case in range(60):
@@ -514,17 +515,17 @@ def test_seeded_random_shapes(pab):
 
 
 SPLIT_SHAPES = [
-    # kind, T, S, L, H, D, dtype: launches that run as split items, in whole or in part
-    (W.SPATIAL, 1, 225, 0, 3, 72, "bf16"),     # all split: eight key tiles, the fewest, the last with one key; 33 queries in the last item
-    (W.SPATIAL, 1, 289, 0, 1, 32, "bf16"),     # ... ten key tiles: groups with two and with three
-    (W.SPATIAL, 5, 252, 0, 8, 72, "bf16"),     # ... several problems per XCD
-    (W.SPATIAL, 2, 1000, 0, 16, 72, "bf16"),   # ... two items per CU
-    (W.SPATIAL, 3, 257, 0, 3, 72, "f32"),      # ... fp32 rows
+    # kind, T, S, L, H, D, dtype: launches of the tile kernel that run as split items, in whole or in part
+    (W.SPATIAL, 1, 1633, 0, 3, 72, "bf16"),    # all split: 52 key tiles, the last with one key; 33 queries in the last item
+    (W.SPATIAL, 2, 1100, 0, 8, 72, "f32"),     # ... fp32 rows; 35 key tiles: groups with eight and with nine
+    (W.SPATIAL, 1, 1667, 0, 16, 32, "f32"),    # ... heads of 32
+    (W.TEMPORAL, 1633, 2, 0, 2, 72, "bf16"),   # ... long clip, strides exchanged
+    (W.CROSS, 2, 500, 600, 16, 72, "f32"),     # ... cross attention: 1000 queries, 600 keys
+    (W.CROSS, 1, 1500, 1650, 6, 72, "bf16"),   # ... long text
     (W.SPATIAL, 7, 700, 0, 12, 72, "bf16"),    # 84 problems, three items each: the last four split
     (W.SPATIAL, 9, 513, 0, 11, 32, "f32"),     # 99 problems: the last 19 split, fp32 rows
-    (W.TEMPORAL, 230, 3, 0, 2, 72, "bf16"),    # long clip, strides exchanged
-    (W.CROSS, 3, 200, 300, 4, 72, "f32"),      # cross attention on the tile kernel: 600 queries, 300 keys
-    (W.CROSS, 1, 90, 530, 2, 72, "bf16"),
+    (W.SPATIAL, 5, 1124, 0, 12, 32, "bf16"),   # 60 problems of heads of 32: the last twelve split
+    (W.SPATIAL, 4, 2866, 0, 6, 32, "bf16"),    # ... 24: the last eight
 ]
 
 
@@ -543,17 +544,26 @@ def test_split_items(pab, kind, T, S, L, H, D, dtype, peaked):
 
 
 FEW_QUERIES = [
-    # kind, T, S, L, H: up to 48 queries of a problem are stored as accumulated, in smaller launches also up to 64, and up to 128
-    # where rows (of 72-element heads) are off 64-byte boundaries; more in row order
+    # kind, T, S, L, H, D, dtype, in row order: problems of few queries on the tile kernel.  Up to 48 queries are stored as accumulated, in
+    # smaller launches also up to 64, and up to 128 where rows are off 64-byte boundaries; more in row order
+    (W.TEMPORAL, 40, 700, 0, 3, 72, "f32", False), (W.TEMPORAL, 40, 700, 0, 3, 32, "f32", False), (W.TEMPORAL, 34, 440, 0, 3, 72, "f32", False),
+    (W.TEMPORAL, 34, 440, 0, 3, 32, "f32", False), (W.TEMPORAL, 49, 700, 0, 3, 72, "f32", True), (W.TEMPORAL, 49, 700, 0, 3, 32, "f32", True),
+    (W.TEMPORAL, 70, 111, 0, 5, 72, "f32", False), (W.TEMPORAL, 70, 100, 0, 6, 72, "f32", True), (W.TEMPORAL, 70, 130, 0, 6, 32, "f32", True),
+    (W.TEMPORAL, 70, 171, 0, 3, 72, "bf16", False), (W.TEMPORAL, 90, 90, 0, 8, 72, "bf16", True), (W.TEMPORAL, 70, 130, 0, 6, 32, "bf16", True),
+    (W.CROSS, 1, 40, 530, 1600, 32, "bf16", False), (W.SPATIAL, 16, 400, 0, 16, 32, "bf16", True),
+]
+SHORT_FEW_QUERIES = [
+    # kind, T, S, L, H: such problems in launches that the short kernel takes, whatever head dim and type
     (W.SPATIAL, 3, 48, 0, 5), (W.SPATIAL, 2, 49, 0, 3), (W.SPATIAL, 4, 33, 0, 2), (W.SPATIAL, 2, 1, 0, 3),
     (W.TEMPORAL, 33, 9, 0, 3), (W.TEMPORAL, 48, 7, 0, 2), (W.TEMPORAL, 49, 7, 0, 2),
     (W.CROSS, 2, 20, 530, 3), (W.SPATIAL, 2, 64, 0, 4), (W.SPATIAL, 2, 65, 0, 4), (W.SPATIAL, 2, 65, 0, 5),
-    (W.SPATIAL, 1, 128, 0, 5), (W.SPATIAL, 1, 129, 0, 5), (W.TEMPORAL, 49, 700, 0, 3),
+    (W.SPATIAL, 1, 128, 0, 5), (W.SPATIAL, 1, 129, 0, 5),
 ]
+SHORT_FEW_QUERIES = [s + t for s in SHORT_FEW_QUERIES for t in ((72, "bf16"), (32, "bf16"), (72, "f32"), (32, "f32"))] + [
+    (W.TEMPORAL, 49, 700, 0, 3, 72, "bf16"), (W.TEMPORAL, 49, 700, 0, 3, 32, "bf16")]
 
 
-@pytest.mark.parametrize("D,dtype", [(72, "bf16"), (32, "bf16"), (72, "f32"), (32, "f32")])
-@pytest.mark.parametrize("kind,T,S,L,H", FEW_QUERIES)
+@pytest.mark.parametrize("kind,T,S,L,H,D,dtype", [s[:7] for s in FEW_QUERIES] + SHORT_FEW_QUERIES)
 def test_few_queries(pab, kind, T, S, L, H, D, dtype):
     print("few queries", W.KIND_NAMES[kind], T, S, L, H, D, dtype, flush=True)
     q, k, v = rand_qkv(kind, T, S, L, H, D, dtype, seed=3000 + T + S)
@@ -589,13 +599,21 @@ SHORT_SHAPES = [
     (W.SPATIAL, 23, 100, 0, 16, 72, "bf16"),   # 41: no groups, four blocks
 ]
 
+# ... and the smallest splits: eight key tiles and more, several problems per XCD, exchanged strides, cross attention on few tokens
+SHORT_SPLITS = [
+    (W.SPATIAL, 1, 225, 0, 3, 72, "bf16"), (W.SPATIAL, 1, 289, 0, 1, 32, "bf16"), (W.SPATIAL, 2, 1000, 0, 16, 72, "bf16"), (W.SPATIAL, 3, 257, 0, 3, 72, "f32"),
+    (W.TEMPORAL, 230, 3, 0, 2, 72, "bf16"), (W.CROSS, 3, 200, 300, 4, 72, "f32"), (W.CROSS, 1, 90, 530, 2, 72, "bf16"),
+]
+
 SHORT_CROSS = [
     # few tokens against the keys that the cross kernels would hold: plan, T, S, L, H, D
     (44, 1, 45, 129, 2, 72), (44, 2, 333, 300, 7, 72), (44, 1, 100, 512, 3, 72), (44, 1, 70, 65, 3, 72), (44, 1, 1, 97, 1, 72),
     (44, 2, 200, 128, 4, 32), (44, 1, 300, 500, 5, 32), (22, 3, 1000, 161, 8, 72), (42, 3, 1000, 128, 5, 32), (42, 2, 1550, 300, 13, 72),
     (41, 2, 1550, 150, 16, 72), (41, 3, 1300, 330, 12, 32),
 ]
-LONG_CROSS = [(3, 1371, L, 16, D) for L in (129, 224, 290, 512) for D in (72, 32)]   # ... and enough tokens for the cross kernel
+# ... and enough tokens for the cross kernels: keys that fill their LDS variants (four tiles in one pass; six, eight, ten and sixteen) and one more
+LONG_CROSS = [(3, 1371, L, 16, D) for L in (129, 224, 290, 512) for D in (72, 32)] + [
+    (3, 1371, L, 16, 72) for L in (96, 97, 128, 192, 193, 256, 257, 320, 321)] + [(3, 1371, L, 16, 32) for L in (97, 128, 320)]
 
 
 @pytest.mark.parametrize("T,S,L,H,D", [s[1:] for s in SHORT_CROSS] + LONG_CROSS)
@@ -613,7 +631,7 @@ SHORT_F32_GROUPS = [(W.SPATIAL, 8, 133, 0, 16, 72, "f32"), (W.SPATIAL, 9, 289, 0
 
 
 @pytest.mark.parametrize("peaked", [0.0, 0.05])
-@pytest.mark.parametrize("kind,T,S,L,H,D,dtype", SHORT_SHAPES + SHORT_F32_GROUPS)
+@pytest.mark.parametrize("kind,T,S,L,H,D,dtype", SHORT_SHAPES + SHORT_SPLITS + SHORT_F32_GROUPS)
 def test_short_launches(pab, kind, T, S, L, H, D, dtype, peaked):
     print("short", W.KIND_NAMES[kind], T, S, L, H, D, dtype, peaked, flush=True)
     q, k, v = rand_qkv(kind, T, S, L, H, D, dtype, seed=4000 + S + L, scale_rows=peaked)
@@ -686,13 +704,18 @@ def test_short_launch_with_an_infinite_last_value(pab, kind, T, S, L, H, D, dtyp
 
 
 TILE_SHAPES = [
-    # kind, T, S, L, H, D, dtype: what the tile kernel keeps of the split items and of the stores as accumulated
-    (W.SPATIAL, 1, 1633, 0, 3, 72, "bf16"),    # all split: 52 key tiles, the last with one key; 33 queries in the last item
+    # kind, T, S, L, H, D, dtype: what else the tile kernel takes beside the short one
     (W.SPATIAL, 9, 1024, 0, 8, 72, "bf16"),    # 72 problems: the last eight split
     (W.SPATIAL, 1, 1650, 0, 3, 72, "f32"),
-    (W.TEMPORAL, 34, 440, 0, 3, 72, "f32"),    # stored as accumulated
-    (W.TEMPORAL, 34, 440, 0, 3, 32, "f32"),
-    (W.TEMPORAL, 70, 171, 0, 3, 72, "bf16"),
+    (W.SPATIAL, 17, 300, 0, 20, 32, "bf16"),   # heads of 32, none split: ragged last key tile, 44 queries in the last item
+    (W.SPATIAL, 16, 256, 0, 33, 72, "bf16"),   # one full query block, eight whole key tiles: steady loop, no ragged tile
+    (W.SPATIAL, 16, 257, 0, 33, 72, "bf16"),   # one query and one key past them
+    (W.SPATIAL, 16, 257, 0, 33, 32, "bf16"),
+    (W.SPATIAL, 16, 65, 0, 33, 72, "bf16"),    # three key tiles: fewer than are requested ahead
+    (W.SPATIAL, 16, 256, 0, 33, 32, "f32"),
+    (W.SPATIAL, 16, 257, 0, 17, 72, "f32"),
+    (W.CROSS, 3, 1371, 530, 16, 32, "bf16"),   # ... long text and many tokens
+    (W.CROSS, 3, 1371, 600, 16, 72, "bf16"),
 ]
 
 

@@ -80,7 +80,7 @@ def plan(tmp_path_factory):
 
 
 def items_of(shape):
-    """(problems, queries, keys, head dim, bytes per element) of a call that runs on the tile kernel."""
+    """(problems, queries, keys, head dim, bytes per element) of a call that the short or the tile kernel takes."""
     kind, T, S, L, H, D, dtype = shape
     return {0: (T * H, S, S), 1: (S * H, T, T), 2: (H, T * S, L)}[kind] + (D, 2 if dtype == "bf16" else 4)
 
@@ -165,26 +165,32 @@ def test_text_projection_rides_beside_the_tile_heights_too(plan):
 
 
 def test_split_shapes_are_split(plan):
-    part = {(0, 7, 700, 0, 12, 72, "bf16"): 4, (0, 9, 513, 0, 11, 32, "f32"): 19}
+    part = {(0, 7, 700, 0, 12, 72, "bf16"): 4, (0, 9, 513, 0, 11, 32, "f32"): 19, (0, 5, 1124, 0, 12, 32, "bf16"): 12, (0, 4, 2866, 0, 6, 32, "bf16"): 8}
     calls = [items_of(shape) for shape in P.SPLIT_SHAPES]
+    assert [r[0] for r in plan("short", calls)] == [0] * len(calls)      # the dispatch asks this first
     for shape, (n_bh, sq, *_), (n_item, bh_plain, n_split) in zip(P.SPLIT_SHAPES, calls, plan("items", calls)):
         assert n_bh - bh_plain == part.get(shape, n_bh) and n_split == -(-sq // 64), shape
+    assert all(r[0] for r in plan("short", [items_of(shape) for shape in P.SHORT_SPLITS]))
 
 
 # problems, queries, keys, head dim, bytes per element: calls that split items make slower, and such that they make faster
 # (the figures are at the rule)
-PLAIN = [(117, 755, 755, 72, 2), (208, 284, 284, 72, 2), (84, 912, 912, 72, 2), (110, 677, 677, 72, 2), (13, 6045, 600, 72, 2),
-         (48, 512, 512, 72, 2), (32, 1590, 1590, 72, 4), (16, 128, 128, 72, 2), (1, 10401, 10401, 72, 4), (10, 6103, 448, 72, 4),
-         (9, 7273, 7273, 72, 4), (10, 11634, 11634, 72, 4), (42, 1600, 1600, 72, 4), (224, 562, 562, 72, 2), (210, 271, 271, 32, 2), (340, 229, 229, 32, 2),
+PLAIN = [(117, 755, 755, 72, 2), (84, 912, 912, 72, 2), (110, 677, 677, 72, 2), (13, 6045, 600, 72, 2), (32, 1590, 1590, 72, 4),
+         (10, 6103, 448, 72, 4), (9, 7273, 7273, 72, 4), (10, 11634, 11634, 72, 4), (42, 1600, 1600, 72, 4), (224, 562, 562, 72, 2), (340, 229, 229, 32, 2),
          (9, 6384, 274, 32, 4), (33, 2481, 2481, 32, 4), (256, 1024, 1024, 72, 2), (256, 1590, 1590, 72, 2), (256, 3600, 3600, 72, 2)]
-SPLIT = [(16, 1024, 1024, 72, 2), (16, 300, 300, 72, 2), (40, 252, 252, 72, 2), (32, 1024, 1024, 72, 2), (72, 1024, 1024, 72, 2),
+SPLIT = [(16, 1024, 1024, 72, 4), (6, 3600, 3600, 72, 2), (72, 1024, 1024, 72, 2), (66, 788, 788, 72, 2), (136, 1000, 1000, 72, 2),
          (84, 700, 700, 72, 2), (40, 3600, 3600, 72, 2), (204, 1024, 1024, 72, 2), (91, 3066, 3066, 72, 4), (272, 1024, 1024, 72, 2),
          (24, 2871, 2871, 72, 2), (10, 4640, 4640, 72, 2), (24, 2866, 2866, 32, 2), (60, 1124, 1124, 32, 2), (42, 1711, 1711, 72, 2)]
+# ... and such that the short kernel takes before the rule is asked
+PLAIN_SHORT = [(208, 284, 284, 72, 2), (48, 512, 512, 72, 2), (16, 128, 128, 72, 2), (1, 10401, 10401, 72, 4), (210, 271, 271, 32, 2)]
+SPLIT_SHORT = [(16, 1024, 1024, 72, 2), (16, 300, 300, 72, 2), (40, 252, 252, 72, 2), (32, 1024, 1024, 72, 2)]
 
 
 def test_split_items_where_they_pay(plan):
-    assert [p[2] for p in plan("items", PLAIN)] == [0] * len(PLAIN)
-    assert all(p[2] > 0 for p in plan("items", SPLIT))
+    assert [p[2] for p in plan("items", PLAIN + PLAIN_SHORT)] == [0] * len(PLAIN + PLAIN_SHORT)
+    assert all(p[2] > 0 for p in plan("items", SPLIT + SPLIT_SHORT))
+    assert [p[0] for p in plan("short", PLAIN + SPLIT)] == [0] * len(PLAIN + SPLIT)
+    assert all(p[0] for p in plan("short", PLAIN_SHORT + SPLIT_SHORT))
     # never more than three split items per CU on any of the eight XCDs, which take every eighth problem each
     shapes = [(n, s, k, D, size) for n in list(range(1, 40)) + [64, 91, 105, 256, 999] for s in (1, 64, 225, 300, 1000, 4000, 20000)
               for k in (1, 200, 500, 1024, 9000) for D in (32, 72) for size in (2, 4)]
@@ -199,9 +205,7 @@ def test_short_launches(plan):
     assert got == [22] * 7 + [44] * 8 + [42] * 6 + [41]
     calls = [items_of(shape) for shape in P.TILE_SHAPES]
     assert [r[0] for r in plan("short", calls)] == [0] * len(calls)
-    split = [n_split > 0 for _, _, n_split in plan("items", calls)]
-    rows = plan("rows", [(n, sq, s[4] * (s[2] if s[0] == 1 else 1) * D * size) for s, (n, sq, _, D, size) in zip(P.TILE_SHAPES, calls)])
-    assert split[:3] == [True] * 3 and [r[0] for r in rows] == [1] * 3 + [0] * 3
+    assert [bh_plain > 0 for _, bh_plain, _ in plan("items", calls)] == [True, False] + [True] * (len(calls) - 2)
     # both sides of the line: problems, queries, keys, head dim, bytes per element
     short = [(96, 256, 256, 72, 2), (40, 700, 700, 72, 2), (192, 290, 290, 72, 2), (256, 225, 225, 72, 2), (72, 462, 462, 72, 2),
              (400, 150, 150, 72, 2), (12, 1590, 1590, 72, 2), (180, 256, 256, 32, 2), (12, 2400, 2400, 32, 2), (143, 129, 129, 32, 4),
@@ -249,9 +253,13 @@ def test_order_of_stores(plan):
     accumulated = [(1600, 34, 230400), (925, 50, 133200), (925, 72, 133200), (1000, 96, 1440), (10 ** 6, 48, 2304)]
     in_rows = [(5005, 80, 720720), (1480, 96, 213120), (256, 400, 2304), (2100, 49, 302400), (4, 129, 720)]
     assert [r[0] for r in plan("rows", accumulated + in_rows)] == [0] * 5 + [1] * 5
-    for D, size in ((72, 2), (72, 4), (32, 2), (32, 4)):      # the GPU test has both, whatever head dim and type
-        calls = [(items_of((*s, D, ""))[:2], s[4] * (s[2] if s[0] == 1 else 1) * D * size) for s in P.FEW_QUERIES]
-        assert {r[0] for r in plan("rows", [(n, sq, pitch) for (n, sq), pitch in calls])} == {0, 1}
+    # the GPU test has both orders for either type and head dim, on the tile kernel
+    calls = [items_of(s[:7]) for s in P.FEW_QUERIES]
+    assert [r[0] for r in plan("short", calls)] == [0] * len(calls)
+    pitches = [s[4] * (s[2] if s[0] == 1 else 1) * D * size for s, (*_, D, size) in zip(P.FEW_QUERIES, calls)]
+    assert [r[0] for r in plan("rows", [(n, sq, pitch) for (n, sq, *_), pitch in zip(calls, pitches)])] == [s[7] for s in P.FEW_QUERIES]
+    assert {s[5:] for s in P.FEW_QUERIES} == {(D, t, o) for D in (72, 32) for t in ("bf16", "f32") for o in (False, True)}
+    assert all(r[0] for r in plan("short", [items_of(s) for s in P.SHORT_FEW_QUERIES]))
 
 
 def test_one_round_of_large_small_tiles(plan):
