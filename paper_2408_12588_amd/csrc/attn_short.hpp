@@ -8,13 +8,13 @@
 // its K and V tiles into LDS of its own (the next K while the softmax runs, the next V at the end of the step) and meets the
 // other key groups of its query tile at one barrier, behind which all of them take a share of the rows: partial sums with the
 // denominator and the maximum beside them, read, weighed, added and stored 16 bytes per lane in row order.
-// 10.3 -> 7.2 us there; 4 frames of 128 tokens and 8 heads 7.0 -> 4.4, 4 of 500 and 8 13.1 -> 9.8, 4 of 64 and 4 (heads of
-// 32, fp32) 4.3 -> 3.0, 48 frames at 1590 positions, 16 heads 350 -> 166, cross attention of 1000 tokens and 8 heads to 300 keys
-// 16.3 -> 6.2.
+// 10.3 -> 6.9 us there; 4 frames of 128 tokens and 8 heads 7.0 -> 4.1, 4 of 500 and 8 13.1 -> 9.5, 4 of 64 and 4 (heads of
+// 32, fp32) 4.3 -> 2.8, 48 frames at 1590 positions, 16 heads 350 -> 166, cross attention of 1000 tokens and 8 heads to 300 keys
+// 16.3 -> 6.1.
 //
-// The price is that a K/V tile serves 32 queries instead of 256: with many query tiles the copies (about 200 cache lines per
-// tile and head, 64 bytes per clock and CU) take longer than the arithmetic.  plan_short and
-// plan_short_cross in launch_plan.hpp have the lines.
+// The price is that a K/V tile serves 32 queries instead of 256: with many query tiles the copies take longer than the arithmetic.
+// 64 rows of 144 bytes are 129 cache lines as counted; 9 frames of 462 tokens and 8 heads (17.2 us) draw 61 GB/s per CU, all that L2
+// gives when every CU asks, 5 of 252 only 26.  plan_short and plan_short_cross in launch_plan.hpp have the lines.
 #pragma once
 #include "attn_short_layout.hpp"
 #include "mfma_util.hpp"
@@ -304,7 +304,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? 2 : 4) void attn_short_ke
     const int row = i / CH, ch = i - row * CH;
     if (i < 32 * CH && q0 + row < sq) {
       const float *src = first + row * OP;
-          f32x2_t lm[G];
+      f32x2_t lm[G];
       f32x4 xa[G], xb[G];
       float m_all = -INFINITY;
 #pragma unroll

@@ -60,7 +60,8 @@ struct GemmParams {
   bf16_t *C2;
   int M2, N2, n_nt2, n_units2;
   int ms2;              // gemm_stream: token rows / 64 of its tiles
-  // GEMM_NORM (gemm_stream: heads of 72, gemm_tile: of 32) and gemm_heads (query / key / value projection): layernorm over the head dimension of planes 0 and 1, then the rotation
+  // GEMM_NORM (gemm_stream: heads of 72, gemm_tile: of 32) and gemm_heads, the query / key / value projection: layernorm over the head
+  // dimension of planes 0 and 1, then the rotation
   const bf16_t *gq, *bq, *gk, *bk;   // [head dim] scale and shift for q and for k
   int S, rope;          // tokens per frame (frame index = token / S); 1: rotate by the frame index (gemm_stream: S >= 64)
   unsigned S_magic;     // gemm_tile: 2^32 / S, at most 2^32 - 1

@@ -19,19 +19,20 @@ struct ItemPlan {
 // takes every eighth (batch, head) problem and has TILE_CUS CUs; workgroups take about the same time, so an XCD's time
 // steps up where its workgroups pass a multiple of TILE_CUS, by half with the second workgroup of a CU (S = 1024, 16 heads:
 // 29.0 us with 24 per XCD, 43.3 with 36), by a whole one with the third.  The problems beyond the last multiple are split,
-// all of them if there is none, where the XCD with the most of their items has no more than
-//   one per CU (16 problems of 1024 tokens 26.3 -> 16.1 us, 16 of 300 11.9 -> 10.8, 72 of 1024 43.3 -> 32.3, 84 of 700
-//     31.6 -> 25.0), from 8 key tiles: with fewer the combination costs more (16 of 128: 7.0 -> 8.8);
-//   after an even multiple, where they would wait for a whole round: two per CU for long sequences (32 of 1024
-//     27.3 -> 23.8, 40 of 3600 202 -> 192; but 48 of 512 17.0 -> 17.6);
+// all of them if there is none (most of those launches are plan_short's, which is asked first), where the XCD with the most of their
+// items has no more than
+//   one per CU (72 problems of 1024 tokens 44.1 -> 32.8 us, 66 of 788 35.4 -> 26.0, 84 of 700 32.0 -> 25.0, 16 of 1024 with fp32 rows
+//     40.0 -> 25.1), from 8 key tiles: with fewer the combination costs more than the steps that it saves;
+//   after an even multiple, where they would wait for a whole round: two per CU for long sequences (6 of 3600 79.6 -> 50.1, 136 of
+//     1000 67.6 -> 58.4, 40 of 3600 204 -> 193, 16 of 1100 with fp32 rows 40.5 -> 34.5; but 48 of 512, from before there was the short
+//     kernel, 17.0 -> 17.6);
 //   after an odd one, where they would run beside the others: two or three per CU for longer ones still, whose items are
 //     cheaper (24 of 2871, 45 items per XCD, 101 -> 77, 10 of 4640, 73 items, 157 -> 136; but 84 of 912, 45 items, 39.8 -> 47.3,
 //     110 of 677 34.0 -> 40.0); with fp32 rows, which are converted on the way in by four times as many items, fewer (heads of
 //     32: 33 of 2481, 80 items, 80 -> 84; of 72: 32 of 1984, 50 items, 82 -> 89).
 // Failing that, those over the last full round of two workgroups per CU, if that is at most a quarter round (91 of 3066, fp32:
 // 499 -> 472; but 224 of 562 with 160 workgroups over 41.0 -> 45.8).
-// More items than that only lose, on one XCD too: 1 problem of 10401 (fp32) 439 -> 619 with 163 items, 10 of 6103 queries and
-// 448 keys (fp32) 33 -> 50 with 96.  752 shapes (heads of 32 and 72, both types, 1 .. 2800 problems): 0.89 of the time of
+// More items than that only lose: 10 of 6103 queries and 448 keys (fp32) 33 -> 50 with 96 on an XCD.  752 shapes (heads of 32 and 72, both types, 1 .. 2800 problems): 0.89 of the time of
 // the former rule (a rest of at most a quarter of the last round, 16 key tiles); none that is split is slower by more than 3 %.
 inline ItemPlan plan_items(long long n_bh, int sq, int sk, int head_dim, int elem_size) {
   constexpr int QBLK = 32 * TILE_NWV;
@@ -100,7 +101,8 @@ inline int plan_short(long long n_bh, int sq, int sk, int head_dim, int elem_siz
   long long most;
   const auto at_most = [&](bool where, long long n) { if (where) most = std::min(most, n); };
   if (elem_size == 2) {
-    most = clip ? n_blocks : per_xcd > 2 * TILE_CUS ? 0 : per_xcd > TILE_CUS ? 2000 : !wide || one ? 2048 : ntile <= 24 ? 1320 : ntile <= 80 ? 1200 : 1080;
+    most = clip ? n_blocks : per_xcd > 2 * TILE_CUS ? 0 : per_xcd > TILE_CUS ? 2000 : !wide || one ? 2048 : ntile <= 24 ? 1320
+                                                                                               : ntile <= 80 ? 1200 : 1080;
     at_most(wide && one && ntile == 7 && per_xcd <= TILE_CUS, 1300);
     at_most(wide && part_split && ntile >= 13, ntile <= 16 ? 1900 : 1500);
     at_most(!wide && ntile >= 7 && 10 * n_bh >= 64 * xcd_bh && (per_xcd <= TILE_CUS || (part_split && ntile > 16)), 1550);
@@ -131,9 +133,10 @@ inline int plan_short_cross(int n_tok, int L, int n_head, int head_dim) {
 
 // Whether the tile kernel moves its results to row order on the way out (store_rows16) or stores them as accumulated.  With few
 // queries most of the eight wavefronts are idle and nothing covers the way through the LDS crossbar; it pays in larger launches,
-// the sooner where pieces of a row start on 64-byte boundaries.  As accumulated -> in row order, us: 34 frames at 200 positions,
-// 8 heads 19.5 -> 20.5, 50 at 185, 5 heads 12.6 -> 13.6, 72 at 185, 5 heads 16.4 -> 17.0, 100 frames of 96 tokens, 10 heads 20.5 -> 21.0;
-// but 80 at 1001, 5 heads 69.9 -> 66.8, 96 at 185, 8 heads 29.3 -> 27.3, 16 frames of 400 tokens, 16 heads 27.6 -> 25.6.
+// the sooner where pieces of a row start on 64-byte boundaries.  As accumulated -> in row order, us: up to 48 queries (fp32 rows: others
+// of so few are plan_short's) 34 frames at 440 positions, 3 heads 22.4 -> 23.4, 36 at 900, 4 heads 51.8 -> 53.3, 48 at 1590, 16 heads
+// 467 -> 470; more of them 72 at 185, 5 heads 16.5 -> 17.1, 100 frames of 96 tokens, 10 heads 20.3 -> 21.0, but 49 at 700, 3 heads (fp32)
+// 38.6 -> 37.9, 80 at 1001, 5 heads 70.6 -> 67.2, 96 at 185, 8 heads 29.2 -> 27.4, 16 frames of 400 tokens, 16 heads 28.3 -> 26.2.
 inline bool store_in_row_order(long long n_bh, int sq, long long row_pitch_bytes) {
   if (sq <= 48) return false;
   return sq > 128 || n_bh > 2048 || (sq > 64 && row_pitch_bytes % 64 == 0);
@@ -317,8 +320,8 @@ inline PairPlan plan_pair(int M, int N, int M2, int N2, int K) {
 // q, k, v projections of a self-attention module with layernorm2 (+ rotation) of q and k, whichever is estimated fastest:
 //   the best plain projection and a pass over q and k (each read and written once at 4.8 TB/s, 3 us at least);
 //   heads of 72: in the epilogue of the large-tile projection (it costs a tile 3 us);
-//   in the epilogue of small tiles: heads of 72, few tokens, one tile of two heads and 64 or 128 tokens per CU: gemm_heads; heads of 32, which are a
-//   pair of sub-tiles: gemm_tile (it costs a launch 0.8 us and a round of tiles as much; whole modules in us, pass -> epilogue:
+//   in the epilogue of small tiles: heads of 72, few tokens, one tile of two heads and 64 or 128 tokens per CU: gemm_heads; heads of
+//   32, which are a pair of sub-tiles: gemm_tile (it costs a launch 0.8 us and a round of tiles as much; whole modules in us, pass -> epilogue:
 //   2880 tokens of 256 24.0 -> 18.4, 3696 of 256 31.4 -> 25.3, 29715 of 384 98.9 -> 90.8, 38288 of 512 428 -> 417; gemm_heads,
 //   three heads per tile, took 13.8 at 189 of 128 where this takes 12.7, 14.0 -> 12.9 at 282 of 128).
 enum { QKV_PASS = 0, QKV_STREAM = 1, QKV_SMALL = 2 };
