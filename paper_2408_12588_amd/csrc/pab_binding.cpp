@@ -3,7 +3,8 @@
 // Small launches are bound by the host: a reused call, which launches nothing, took 1.75 us from Python, of which the library
 // took 0.1: 0.55 for the pointers of three tensors, 0.3 for the stream, 0.45 for ctypes, the rest for the steps in between.
 // (With it: a reused call 0.37, an operation of its own 5.8 - 6.2 -> 3.1 - 3.7 with its launch, a run of 60 calls over a tiny model
-// 211 - 228 -> 121 - 145, three machines, each without and with it.)  Here plain torch tensors are looked at through torch's own C++ interface and the library is called directly.  Whatever is not
+// 211 - 228 -> 121 - 145, three machines, each without and with it.)
+// Here plain torch tensors are looked at through torch's own C++ interface and the library is called directly.  Whatever is not
 // a plain dense device tensor or a plain number goes back to the Python code (NotImplemented), which has the same checks and
 // raises the errors.
 #include <torch/csrc/autograd/python_variable.h>
